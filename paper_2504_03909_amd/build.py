@@ -23,7 +23,8 @@ COMMON = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-result", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}",
 ]
-SOURCES = ["he_kernels.hip", "he_api.cpp", "ckks.hip"]
+SOURCES = ["he_kernels.hip", "he_api.cpp", "ckks.hip", "pow_lane32.hip", "pow_twin32.hip", "pow_lane16.hip",
+           "pow_group.hip"]
 
 
 def hipcc() -> str:

@@ -57,6 +57,13 @@ he::DExp mk_exp(const uint32_t *base, const hekey::ExpOff &o) {
   return he::DExp{base + o.e, o.nwin, base + o.ops, o.nops};
 }
 
+he::DPair mk_pair(const uint32_t *base, const hekey::PairOff &o) {
+  he::DPair d{};
+  for (int v = 0; v < he29::kPairVariants; ++v) d.c[v] = base + o.c[v];
+  d.ninv = o.ninv;
+  return d;
+}
+
 // Builds every constant of the key and uploads them to the current device.
 int build_key(he_key *k) {
   const hekey::KeyConsts kc = hekey::derive(k->n_bits, k->n, k->p, k->q, k->priv);
@@ -75,6 +82,7 @@ int build_key(he_key *k) {
   d.has_priv = k->priv;
   d.n = mk_mod(base, on);
   d.n2 = mk_mod(base, on2);
+  d.pair_n = mk_pair(base, kc.pair_n);
   d.e_n = mk_exp(base, oe);
   d.nR_n2 = base + o_nR;
   d.half = base + o_half;
@@ -84,10 +92,11 @@ int build_key(he_key *k) {
       he::DPrime &P = d.pr[w];
       P.P = mk_mod(base, po[w]->P);
       P.P2 = mk_mod(base, po[w]->P2);
+      P.pair = mk_pair(base, po[w]->pair);
       P.e_enc = mk_exp(base, po[w]->e_enc);
       P.e_lift = mk_exp(base, po[w]->e_lift);
       P.e_dec = mk_exp(base, po[w]->e_dec);
-      P.QR_P = base + po[w]->QR_P;
+      P.QR2_P = base + po[w]->QR2_P;
       P.PR_P2 = base + po[w]->PR_P2;
       P.Pinv = base + po[w]->Pinv;
       P.hR_P = base + po[w]->hR_P;
@@ -180,11 +189,18 @@ int ensure(Buf &b, size_t bytes, hipStream_t s) {
 // exponentiations per (device, key size, kind, count class), filled by
 // he_crt_autotune; count class = bit length of the count.
 struct PowShape {
-  int G = 0, waves = 0;  // waves 0: the kernel's own occupancy
+  int G = 0, waves = 0;  // G 0: the default plan; waves 0: the kernel's own occupancy
   int tailG = 0;         // lanes per integer of the last partial round's launch (0: no separate launch)
 };
 std::mutex g_pow_mu;
 std::map<std::tuple<int, int, int, int>, PowShape> g_pow_tuned;
+
+// The widths he_crt_set_shape and the remainder's launch are named by.
+bool pow_shape_named(int KP, int kind, int G) {
+  const int S32 = kind == 4 ? 16 * KP : (kind == 1 ? 64 * KP : 32 * KP);
+  return (G == 2 || G == 4 || G == 8 || G == 16) &&
+         (S32 == 16 || S32 == 32 || (S32 == 64 && G != 2) || (S32 == 128 && G >= 8));
+}
 
 int count_class(uint64_t count) {
   int b = 0;
@@ -195,36 +211,13 @@ int count_class(uint64_t count) {
   return b;
 }
 
-// 32-bit limbs of the modulus of an exponentiation of `kind`: 4 mod P, 0
-// and 2 mod P^2, 1 (public key) mod n^2.
-int pow_s32(int KP, int kind) { return kind == 4 ? 16 * KP : (kind == 1 ? 64 * KP : 32 * KP); }
-
 he::PowLaunch pow_launch_at(int KP, int kind, uint64_t count, PowShape sh) {
-  const int S32 = pow_s32(KP, kind);
-  if (sh.G == 0 || !he::pow_shape_valid(S32, sh.G)) sh = PowShape{he::pick_group(KP, kind, count), 0};
-  const uint32_t dyn = he::pow_dyn_lds(S32, sh.G, sh.waves);
+  const uint32_t dyn = he::pow_dyn_lds(KP, kind, sh.G, sh.waves);
   const uint64_t per_wave = 64 / sh.G;
   const uint64_t work_blocks = (2 * ((count + per_wave - 1) / per_wave) + 3) / 4;
   const uint32_t grid =
-      (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(he::pow_resident_blocks(S32, sh.G, dyn), work_blocks));
+      (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(he::pow_resident_blocks(KP, kind, sh.G, dyn), work_blocks));
   return he::PowLaunch{sh.G, grid, dyn};
-}
-
-// The shape used when the autotuner has not run: pick_group's width, at the
-// kernel's own occupancy unless two waves per SIMD take as many rounds of
-// units (the resident waves each claiming one) to get through the batch.
-// Fewer waves per SIMD each run faster, so in that case they finish sooner.
-PowShape default_pow_shape(int KP, int kind, uint64_t count) {
-  const int S32 = pow_s32(KP, kind);
-  PowShape sh{he::pick_group(KP, kind, count), 0, 0};
-  const uint32_t dyn2 = he::pow_dyn_lds(S32, sh.G, 2);
-  if (dyn2 == 0) return sh;
-  const uint64_t per_wave = 64 / sh.G;
-  const uint64_t units = 2 * ((count + per_wave - 1) / per_wave);
-  const uint64_t w_own = 4ull * he::pow_resident_blocks(S32, sh.G, 0);
-  const uint64_t w_two = 4ull * he::pow_resident_blocks(S32, sh.G, dyn2);
-  if (w_two < w_own && (units + w_two - 1) / w_two == (units + w_own - 1) / w_own) sh.waves = 2;
-  return sh;
 }
 
 // The launches of shape `sh` over `count` ciphertexts.  With sh.tailG, the
@@ -236,8 +229,7 @@ PowShape default_pow_shape(int KP, int kind, uint64_t count) {
 // round or no remainder.
 he::PowPlan pow_plan_at(int KP, int kind, uint64_t count, PowShape sh) {
   he::PowPlan p{pow_launch_at(KP, kind, count, sh), count, he::PowLaunch{0, 0, 0}};
-  const int S32 = pow_s32(KP, kind);
-  if (sh.tailG == 0 || sh.tailG == p.main.G || !he::pow_shape_valid(S32, sh.tailG)) return p;
+  if (sh.tailG == 0 || sh.tailG == p.main.G || !he::pow_shape_valid(KP, kind, sh.tailG)) return p;
   const uint64_t per_wave = 64 / p.main.G;
   const uint64_t units = 2 * ((count + per_wave - 1) / per_wave);
   const uint64_t waves = 4ull * p.main.grid;
@@ -255,11 +247,70 @@ uint64_t plan_table_bytes(int KP, int kind, const he::PowPlan &p) {
   return b;
 }
 
+// Launch plan of an exponentiation no shape was tuned or pinned for.  A wave
+// on a SIMD of its own issues nearly as fast as two, so a launch's time is
+// first + (n - 1) more, n the waves the fullest SIMD gets: `first` is one wave
+// alone (for wide groups the latency of their steps), `more` what each further
+// wave adds once latencies are covered.  Narrow groups need fewer instructions
+// per integer (more / 64 G falls with G), wide ones fill the device with fewer
+// integers and leave a smaller last wave.  Tried: every width for the whole
+// count, and every width for as many whole waves per SIMD as the count holds
+// with the rest in a second launch at a wider one.
+// The constants are milliseconds measured at one and at several waves per
+// SIMD (MI355X, about 2.15 GHz under this load); only their ratios matter.
+// E.g. 200,000 lifts at 2048 bits: 81 ms for 196,608 at one lane and 3.3 ms for
+// the rest at 8 lanes, against 90 ms in one launch and 105 ms at 8 lanes.
+struct PowCost {
+  int G;
+  double first, more;
+};
+const std::vector<PowCost> &pow_costs(int KP, int kind) {
+  static const std::vector<PowCost> mod16 = {{1, .87, .83}, {2, .88, .59}, {4, .63, .37}, {8, .745, .34}, {16, 1.13, .37}};
+  static const std::vector<PowCost> mod32 = {{1, 5.65, 5.85}, {2, 3.8, 2.9}, {4, 2.55, 1.73}, {8, 2.33, 1.32}, {16, 2.6, 1.15}};
+  static const std::vector<PowCost> pair16 = {{1, 2.03, 1.85}, {2, 1.29, 1.0}, {4, .88, .58}, {8, .80, .41}, {16, .866, .39}};
+  static const std::vector<PowCost> pair32 = {{1, 14.1, 13.5}, {2, 8.0, 7.4}, {4, 5.1, 3.9}, {8, 3.25, 2.16}, {16, 2.86, 1.62}};
+  static const std::vector<PowCost> pair64 = {{8, 19.2, 13.3}, {16, 12.45, 8.1}};
+  if (kind == 4) return KP == 1 ? mod16 : mod32;
+  if (kind == 1) return KP == 1 ? pair32 : pair64;
+  return KP == 1 ? pair16 : pair32;
+}
+
+he::PowPlan default_pow_plan(int KP, int kind, uint64_t count) {
+  const uint64_t simds = 4ull * (uint64_t)he::device_cus();
+  auto waves = [](int G, uint64_t n) { return 2 * ((n + 64 / G - 1) / (64 / G)); };
+  auto cost = [&](const PowCost &c, uint64_t n) {
+    return c.first + (double)((waves(c.G, n) + simds - 1) / simds - 1) * c.more;
+  };
+  double best = 1e300;
+  int G = 16, tailG = 0;
+  uint64_t main_count = count;
+  for (const PowCost &c : pow_costs(KP, kind)) {
+    if (cost(c, count) < best) {
+      best = cost(c, count);
+      G = c.G;
+      tailG = 0;
+      main_count = count;
+    }
+    const uint64_t whole = waves(c.G, count) / simds * simds / 2 * (64 / c.G);
+    if (whole == 0 || whole >= count) continue;
+    for (const PowCost &t : pow_costs(KP, kind)) {
+      if (t.G <= c.G || cost(c, whole) + cost(t, count - whole) >= best) continue;
+      best = cost(c, whole) + cost(t, count - whole);
+      G = c.G;
+      tailG = t.G;
+      main_count = whole;
+    }
+  }
+  he::PowPlan p{pow_launch_at(KP, kind, main_count, PowShape{G, 0, 0}), main_count, he::PowLaunch{0, 0, 0}, nullptr};
+  if (tailG) p.tail = pow_launch_at(KP, kind, count - main_count, PowShape{tailG, 0, 0});
+  return p;
+}
+
 // The launches of an exponentiation over `count` ciphertexts (units): the
-// tuned shape for its class if the autotuner ran, else default_pow_shape's
-// (one launch).
+// tuned or pinned shape for its class if there is one (G 0: the autotuner found
+// none faster than the default plan), else default_pow_plan's.
 he::PowPlan pow_plan(int KP, int kind, uint64_t count) {
-  PowShape sh = default_pow_shape(KP, kind, count);
+  PowShape sh;
   int dev = 0;
   (void)hipGetDevice(&dev);
   {
@@ -267,7 +318,7 @@ he::PowPlan pow_plan(int KP, int kind, uint64_t count) {
     auto it = g_pow_tuned.find({dev, KP, kind, count_class(count)});
     if (it != g_pow_tuned.end()) sh = it->second;
   }
-  return pow_plan_at(KP, kind, count, sh);
+  return sh.G ? pow_plan_at(KP, kind, count, sh) : default_pow_plan(KP, kind, count);
 }
 
 // m == nullptr encrypts zeros (the obfuscators r^n mod n^2).
@@ -303,8 +354,8 @@ int encrypt_impl(const he_key *key, const int64_t *m, uint64_t count, const uint
     rc = ensure(w->ctr, 256, stream);
     if (rc) return rc;
     p.ctr = (uint32_t *)w->ctr.p;
-    // r mod n^2, then r^n mod n^2 in place: count + (count & 1) rows of 2L limbs
-    rc = ensure(w->tmp, (count + 1) * 2 * L * sizeof(uint32_t), stream);
+    // r mod n, then r^n mod n^2: count + (count & 1) rows of L and of 2L limbs
+    rc = ensure(w->tmp, (count + 1) * 3 * L * sizeof(uint32_t), stream);
     if (rc) return rc;
     HE_TRY_HIP(he::launch_enc_pub(KP, key->dk, m, count, r, r_seed, r_offset, (uint32_t *)w->tmp.p, ct,
                                   (uint32_t *)w->tab.p, p, stream));
@@ -501,7 +552,7 @@ int he_decrypt(const he_key *key, const uint32_t *ct, uint64_t count, int64_t *m
   rc = ensure(w->ctr, 256, stream);
   if (rc) return rc;
   p.ctr = (uint32_t *)w->ctr.p;
-  // c mod P^2, then c^(P-1) mod P^2, per (ciphertext, prime): 2L limbs per ciphertext
+  // c^(P-1) mod P^2 per (ciphertext, prime): 2L limbs per ciphertext
   rc = ensure(w->tmp, count * 2 * L * sizeof(uint32_t), stream);
   if (rc) return rc;
   HE_TRY_HIP(he::launch_dec(KP, key->dk, ct, count, (uint32_t *)w->tmp.p, m, raw, n_overflow,
@@ -564,11 +615,18 @@ int he_decrypt_noalloc(const he_key *key, const uint32_t *ct, uint64_t count, in
   int rc = scratch_address(&base);
   if (rc) return rc;
   const size_t xpq_bytes = (count * 2 * L * sizeof(uint32_t) + 255) / 256 * 256;
-  // one launch whose grid is cut to the tables the scratch holds
-  he::PowLaunch l = pow_plan(KP, 2, count).main;
-  const uint64_t fit = (kNoAllocBytes - xpq_bytes) / he::table_bytes_per_block(KP, 2, l.G);
-  if (fit == 0) return fail(HE_ERR_ARG, "he_decrypt_noalloc: no room for one block's window tables");
-  l.grid = (uint32_t)std::min<uint64_t>(fit, l.grid);
+  // One launch whose grid is cut to the tables the scratch holds, at the
+  // narrowest width that still puts a wave on every SIMD (a table holds as
+  // many integers at every width, so wider groups mean more waves).
+  const uint64_t cus = (uint64_t)he::device_cus();
+  he::PowLaunch l{};
+  for (int G : {2, 4, 8, 16}) {
+    l = pow_launch_at(KP, 2, count, PowShape{G, 0, 0});
+    const uint64_t fit = (kNoAllocBytes - xpq_bytes) / he::table_bytes_per_block(KP, 2, G);
+    if (fit == 0) return fail(HE_ERR_ARG, "he_decrypt_noalloc: no room for one block's window tables");
+    l.grid = (uint32_t)std::min<uint64_t>(fit, l.grid);
+    if (l.grid >= cus) break;
+  }
   uint32_t *xpq = (uint32_t *)base;
   uint32_t *tab = (uint32_t *)((char *)base + xpq_bytes);
   // static units: no work counter in the scratch
@@ -954,14 +1012,14 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   const uint64_t n_ct = std::max(enc_count, dec_count);
   int dev = 0;
   HE_TRY_HIP(hipGetDevice(&dev));
-  // trial buffers: r mod P / t, omega, ciphertexts, c mod P^2, window tables,
-  // work counters
+  // trial buffers: r mod P / t, omega, ciphertexts, their powers, window
+  // tables, work counters
   DevBuf tq, cpq, ct, xpq, tab, ctr;
   size_t tab_bytes = 0;
   for (int kind : {4, 0, 2})
-    for (int G : {2, 4, 8, 16})
-      if (he::pow_shape_valid(pow_s32(KP, kind), G))
-        tab_bytes = std::max<size_t>(tab_bytes, (size_t)he::pow_resident_blocks(pow_s32(KP, kind), G, 0) *
+    for (int G : {1, 2, 4, 8, 16})
+      if (he::pow_shape_valid(KP, kind, G))
+        tab_bytes = std::max<size_t>(tab_bytes, (size_t)he::pow_resident_blocks(KP, kind, G, 0) *
                                                    he::table_bytes_per_block(KP, kind, G));
   const size_t sizes[6] = {n_ct * L * 4, n_ct * 2 * L * 4, n_ct * 2 * L * 4, n_ct * 2 * L * 4, tab_bytes, 256};
   DevBuf *bufs[6] = {&tq, &cpq, &ct, &xpq, &tab, &ctr};
@@ -972,12 +1030,10 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
     }
   uint32_t *tq_p = (uint32_t *)tq.p, *cpq_p = (uint32_t *)cpq.p, *ct_p = (uint32_t *)ct.p,
            *xpq_p = (uint32_t *)xpq.p, *tab_p = (uint32_t *)tab.p;
-  const uint32_t SP = 16 * KP, SP2 = 32 * KP;
-  // real operands: r mod P, one encryption (default shapes), c mod P^2
+  // real operands: r mod P, one encryption (default shapes)
   HE_TRY_HIP(he::launch_enc_r(KP, key->dk, enc_count, nullptr, 1, 0, tq_p, stream));
   int rc = encrypt_impl(key, nullptr, n_ct, nullptr, 1, 0, ct_p, stream, false);
   if (rc) return rc;
-  HE_TRY_HIP(he::launch_dec_pre(KP, key->dk, ct_p, dec_count, xpq_p, stream));
   hipEvent_t e0, e1;
   HE_TRY_HIP(hipEventCreate(&e0));
   HE_TRY_HIP(hipEventCreate(&e1));
@@ -990,9 +1046,8 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
     auto trial = [&](const PowShape &sh, he::PowPlan p) -> int {
       p.ctr = (uint32_t *)ctr.p;
       auto run = [&]() -> hipError_t {
-        if (kind == 4) return he::launch_pow_kind(KP, key->dk, 4, tq_p, SP, SP, tq_p, SP, count, tab_p, p, stream);
-        if (kind == 0) return he::launch_pow_kind(KP, key->dk, 0, tq_p, SP, SP, cpq_p, SP2, count, tab_p, p, stream);
-        return he::launch_pow_kind(KP, key->dk, 2, xpq_p, SP2, SP2, xpq_p, SP2, count, tab_p, p, stream);
+        return he::launch_pow_kind(KP, key->dk, kind, kind == 2 ? ct_p : tq_p, kind == 4 ? tq_p : (kind == 0 ? cpq_p : xpq_p),
+                                   count, tab_p, p, stream);
       };
       float ms = 0;
       const int r = time_ms(run, stream, e0, e1, &ms);
@@ -1006,8 +1061,8 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
     // lanes per integer and waves per SIMD in one launch, then, at the best
     // of those, a separate launch for the last partial round at each wider
     // group
-    for (int G : {2, 4, 8, 16}) {
-      if (!he::pow_shape_valid(pow_s32(KP, kind), G)) continue;
+    for (int G : {1, 2, 4, 8, 16}) {
+      if (!he::pow_shape_valid(KP, kind, G)) continue;
       for (int waves : {0, 3, 2}) {
         const PowShape sh{G, waves, 0};
         const he::PowPlan p = pow_plan_at(KP, kind, count, sh);
@@ -1016,9 +1071,12 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
       }
       if (rc) break;
     }
+    // the default plan, kept as such (its split follows the count)
     const PowShape one = best[t];
+    const he::PowPlan dp = default_pow_plan(KP, kind, count);
+    if (!rc) rc = trial(PowShape{}, dp);
     for (int tg : {4, 8, 16}) {
-      if (rc || tg <= one.G || !he::pow_shape_valid(pow_s32(KP, kind), tg)) continue;
+      if (rc || tg <= one.G || !he::pow_shape_valid(KP, kind, tg)) continue;
       const PowShape sh{one.G, one.waves, tg};
       const he::PowPlan p = pow_plan_at(KP, kind, count, sh);
       if (p.tail.G == 0) break;  // whole rounds only, or less than one: nothing to split
@@ -1036,9 +1094,10 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   }
   for (int t = 0; t < 3; ++t) {
     if (choice) {
-      choice[3 * t] = (uint32_t)best[t].G;
+      const he::PowPlan dp = default_pow_plan(KP, kinds[t], kinds[t] == 2 ? dec_count : enc_count);
+      choice[3 * t] = (uint32_t)(best[t].G ? best[t].G : dp.main.G);
       choice[3 * t + 1] = (uint32_t)best[t].waves;
-      choice[3 * t + 2] = (uint32_t)best[t].tailG;
+      choice[3 * t + 2] = (uint32_t)(best[t].G ? best[t].tailG : dp.tail.G);
     }
     if (ms_out) ms_out[t] = best_ms[t];
   }
@@ -1054,11 +1113,10 @@ extern "C" int he_crt_set_shape(const he_key *key, uint32_t kind, uint64_t count
   const int KP = kp_of(key), k = kind == 0 ? 4 : (kind == 1 ? 0 : (kind == 2 ? 2 : 1));
   // public-key encryption plans its exponentiation over unit pairs of two ciphertexts
   const uint64_t units = kind == 3 ? (count + 1) / 2 : count;
-  const int S32 = pow_s32(KP, k);
-  if (!he::pow_shape_valid(S32, (int)lanes))
+  if (!pow_shape_named(KP, k, (int)lanes))
     return fail(HE_ERR_ARG, "lanes " + std::to_string(lanes) + " not built for this kind and key size");
   if (waves != 0 && waves != 2 && waves != 3) return fail(HE_ERR_ARG, "waves must be 0 (own occupancy), 2 or 3");
-  if (tail_lanes != 0 && (tail_lanes <= lanes || !he::pow_shape_valid(S32, (int)tail_lanes)))
+  if (tail_lanes != 0 && (tail_lanes <= lanes || !pow_shape_named(KP, k, (int)tail_lanes)))
     return fail(HE_ERR_ARG, "tail_lanes must be 0 or a built width above lanes");
   int dev = 0;
   HE_TRY_HIP(hipGetDevice(&dev));

@@ -28,14 +28,41 @@ struct DExp {
   int nops;
 };
 
+// Constants of the two-digit form of residues mod N^2 (radix29.hpp), per
+// limb-count variant.
+struct DPair {
+  const uint32_t *c[he29::kPairVariants];
+  uint32_t ninv;  // -N^-1 mod 2^32
+};
+
+// Arguments of an exponentiation on the engines of pair29.hpp: unit (i, w)
+// reads its pieces at in + i in_i + w in_w and writes its digits at
+// out + i out_i + w out_w.
+struct PairPowArgs {
+  const uint32_t *consts[2];
+  uint32_t ninv[2];
+  DExp exp[2];
+  const uint32_t *in;
+  uint32_t *out;
+  uint32_t in_i, in_w, out_i, out_w;
+  int pieces;
+  uint64_t count;
+  uint32_t *tabs;
+  uint32_t *next;
+};
+// The kernel for a base of SN 32-bit limbs at L lanes per integer (0: one
+// residue mod N per lane), null if not built.
+const void *pow_pair_kernel(int SN, int L, bool ct);
+
 // Per-prime constants for the CRT paths; P is this prime, Q the other one.
 // S_P = L/2 limbs for P, S_P2 = L limbs for P^2 (L = limbs of n).
 struct DPrime {
   DMod P, P2;
+  DPair pair;
   DExp e_enc;        // Q mod (P - 1): r^Q mod P = r^(Q mod (P-1)) mod P
   DExp e_lift;       // P: x -> x^P mod P^2 depends only on x mod P
   DExp e_dec;        // P - 1: decryption exponent
-  const uint32_t *QR_P;   // Q R mod P          (S_P limbs)
+  const uint32_t *QR2_P;  // Q R^2 mod P        (S_P limbs)
   const uint32_t *PR_P2;  // P R' mod P^2       (S_P2 limbs)
   const uint32_t *Pinv;   // P^-1 mod 2^(32 S_P)
   const uint32_t *hR_P;   // h_P R mod P, h_P = L_P(g^(P-1) mod P^2)^-1 mod P
@@ -45,6 +72,7 @@ struct DKey {
   uint32_t n_bits;
   int has_priv;
   DMod n, n2;              // S_N = L, S_N2 = 2L limbs
+  DPair pair_n;
   DExp e_n;                // n as an exponent (public encryption)
   const uint32_t *nR_n2;   // n R'' mod n^2
   const uint32_t *half;    // (n + 1) / 2 (L limbs) for the signed decode
@@ -127,12 +155,13 @@ struct PowPlan {
   PowLaunch tail;
   uint32_t *ctr;
 };
-// tq: [count][2][S_P] (r mod P, then t in place), cpq: [count][2][S_P2].
+// tq: [count][2][S_P] (r mod P, then t in place), cpq: [count][2][S_P2] (omega
+// as two digits base P).
 hipError_t launch_enc_crt(int KP, const DKey &k, const int64_t *m, uint64_t count, const uint32_t *r, uint64_t seed,
                           uint64_t roff, uint32_t *tq, uint32_t *cpq, uint32_t *ct, uint32_t *tab,
                           const PowPlan &p1, const PowPlan &p2, hipStream_t s);
-// Public-key encryption: x holds count + (count & 1) rows of S_N2 limbs (r mod
-// n^2, then x^n in place); p plans the exponentiation over (count + 1) / 2
+// Public-key encryption: x holds count + (count & 1) rows of 3 S_N limbs (all
+// rows of r mod n, then all of r^n mod n^2 as two digits base n); p plans the exponentiation over (count + 1) / 2
 // unit pairs (kind 1).
 hipError_t launch_enc_pub(int KP, const DKey &k, const int64_t *m, uint64_t count, const uint32_t *r, uint64_t seed,
                           uint64_t roff, uint32_t *x, uint32_t *ct, uint32_t *tab, const PowPlan &p, hipStream_t s);
@@ -154,15 +183,13 @@ uint32_t pack_slots(int n_bits, uint64_t count);
 hipError_t launch_mont_convert(int KP, const DKey &k, const uint32_t *in, uint64_t count,
                                uint32_t *out, bool to_mont, hipStream_t s);
 // The pieces, for the autotuner: r mod P into tq; one private-key
-// exponentiation of `kind` (4 mod P, 0 lift, 2 decryption; in/out strides
-// and limbs per (ciphertext, prime) unit); c mod P^2 into xpq.
+// exponentiation of `kind` (4 mod P: tq in place, 0 lift: tq into out, 2
+// decryption: ciphertexts into out).
 hipError_t launch_enc_r(int KP, const DKey &k, uint64_t count, const uint32_t *r, uint64_t seed, uint64_t roff,
                         uint32_t *tq, hipStream_t s);
-hipError_t launch_pow_kind(int KP, const DKey &k, int kind, const uint32_t *in, uint32_t in_stride,
-                           uint32_t in_limbs, uint32_t *out, uint32_t out_stride, uint64_t count, uint32_t *tab,
-                           const PowPlan &p, hipStream_t s);
-hipError_t launch_dec_pre(int KP, const DKey &k, const uint32_t *ct, uint64_t count, uint32_t *xpq, hipStream_t s);
-// xpq: [count][2][S_P2] (c mod P^2, then c^(P-1) mod P^2 in place).
+hipError_t launch_pow_kind(int KP, const DKey &k, int kind, const uint32_t *in, uint32_t *out, uint64_t count,
+                           uint32_t *tab, const PowPlan &p, hipStream_t s);
+// xpq: [count][2][S_P2] (c^(P-1) mod P^2 as two digits base P).
 hipError_t launch_dec(int KP, const DKey &k, const uint32_t *ct, uint64_t count,
                       uint32_t *xpq, int64_t *m, uint32_t *raw, uint32_t *n_overflow,
                       uint32_t *tab, const PowPlan &p, hipStream_t s);
@@ -186,18 +213,15 @@ hipError_t launch_hist(int KP, const DKey &k, const uint32_t *ctm, const DJob *h
 hipError_t launch_fill(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_probe_mul(uint64_t iters, uint32_t grid, uint32_t *sink, hipStream_t s);
 
-// The private-key exponentiation k_pow over an S32-limb modulus (S_P or
-// S_P2 32-bit limbs) at G lanes per integer: whether that shape is built,
-// its resident blocks with `dyn` bytes of dynamic LDS, and the dynamic LDS
-// that caps it at `waves` blocks per compute unit (0: no cap).
-bool pow_shape_valid(int S32, int G);
-uint32_t pow_resident_blocks(int S32, int G, uint32_t dyn);
-uint32_t pow_dyn_lds(int S32, int G, int waves);
-// Window-table scratch bytes per resident block of k_pow at G lanes: kinds 4
-// (mod P), 0 (lift mod P^2), 2 (decryption mod P^2), 1 (public key, mod n^2).
+// The exponentiations by kind -- 4 mod P, 0 (lift) and 2 (decryption) mod P^2,
+// 1 (public key) mod n^2 -- at G lanes per integer: whether that shape is
+// built, its resident blocks with `dyn` bytes of dynamic LDS, and the dynamic
+// LDS that caps it at `waves` blocks per compute unit (0: no cap).
+bool pow_shape_valid(int KP, int kind, int G);
+int device_cus();
+uint32_t pow_resident_blocks(int KP, int kind, int G, uint32_t dyn);
+uint32_t pow_dyn_lds(int KP, int kind, int G, int waves);
+// Window-table scratch bytes per resident block.
 uint64_t table_bytes_per_block(int KP, int kind, int G);
-// Default lanes per integer for an exponentiation of `kind` over `count`
-// unit pairs (ciphertexts for the private-key kinds).
-int pick_group(int KP, int kind, uint64_t count);
 
 }  // namespace he

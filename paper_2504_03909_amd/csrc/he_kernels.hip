@@ -104,19 +104,19 @@ __global__ void k_encode(const double *__restrict__ x, uint64_t count, uint32_t 
 }
 
 // ----------------------------------------------------- private-key exponentiation
-// k_pow: x_u <- x_u^(e_P) mod M_P for units u = (ciphertext i, prime P), the
-// radix-2^29 exponentiation alone (the products around it run in the 16-lane
-// kernels below, so this kernel holds nothing but the exponentiation's own
-// state).  Unit (i, w) reads in_limbs limbs at in + (2 i + w) in_stride
-// (zero-extended to S32) and writes S32 canonical limbs at
-// out + (2 i + w) out_stride.  Work unit = (prime, 64/G consecutive
-// ciphertexts), so the modulus and exponent are the same for the whole wave.
-// CT: constant-time window-table reads.  At most 3 waves per SIMD: the
-// 18-limb-per-lane shapes need about 168 VGPRs to run their step loops
-// without spills (at 128, for 4 waves, the loops spill and run 25% slower).
-// With `next` (a counter zeroed before the launch) the waves claim units as
-// they finish them, so they end together; without, wave w takes units w,
-// w + waves, ...
+// k_pow: x_u <- x_u^(e_P) mod P for units u = (ciphertext i, prime P) at 2 to 16
+// lanes per integer, the radix-2^29 exponentiation alone (the products around
+// it run in the 16-lane kernels below, so this kernel holds nothing but the
+// exponentiation's own state).  Powers mod P^2 and mod n^2, and mod P with one
+// integer per lane, run in k_pow_pair (pow_pair.hpp).  Unit (i, w) reads
+// in_limbs limbs at in + (2 i + w) in_stride (zero-extended to S32) and writes
+// S32 canonical limbs at out + (2 i + w) out_stride.  Work unit = (prime, 64/G
+// consecutive ciphertexts), so the modulus and exponent are the same for the
+// whole wave.  CT: constant-time window-table reads.  At most 3 waves per SIMD:
+// the 18-limb-per-lane shape needs about 168 VGPRs to run its step loops
+// without spills.  With `next` (a counter zeroed before the launch) the waves
+// claim units as they finish them, so they end together; without, wave w takes
+// units w, w + waves, ...
 struct PowArgs {
   DMod mod[2];
   DExp exp[2];
@@ -160,8 +160,8 @@ __global__ __launch_bounds__(kBlockThreads, 3) void k_pow(PowArgs a) {
 // (x -> x^P mod P^2 depends only on x mod P), and 1 + m n = 1 + P (m Q mod P)
 // mod P^2.  k_enc_r reduces r mod P, k_pow computes t = r^(Q mod (P-1)) mod P
 // (mod-P arithmetic, 2-lane groups for large counts) and then omega = t^P mod
-// P^2 (4-lane groups), and k_enc_crt_b forms c_P = omega (1 + P (m Q mod P))
-// and combines c_p, c_q by the CRT.
+// P^2 as two digits base P, and k_enc_crt_b forms c_P = omega (1 + P (m Q mod
+// P)) and combines c_p, c_q by the CRT.
 
 // r mod P for each (ciphertext i, prime P) into tq[2 i + P] (S_P limbs): r's
 // S_P-limb words w_k (two for an explicit r, three for the seeded one), each
@@ -216,25 +216,28 @@ __global__ __launch_bounds__(kBlockThreads) void k_enc_crt_b(DKey key, const int
   uint32_t cw[2][KP2];
 #pragma unroll 1
   for (int which = 0; which < 2; ++which) {
+    // omega = a + e P (its digits), f = 1 + P u with u = m Q mod P:
+    // omega f = a + P (e + a u mod P) mod P^2
     const DPrime &P = key.pr[which];
-    uint32_t w[KP2], f[KP2], c2[KP2];
-    ld<KP2>(w, cpq + (i * 2 + which) * SP2);  // omega = t^P mod P^2
+    const uint32_t *om = cpq + (i * 2 + which) * SP2;
+    uint32_t f[KP2], a2[KP2], c2[KP2];
     {
-      // u = (m mod P) Q mod P, then f = 1 + m n mod P^2 = 1 + P u
       const Mod<KP> Mp = load_mod<KP>(P.P.N, P.P.ninv);
-      uint32_t uu[KP], c[KP];
-      signed_mod<KP>(uu, mi, Mp.n);
-      ld<KP>(c, P.QR_P);
-      mont_mul<KP>(uu, uu, c, Mp, lds);
-      relayout<KP, KP2>(f, uu, lds);
+      uint32_t u[KP], a[KP], e[KP];
+      signed_mod<KP>(u, mi, Mp.n);
+      ld<KP>(a, P.QR2_P);
+      mont_mul<KP>(u, u, a, Mp, lds);  // u R
+      ld<KP>(a, om);
+      mont_mul<KP>(u, u, a, Mp, lds);  // a u
+      ld<KP>(e, om + SP2 / 2);
+      add_mod<KP>(u, u, e, Mp);
+      relayout<KP, KP2>(f, u, lds);
+      relayout<KP, KP2>(a2, a, lds);
     }
     const Mod<KP2> M2 = load_mod<KP2>(P.P2.N, P.P2.ninv);
     ld<KP2>(c2, P.PR_P2);
     mont_mul<KP2>(f, f, c2, M2, lds);
-    add_one<KP2>(f);
-    ld<KP2>(c2, P.P2.R2);
-    mont_mul<KP2>(f, f, c2, M2, lds);  // Montgomery form of f
-    mont_mul<KP2>(cw[which], w, f, M2, lds);  // the Montgomery factor of f cancels
+    add_plain<KP2>(cw[which], f, a2);
   }
   const DPrime &Pp = key.pr[0];
   const Mod<KP2> M2 = load_mod<KP2>(Pp.P2.N, Pp.P2.ninv);
@@ -255,64 +258,73 @@ __global__ __launch_bounds__(kBlockThreads) void k_enc_crt_b(DKey key, const int
 
 // ------------------------------------------------------ public-key encryption
 // c = (1 + (m mod n) n) r^n mod n^2 by one exponentiation mod n^2, in three
-// launches like the CRT path: k_pub_pre reduces r mod n^2 (the seeded X of
-// L + 2 limbs is used as is: r^n mod n^2 depends only on r mod n), k_pow
-// raises it to n (its units of both "primes" are n^2 and n, so a unit pair
-// covers two consecutive ciphertexts), k_pub_post multiplies by 1 + (m mod
-// n) n.  One 16-lane group per ciphertext in the light kernels.  x has
-// count + (count & 1) rows: an odd count's last row is repeated, so the
+// launches like the CRT path: k_pub_pre reduces r mod n (r^n mod n^2 depends
+// only on r mod n), k_pow_pair raises it to n in two digits base n (its units
+// of both "primes" are n, so a unit pair covers two consecutive ciphertexts),
+// k_pub_post multiplies by 1 + (m mod n) n.  One 16-lane group per ciphertext
+// in the light kernels.  x has count + (count & 1) rows: an odd count's last row is repeated, so the
 // exponentiation's last unit pair reads and writes a row of its own.
 template <int KP>
 __global__ __launch_bounds__(kBlockThreads) void k_pub_pre(DKey key, uint64_t count, const uint32_t *__restrict__ r,
                                                           uint64_t seed, uint64_t roff, uint32_t *__restrict__ x) {
-  constexpr int KN2 = 4 * KP, SN2 = 64 * KP, L = 32 * KP;
-  __shared__ __align__(16) uint32_t lds_all[16 * SN2];
+  constexpr int KN = 2 * KP, L = 32 * KP;
+  __shared__ __align__(16) uint32_t lds_all[16 * L];
   const uint32_t gi = wave_in_block() * 4 + group_in_wave();
-  uint32_t *lds = lds_all + gi * SN2;
+  uint32_t *lds = lds_all + gi * L;
   const uint64_t rows = count + (count & 1);
   uint64_t row = (uint64_t)blockIdx.x * 16 + gi;
   const bool valid = row < rows;
   if (!valid) row = rows - 1;
   const uint64_t i = row < count ? row : count - 1;
   const uint64_t W = (uint64_t)L / 2 + 1;
-  const Mod<KN2> M = load_mod<KN2>(key.n2.N, key.n2.ninv);
-  uint32_t v[KN2], c[KN2];
-  if (r)
-    ld_part<KN2>(v, r + i * L, L);
-  else
-    seeded_limbs<KN2>(v, seed, (roff + i) * W, 0, L + 2);
-  // v mod n^2: a Montgomery product with R^2 gives v R, one with 1 leaves
-  // the Montgomery domain
-  ld<KN2>(c, key.n2.R2);
-  mont_mul<KN2>(v, v, c, M, lds);
-  set_small(c, 1u);
-  mont_mul<KN2>(v, v, c, M, lds);
-  if (valid) st<KN2>(x + row * SN2, v);
+  const Mod<KN> M = load_mod<KN>(key.n.N, key.n.ninv);
+  // r's L-limb words w_k (one for an explicit r, two for the seeded one), each
+  // times R^k mod n by a Montgomery product with R^(k+1) mod n, summed
+  uint32_t v[KN], t[KN], c[KN];
+  set_zero(v);
+#pragma unroll 1
+  for (int k = 0; k < (r ? 1 : 2); ++k) {
+    if (r)
+      ld<KN>(t, r + i * L);
+    else
+      seeded_limbs<KN>(t, seed, (roff + i) * W, k * L, L + 2);
+    ld<KN>(c, k == 0 ? key.n.R1 : key.n.R2);
+    mont_mul<KN>(t, t, c, M, lds);
+    add_mod<KN>(v, v, t, M);
+  }
+  if (valid) st<KN>(x + row * L, v);
 }
 
+// ct = (a + e n) (1 + m n) = a + n (e + a m mod n) mod n^2.
 template <int KP>
 __global__ __launch_bounds__(kBlockThreads) void k_pub_post(DKey key, const int64_t *__restrict__ m, uint64_t count,
                                                            const uint32_t *__restrict__ x, uint32_t *__restrict__ ct) {
-  constexpr int KN2 = 4 * KP, SN2 = 64 * KP, L = 32 * KP;
+  constexpr int KN = 2 * KP, KN2 = 4 * KP, SN2 = 64 * KP, L = 32 * KP;
   __shared__ __align__(16) uint32_t lds_all[16 * SN2];
   const uint32_t gi = wave_in_block() * 4 + group_in_wave();
   uint32_t *lds = lds_all + gi * SN2;
   uint64_t i = (uint64_t)blockIdx.x * 16 + gi;
   const bool valid = i < count;
   if (!valid) i = count - 1;
+  uint32_t f[KN2], a2[KN2], c2[KN2];
+  {
+    const Mod<KN> Mn = load_mod<KN>(key.n.N, key.n.ninv);
+    uint32_t u[KN], a[KN], e[KN];
+    signed_mod<KN>(u, m ? m[i] : 0, Mn.n);
+    ld<KN>(a, key.n.R2);
+    mont_mul<KN>(u, u, a, Mn, lds);  // m R
+    ld<KN>(a, x + i * SN2);
+    mont_mul<KN>(u, u, a, Mn, lds);  // a m
+    ld<KN>(e, x + i * SN2 + L);
+    add_mod<KN>(u, u, e, Mn);
+    relayout<KN, KN2>(f, u, lds);
+    relayout<KN, KN2>(a2, a, lds);
+  }
   const Mod<KN2> M = load_mod<KN2>(key.n2.N, key.n2.ninv);
-  uint32_t v[KN2], c[KN2], f[KN2];
-  ld<KN2>(v, x + i * SN2);
-  // f = 1 + (m mod n) n, exact (< n^2), in Montgomery form
-  ld_part<KN2>(c, key.n.N, L);
-  signed_mod<KN2>(f, m ? m[i] : 0, c);
-  ld<KN2>(c, key.nR_n2);
-  mont_mul<KN2>(f, f, c, M, lds);
-  add_one<KN2>(f);
-  ld<KN2>(c, key.n2.R2);
-  mont_mul<KN2>(f, f, c, M, lds);
-  mont_mul<KN2>(v, v, f, M, lds);
-  if (valid) st<KN2>(ct + i * SN2, v);
+  ld<KN2>(c2, key.nR_n2);
+  mont_mul<KN2>(f, f, c2, M, lds);
+  add_plain<KN2>(f, f, a2);
+  if (valid) st<KN2>(ct + i * SN2, f);
 }
 
 // ------------------------------------------------ obfuscated encryption
@@ -697,44 +709,19 @@ __global__ __launch_bounds__(kBlockThreads) void k_mont_convert(DKey key, const 
 }
 
 // -------------------------------------------------------------- decryption
-// For (ciphertext i, prime P): x = c^(P-1) mod P^2 (k_pow), then
-// m_P = ((x - 1) / P) h_P mod P, and Garner's combination of m_p, m_q.
-// k_dec_pre: c mod P^2 for both primes into xpq[2 i + P] (S_P2 limbs):
-// c mod P^2 = c0 + c1 R' mod P^2 (halves c0, c1; R' = 2^(32 S_P2)), each half
-// by a Montgomery product with R' resp. R'^2.  One 16-lane group per (i, P).
-template <int KP>
-__global__ __launch_bounds__(kBlockThreads) void k_dec_pre(DKey key, const uint32_t *__restrict__ ct, uint64_t count,
-                                                          uint32_t *__restrict__ xpq) {
-  constexpr int KP2 = 2 * KP, SP2 = 32 * KP, SN2 = 64 * KP;
-  __shared__ __align__(16) uint32_t lds_all[16 * SP2];
-  const uint32_t gi = wave_in_block() * 4 + group_in_wave();
-  uint32_t *lds = lds_all + gi * SP2;
-  uint64_t u = (uint64_t)blockIdx.x * 16 + gi;
-  const bool valid = u < 2 * count;
-  if (!valid) u = 2 * count - 1;
-  const uint64_t i = u >> 1;
-  const DPrime &P = key.pr[u & 1];
-  const Mod<KP2> M2 = load_mod<KP2>(P.P2.N, P.P2.ninv);
-  uint32_t x[KP2], y[KP2], c[KP2];
-  ld<KP2>(x, ct + i * SN2);
-  ld<KP2>(y, ct + i * SN2 + SP2);
-  ld<KP2>(c, P.P2.R1);
-  mont_mul<KP2>(x, x, c, M2, lds);
-  ld<KP2>(c, P.P2.R2);
-  mont_mul<KP2>(y, y, c, M2, lds);
-  add_mod<KP2>(x, x, y, M2);
-  if (valid) st<KP2>(xpq + u * SP2, x);
-}
+// For (ciphertext i, prime P): x = c^(P-1) mod P^2 = a + e P (k_pow_pair, from
+// the ciphertext's four pieces of S_P limbs), then m_P = ((x - 1) / P) h_P mod
+// P, and Garner's combination of m_p, m_q.
 
-// m_P = ((x_P - 1) / P) h_P mod P from x_P = c^(P-1) mod P^2 (exact
-// division: (x - 1) P^-1 mod 2^(32 S_P), a low-half product), then
-// m = m_q + q ((m_p - m_q) q^-1 mod p) and the signed decode.
+// m_P = ((x_P - 1) / P) h_P mod P from x_P = a + e P (the exact division as (x -
+// 1) P^-1 = e + (a - 1) P^-1 mod 2^(32 S_P), a low-half product; e itself for a
+// unit), then m = m_q + q ((m_p - m_q) q^-1 mod p) and the signed decode.
 template <int KP>
 __global__ __launch_bounds__(kBlockThreads) void k_dec_b(DKey key, const uint32_t *__restrict__ xpq,
                                                         uint64_t count, int64_t *__restrict__ mout,
                                                         uint32_t *__restrict__ raw,
                                                         uint32_t *__restrict__ n_overflow) {
-  constexpr int KN = 2 * KP, KP2 = 2 * KP, SP2 = 32 * KP, SN = 32 * KP;
+  constexpr int KN = 2 * KP, SP2 = 32 * KP, SN = 32 * KP;
   __shared__ __align__(16) uint32_t lds_all[16 * SN];
   const uint32_t gi = wave_in_block() * 4 + group_in_wave();
   uint32_t *lds = lds_all + gi * SN;
@@ -745,16 +732,18 @@ __global__ __launch_bounds__(kBlockThreads) void k_dec_b(DKey key, const uint32_
 #pragma unroll 1
   for (int which = 0; which < 2; ++which) {
     const DPrime &P = key.pr[which];
-    uint32_t x[KP2], one[KP2], lo[KP], k[KP], c[KP];
-    ld<KP2>(x, xpq + (i * 2 + which) * SP2);  // canonical, = 1 mod P
-    set_small<KP2>(one, 1u);
-    sub_plain<KP2>(x, x, one);                 // x - 1 = k P
-    relayout<KP2, KP>(lo, x, lds);
+    uint32_t a[KP], one[KP], k[KP], c[KP];
+    const uint32_t *x = xpq + (i * 2 + which) * SP2;
+    ld<KP>(a, x);
+    set_small<KP>(one, 1u);
+    sub_plain<KP>(a, a, one);  // mod 2^(32 S_P)
     ld<KP>(c, P.Pinv);
-    st<KP>(lds, lo);
+    st<KP>(lds, a);
     __builtin_amdgcn_wave_barrier();
     mul_lo_lds<KP>(k, lds, c);
     __builtin_amdgcn_wave_barrier();
+    ld<KP>(c, x + SP2 / 2);
+    add_plain<KP>(k, k, c);
     const Mod<KP> Mp = load_mod<KP>(P.P.N, P.P.ninv);
     ld<KP>(c, P.hR_P);
     mont_mul<KP>(mpq[which], k, c, Mp, lds);
@@ -1280,6 +1269,16 @@ __global__ __launch_bounds__(256) void k_probe_mul(uint64_t iters, uint32_t *sin
 }
 
 // ================================================================ launchers
+int device_cus() {
+  static int cus = 0;
+  if (!cus) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+      cus = 1;
+  }
+  return cus;
+}
 static inline uint32_t blocks_for(uint64_t n, uint64_t per) { return (uint32_t)((n + per - 1) / per); }
 
 hipError_t launch_encode(const double *x, uint64_t count, uint32_t frac_bits, int64_t *m,
@@ -1290,96 +1289,101 @@ hipError_t launch_encode(const double *x, uint64_t count, uint32_t frac_bits, in
   return hipGetLastError();
 }
 
-// k_pow at (S32, G, CT), as a function pointer for the generic launch.
-template <int S32, int G>
-static const void *pow_fn(bool ct) {
-  return ct ? (const void *)k_pow<S32, G, true> : (const void *)k_pow<S32, G, false>;
-}
-static const void *pow_kernel(int S32, int G, bool ct) {
-  switch (S32) {
-    case 16:
-      return G == 2 ? pow_fn<16, 2>(ct) : G == 4 ? pow_fn<16, 4>(ct) : G == 8 ? pow_fn<16, 8>(ct) : pow_fn<16, 16>(ct);
-    case 32:
-      return G == 2 ? pow_fn<32, 2>(ct) : G == 4 ? pow_fn<32, 4>(ct) : G == 8 ? pow_fn<32, 8>(ct) : pow_fn<32, 16>(ct);
-    case 64:  // 2-lane groups would exceed the column bound of the radix-2^29 products
-      return G == 4 ? pow_fn<64, 4>(ct) : G == 8 ? pow_fn<64, 8>(ct) : pow_fn<64, 16>(ct);
-    default:  // 128: the public exponent n mod n^2 at 2048-bit keys, never secret
-      return G == 8 ? (const void *)k_pow<128, 8, false> : (const void *)k_pow<128, 16, false>;
-  }
-}
-bool pow_shape_valid(int S32, int G) {
-  return (G == 2 || G == 4 || G == 8 || G == 16) &&
-         (S32 == 16 || S32 == 32 || (S32 == 64 && G != 2) || (S32 == 128 && G >= 8));
+const void *pow_lane16(int SN, int L, bool ct);
+const void *pow_lane32(int SN, int L, bool ct);
+const void *pow_twin32(int SN, int L, bool ct);
+const void *pow_group(int SN, int L, bool ct);
+const void *pow_pair_kernel(int SN, int L, bool ct) {
+  for (auto f : {pow_lane16, pow_lane32, pow_twin32, pow_group})
+    if (const void *k = f(SN, L, ct)) return k;
+  return nullptr;
 }
 
-// Modulus and exponent of an exponentiation per prime: kind 4
-// r^(Q mod (P-1)) mod P, kind 0 t^P mod P^2, kind 2 c^(P-1) mod P^2; kind 1
-// (public key) x^n mod n^2 for both.
-static PowArgs pow_args(const DKey &k, int kind, const uint32_t *in, uint32_t in_stride, uint32_t in_limbs,
-                        uint32_t *out, uint32_t out_stride, uint64_t count, uint32_t *tabs) {
-  PowArgs a{};
-  for (int w = 0; w < 2; ++w) {
-    if (kind == 1) {
-      a.mod[w] = k.n2;
-      a.exp[w] = k.e_n;
-      continue;
-    }
-    const DPrime &P = k.pr[w];
-    a.mod[w] = kind == 4 ? P.P : P.P2;
-    a.exp[w] = kind == 4 ? P.e_enc : (kind == 0 ? P.e_lift : P.e_dec);
+// Base limbs of an exponentiation of `kind`: p, q (kinds 4, 0, 2) or n (1).
+static int pow_base(int KP, int kind) { return kind == 1 ? 32 * KP : 16 * KP; }
+
+// The exponentiation kernel of `kind` at G lanes per integer, null if not
+// built.  Mod P: k_pow from 2 lanes on, one residue per lane below.  The
+// public exponent n is never secret.
+template <int S32>
+static const void *pow_mod_kernel(int G, bool ct) {
+  switch (G) {
+    case 2: return ct ? (const void *)k_pow<S32, 2, true> : (const void *)k_pow<S32, 2, false>;
+    case 4: return ct ? (const void *)k_pow<S32, 4, true> : (const void *)k_pow<S32, 4, false>;
+    case 8: return ct ? (const void *)k_pow<S32, 8, true> : (const void *)k_pow<S32, 8, false>;
+    case 16: return ct ? (const void *)k_pow<S32, 16, true> : (const void *)k_pow<S32, 16, false>;
+    default: return nullptr;
   }
-  a.in = in;
-  a.in_stride = in_stride;
-  a.in_limbs = in_limbs;
-  a.out = out;
-  a.out_stride = out_stride;
+}
+static const void *pow_kernel(int KP, int kind, int G, bool ct) {
+  const int SN = pow_base(KP, kind);
+  if (kind != 4) return pow_pair_kernel(SN, G, ct && kind != 1);
+  if (G == 1) return pow_pair_kernel(SN, 0, ct);
+  return KP == 1 ? pow_mod_kernel<16>(G, ct) : pow_mod_kernel<32>(G, ct);
+}
+bool pow_shape_valid(int KP, int kind, int G) { return pow_kernel(KP, kind, G, false) != nullptr; }
+
+// One launch of an exponentiation over the unit pairs [first, first + count).
+static hipError_t launch_pow(int KP, const DKey &k, int kind, const uint32_t *in, uint32_t *out, uint64_t first,
+                             uint64_t count, uint32_t *tabs, uint32_t *next, const PowLaunch &l, hipStream_t s) {
+  const uint32_t SN = (uint32_t)pow_base(KP, kind);
+  const void *fn = pow_kernel(KP, kind, l.G, k.ct != 0);
+  if (!fn) return hipErrorInvalidValue;
+  if (kind == 4 && l.G > 1) {
+    PowArgs a{};
+    for (int w = 0; w < 2; ++w) {
+      a.mod[w] = k.pr[w].P;
+      a.exp[w] = k.pr[w].e_enc;
+    }
+    a.in = in + first * 2 * SN;
+    a.out = out + first * 2 * SN;
+    a.in_stride = a.in_limbs = a.out_stride = SN;
+    a.count = count;
+    a.tabs = tabs;
+    a.next = next;
+    void *args[] = {&a};
+    return hipLaunchKernel(fn, dim3(l.grid), dim3(kBlockThreads), args, l.dyn, s);
+  }
+  PairPowArgs a{};
+  const int v = kind == 4 ? 0 : he29::pair_variant(l.G / 2);
+  for (int w = 0; w < 2; ++w) {
+    const DPair &pc = kind == 1 ? k.pair_n : k.pr[w].pair;
+    a.consts[w] = pc.c[v];
+    a.ninv[w] = pc.ninv;
+    a.exp[w] = kind == 1 ? k.e_n : (kind == 4 ? k.pr[w].e_enc : (kind == 0 ? k.pr[w].e_lift : k.pr[w].e_dec));
+  }
+  a.pieces = kind == 2 ? 4 : 1;
+  a.in_w = kind == 2 ? 0 : SN;
+  a.in_i = kind == 2 ? 4 * SN : 2 * SN;
+  a.out_w = kind == 4 ? SN : 2 * SN;
+  a.out_i = 2 * a.out_w;
+  a.in = in + first * a.in_i;
+  a.out = out + first * a.out_i;
   a.count = count;
   a.tabs = tabs;
-  return a;
-}
-
-static hipError_t launch_pow(int S32, bool ct, PowArgs a, const PowLaunch &l, hipStream_t s) {
-  if (!pow_shape_valid(S32, l.G)) return hipErrorInvalidValue;
+  a.next = next;
   void *args[] = {&a};
-  return hipLaunchKernel(pow_kernel(S32, l.G, ct), dim3(l.grid), dim3(kBlockThreads), args, l.dyn, s);
+  return hipLaunchKernel(fn, dim3(l.grid), dim3(kBlockThreads), args, l.dyn, s);
 }
 
-// The plan's launches over a.count ciphertexts: the first main_count at
-// p.main, the rest at p.tail (in and out advanced by the units before them,
-// two per ciphertext), each with its work counter in p.ctr when given
-// (cleared here, in stream order).
-static hipError_t launch_pow_plan(int S32, bool ct, PowArgs a, const PowPlan &p, hipStream_t s) {
-  const uint64_t count = a.count;
+// The plan's launches over `count` unit pairs: the first main_count at
+// p.main, the rest at p.tail, each with its work counter in p.ctr when given
+// (cleared here, in stream order).  Kind 4 works on tq in place, 0 reads tq, 2
+// the ciphertexts, 1 the rows of r mod n; the last three write two digits.
+hipError_t launch_pow_kind(int KP, const DKey &k, int kind, const uint32_t *in, uint32_t *out, uint64_t count,
+                           uint32_t *tab, const PowPlan &p, hipStream_t s) {
+  if (!count) return hipSuccess;
   const uint64_t mc = p.tail.G ? std::min(p.main_count, count) : count;
   if (p.ctr) {
     const hipError_t e = launch_fill(p.ctr, 2, 0u, s);
     if (e != hipSuccess) return e;
   }
   if (mc) {
-    PowArgs am = a;
-    am.count = mc;
-    am.next = p.ctr;
-    const hipError_t e = launch_pow(S32, ct, am, p.main, s);
+    const hipError_t e = launch_pow(KP, k, kind, in, out, 0, mc, tab, p.ctr, p.main, s);
     if (e != hipSuccess) return e;
   }
-  if (mc < count) {
-    PowArgs at = a;
-    at.in += mc * 2 * a.in_stride;
-    at.out += mc * 2 * a.out_stride;
-    at.count = count - mc;
-    at.next = p.ctr ? p.ctr + 1 : nullptr;
-    return launch_pow(S32, ct, at, p.tail, s);
-  }
+  if (mc < count) return launch_pow(KP, k, kind, in, out, mc, count - mc, tab, p.ctr ? p.ctr + 1 : nullptr, p.tail, s);
   return hipSuccess;
-}
-
-hipError_t launch_pow_kind(int KP, const DKey &k, int kind, const uint32_t *in, uint32_t in_stride,
-                           uint32_t in_limbs, uint32_t *out, uint32_t out_stride, uint64_t count, uint32_t *tab,
-                           const PowPlan &p, hipStream_t s) {
-  if (!count) return hipSuccess;
-  const int S32 = kind == 4 ? 16 * KP : (kind == 1 ? 64 * KP : 32 * KP);
-  return launch_pow_plan(S32, k.ct != 0, pow_args(k, kind, in, in_stride, in_limbs, out, out_stride, count, tab), p,
-                         s);
 }
 
 hipError_t launch_enc_r(int KP, const DKey &k, uint64_t count, const uint32_t *r, uint64_t seed, uint64_t roff,
@@ -1394,25 +1398,15 @@ hipError_t launch_enc_r(int KP, const DKey &k, uint64_t count, const uint32_t *r
   return hipGetLastError();
 }
 
-hipError_t launch_dec_pre(int KP, const DKey &k, const uint32_t *ct, uint64_t count, uint32_t *xpq, hipStream_t s) {
-  if (!count) return hipSuccess;
-  if (KP == 1)
-    hipLaunchKernelGGL(k_dec_pre<1>, dim3(blocks_for(2 * count, 16)), dim3(kBlockThreads), 0, s, k, ct, count, xpq);
-  else
-    hipLaunchKernelGGL(k_dec_pre<2>, dim3(blocks_for(2 * count, 16)), dim3(kBlockThreads), 0, s, k, ct, count, xpq);
-  return hipGetLastError();
-}
-
 template <int KP>
 static hipError_t enc_crt(const DKey &k, const int64_t *m, uint64_t count, const uint32_t *r, uint64_t seed,
                           uint64_t roff, uint32_t *tq, uint32_t *cpq, uint32_t *ct, uint32_t *tab,
                           const PowPlan &p1, const PowPlan &p2, hipStream_t s) {
-  constexpr int SP = 16 * KP, SP2 = 32 * KP;
   hipLaunchKernelGGL(k_enc_r<KP>, dim3(blocks_for(2 * count, 16)), dim3(kBlockThreads), 0, s, k, count, r, seed,
                      roff, tq);
-  hipError_t e = launch_pow_plan(SP, k.ct != 0, pow_args(k, 4, tq, SP, SP, tq, SP, count, tab), p1, s);
+  hipError_t e = launch_pow_kind(KP, k, 4, tq, tq, count, tab, p1, s);
   if (e != hipSuccess) return e;
-  e = launch_pow_plan(SP2, k.ct != 0, pow_args(k, 0, tq, SP, SP, cpq, SP2, count, tab), p2, s);
+  e = launch_pow_kind(KP, k, 0, tq, cpq, count, tab, p2, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_enc_crt_b<KP>, dim3(blocks_for(count, 16)), dim3(kBlockThreads), 0, s, k, m,
                      (const uint32_t *)cpq, count, ct);
@@ -1429,13 +1423,14 @@ hipError_t launch_enc_crt(int KP, const DKey &k, const int64_t *m, uint64_t coun
 template <int KP>
 static hipError_t enc_pub(const DKey &k, const int64_t *m, uint64_t count, const uint32_t *r, uint64_t seed,
                           uint64_t roff, uint32_t *x, uint32_t *ct, uint32_t *tab, const PowPlan &p, hipStream_t s) {
-  constexpr int SN2 = 64 * KP;
-  hipLaunchKernelGGL(k_pub_pre<KP>, dim3(blocks_for(count + (count & 1), 16)), dim3(kBlockThreads), 0, s, k, count,
+  const uint64_t rows = count + (count & 1);
+  uint32_t *digits = x + rows * 32 * KP;
+  hipLaunchKernelGGL(k_pub_pre<KP>, dim3(blocks_for(rows, 16)), dim3(kBlockThreads), 0, s, k, count,
                      r, seed, roff, x);
-  const hipError_t e = launch_pow_plan(SN2, false, pow_args(k, 1, x, SN2, SN2, x, SN2, (count + 1) / 2, tab), p, s);
+  const hipError_t e = launch_pow_kind(KP, k, 1, x, digits, rows / 2, tab, p, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_pub_post<KP>, dim3(blocks_for(count, 16)), dim3(kBlockThreads), 0, s, k, m, count,
-                     (const uint32_t *)x, ct);
+                     (const uint32_t *)digits, ct);
   return hipGetLastError();
 }
 hipError_t launch_enc_pub(int KP, const DKey &k, const int64_t *m, uint64_t count, const uint32_t *r, uint64_t seed,
@@ -1537,9 +1532,7 @@ hipError_t launch_mont_convert(int KP, const DKey &k, const uint32_t *in, uint64
 template <int KP>
 static hipError_t dec(const DKey &k, const uint32_t *ct, uint64_t count, uint32_t *xpq, int64_t *m,
                       uint32_t *raw, uint32_t *n_overflow, uint32_t *tab, const PowPlan &p, hipStream_t s) {
-  constexpr int SP2 = 32 * KP;
-  hipLaunchKernelGGL(k_dec_pre<KP>, dim3(blocks_for(2 * count, 16)), dim3(kBlockThreads), 0, s, k, ct, count, xpq);
-  hipError_t e = launch_pow_plan(SP2, k.ct != 0, pow_args(k, 2, xpq, SP2, SP2, xpq, SP2, count, tab), p, s);
+  const hipError_t e = launch_pow_kind(KP, k, 2, ct, xpq, count, tab, p, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_dec_b<KP>, dim3(blocks_for(count, 16)), dim3(kBlockThreads), 0, s, k,
                      (const uint32_t *)xpq, count, m, raw, n_overflow);
@@ -1618,32 +1611,20 @@ uint32_t ct_div_batch(uint64_t count) {
   return (uint32_t)std::max<uint64_t>(1, (count + groups - 1) / groups);
 }
 
-static int device_cus() {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-      cus = 1;
-  }
-  return cus;
-}
 
-// Resident blocks of k_pow<S32, G> on the device with `dyn` bytes of dynamic LDS.
-uint32_t pow_resident_blocks(int S32, int G, uint32_t dyn) {
+// Resident blocks of the exponentiation of `kind` at G lanes with `dyn` bytes
+// of dynamic LDS.
+uint32_t pow_resident_blocks(int KP, int kind, int G, uint32_t dyn) {
   static std::mutex mu;
-  static std::map<std::tuple<int, int, uint32_t>, uint32_t> cache;
+  static std::map<std::tuple<const void *, uint32_t>, uint32_t> cache;
+  const void *fn = pow_kernel(KP, kind, G, false);
   std::lock_guard<std::mutex> lk(mu);
-  auto it = cache.find({S32, G, dyn});
+  auto it = cache.find({fn, dyn});
   if (it != cache.end()) return it->second;
   int nb = 0;
-  if (!pow_shape_valid(S32, G) ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, pow_kernel(S32, G, false), kBlockThreads, dyn) !=
-          hipSuccess ||
-      nb < 1)
-    nb = 1;
+  if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kBlockThreads, dyn) != hipSuccess || nb < 1) nb = 1;
   const uint32_t r = (uint32_t)(nb * device_cus());
-  cache[{S32, G, dyn}] = r;
+  cache[{fn, dyn}] = r;
   return r;
 }
 
@@ -1663,13 +1644,13 @@ static uint32_t cap_dyn_lds(const void *fn, int natural, int waves) {
   return dyn > 0 ? (uint32_t)((dyn + 255) / 256 * 256) : 0u;
 }
 
-// Dynamic LDS that caps k_pow<S32, G> at `waves` blocks (= waves per SIMD)
+// Dynamic LDS that caps the exponentiation at `waves` blocks (= waves per SIMD)
 // per compute unit: enough that waves + 1 blocks do not fit.  0 when waves
 // is 0 or the kernel's own occupancy is at most `waves`.
-uint32_t pow_dyn_lds(int S32, int G, int waves) {
-  if (waves <= 0 || !pow_shape_valid(S32, G)) return 0;
-  return cap_dyn_lds(pow_kernel(S32, G, false), (int)(pow_resident_blocks(S32, G, 0) / (uint32_t)device_cus()),
-                     waves);
+uint32_t pow_dyn_lds(int KP, int kind, int G, int waves) {
+  if (waves <= 0 || !pow_shape_valid(KP, kind, G)) return 0;
+  return cap_dyn_lds(pow_kernel(KP, kind, G, false),
+                     (int)(pow_resident_blocks(KP, kind, G, 0) / (uint32_t)device_cus()), waves);
 }
 
 // Histogram product kernel shapes: 16-lane groups, or 8-lane groups where
@@ -1701,25 +1682,11 @@ uint32_t hist_dyn_lds(int KP, int G, int waves) {
 }
 
 uint64_t table_bytes_per_block(int KP, int kind, int G) {
-  // limbs of the modulus the kernel's exponentiation tables work in
-  // (radix-2^29 limbs): mod P (kind 4), mod P^2 (0, 2), mod n^2 (1)
-  const uint64_t S = (uint64_t)he29::limbs_for_group(kind == 1 ? 64 * KP : (kind == 4 ? 16 * KP : 32 * KP), G);
+  // radix-2^29 limbs per table entry: two digits, or one residue mod P
+  const int SN = pow_base(KP, kind);
+  const uint64_t S = kind != 4 ? 2ull * he29::pair_limbs(SN, he29::pair_variant(G / 2))
+                               : (G == 1 ? (uint64_t)he29::pair_limbs(SN, 0) : (uint64_t)he29::limbs_for_group(SN, G));
   return (uint64_t)(kBlockThreads / G) * (kTable + 1) * S * sizeof(uint32_t);
-}
-
-// Group width for an exponentiation (kind 4 mod P, 0 lift, 2 decryption, 1
-// public key) over `count` units pairs: the narrowest built group (more
-// limbs per lane, less cross-lane work per product) whose launch still gives
-// every SIMD at least two waves; below that, wider groups buy parallelism.
-int pick_group(int KP, int kind, uint64_t count) {
-  const int S32 = kind == 4 ? 16 * KP : (kind == 1 ? 64 * KP : 32 * KP);
-  const uint64_t need = 2ull * 4 * (uint64_t)device_cus();  // two waves on each of the 4 SIMDs per CU
-  for (int G : {2, 4, 8}) {
-    if (!pow_shape_valid(S32, G) || (G == 2 && kind != 4)) continue;  // 2 lanes: the mod-P exponentiation only
-    const uint64_t waves = 2 * ((count + 64 / G - 1) / (64 / G));
-    if (waves >= need) return G;
-  }
-  return 16;
 }
 
 }  // namespace he

@@ -47,6 +47,11 @@ struct ModOff {  // Montgomery modulus N of S limbs, R = 2^(32 S)
   // radix-2^29 form per variant: N, R mod N and R^2 mod N with R = 2^(29 S29)
   size_t N29[he29::kVariants], R1_29[he29::kVariants], R2_29[he29::kVariants];
 };
+// Constants of the two-digit form of residues mod N^2, per limb-count variant.
+struct PairOff {
+  size_t c[he29::kPairVariants];
+  uint32_t ninv;
+};
 struct ExpOff {
   size_t e;
   int nwin;
@@ -89,12 +94,14 @@ inline std::vector<uint32_t> sliding_schedule(const Limbs &e) {
 }
 struct PrimeOff {
   ModOff P, P2;
+  PairOff pair;
   ExpOff e_enc, e_lift, e_dec;
-  size_t QR_P, PR_P2, Pinv, hR_P;
+  size_t QR_P, QR2_P, PR_P2, Pinv, hR_P;
 };
 struct KeyConsts {
   Blob blob;
   ModOff n, n2;
+  PairOff pair_n;
   ExpOff e_n;
   size_t nR_n2 = 0, half = 0;
   PrimeOff pr[2]{};
@@ -125,6 +132,40 @@ inline ModOff put_mod(Blob &b, const Limbs &N, size_t S) {
   return m;
 }
 
+// The two-digit constants of N (S 32-bit limbs), see radix29.hpp.  X mod N^2
+// is the pair (c, d 2^29 mod N) with X = c - d N.  Piece h of an input
+// sum_h x_h 2^(32 S h) enters by the product with 2^(32 S h) R^2 mod N^2.
+inline PairOff put_pair(Blob &b, const Limbs &N, size_t S) {
+  PairOff o;
+  o.ninv = hebn::neg_inv32(N[0]);
+  const Limbs N2 = hebn::mul(N, N), shift = hebn::mod(pow2(he29::kBits), N);
+  for (int v = 0; v < he29::kPairVariants; ++v) {
+    const size_t S29 = (size_t)he29::pair_limbs((int)S, v);
+    const Limbs R = hebn::mod(pow2(he29::kBits * S29), N2);
+    auto put = [&](const Limbs &X) {
+      Limbs e, c;
+      hebn::divmod(X, N, &e, &c);  // X = c + e N
+      const Limbs d = hebn::is_zero(e) ? e : hebn::sub(N, e);
+      const size_t at = b.put29(c, S29);
+      b.words.resize(at + S29);  // the digits are adjacent
+      b.put29(hebn::mulmod(d, shift, N), S29);
+      b.words.resize(at + 2 * S29);
+    };
+    o.c[v] = b.words.size();
+    Limbs piece = hebn::mulmod(R, R, N2);
+    const Limbs step = hebn::mod(pow2(32 * S), N2);
+    for (int h = 0; h < he29::kPairPieces; ++h) {
+      put(piece);
+      piece = hebn::mulmod(piece, step, N2);
+    }
+    put(hebn::from_u64(1));
+    put(hebn::mod(pow2(he29::kBits * (S29 - 1)), N));
+    put(R);
+    b.put29(N, S29);
+  }
+  return o;
+}
+
 inline ExpOff put_exp(Blob &b, const Limbs &e, size_t limbs) {
   ExpOff x;
   x.e = b.put(e, limbs, 1);
@@ -145,6 +186,7 @@ inline PrimeOff put_prime(Blob &b, const Limbs &P, const Limbs &Q, const Limbs &
   const Limbs P2 = hebn::mul(P, P);
   o.P = put_mod(b, P, SP);
   o.P2 = put_mod(b, P2, 2 * SP);
+  o.pair = put_pair(b, P, SP);
   const Limbs Pm1 = hebn::sub(P, one);
   o.e_enc = put_exp(b, hebn::mod(Q, Pm1), SP);
   o.e_lift = put_exp(b, P, SP);
@@ -152,6 +194,7 @@ inline PrimeOff put_prime(Blob &b, const Limbs &P, const Limbs &Q, const Limbs &
   const Limbs RP = hebn::mod(pow2(32 * SP), P);
   const Limbs RP2 = hebn::mod(pow2(64 * SP), P2);
   o.QR_P = b.put(hebn::mulmod(Q, RP, P), SP);
+  o.QR2_P = b.put(hebn::mulmod(hebn::mulmod(Q, RP, P), RP, P), SP);
   o.PR_P2 = b.put(hebn::mulmod(P, RP2, P2), 2 * SP);
   o.Pinv = b.put(hebn::inv_pow2(P, 32 * SP), SP);
   // h_P = L_P(g^(P-1) mod P^2)^-1 mod P with g = n + 1, L_P(x) = (x - 1) / P
@@ -171,6 +214,7 @@ inline KeyConsts derive(uint32_t n_bits, const Limbs &n, const Limbs &p, const L
   Blob &b = k.blob;
   k.n = put_mod(b, n, L);
   k.n2 = put_mod(b, n2, 2 * L);
+  k.pair_n = put_pair(b, n, L);
   k.e_n = put_exp(b, n, L);
   const Limbs Rn2 = hebn::mod(pow2(64 * L), n2);
   const Limbs Rn = hebn::mod(pow2(32 * L), n);

@@ -361,9 +361,9 @@ __device__ __forceinline__ void mm29_mem(uint32_t (&t)[K], const uint32_t *a, co
 // the lane (every carry is 0 or 1: only the second limb can exceed 2^29), a
 // ballot carry-lookahead across the group, then d = t - N the same way (in
 // the lane, then a borrow lookahead); t is replaced by d unless the
-// subtraction borrows out of the group's top limb.
+// subtraction borrows out of the group's top limb.  True if N was subtracted.
 template <int K, int G>
-__device__ __forceinline__ void canon29(uint32_t (&t)[K], const Mod29<K> &M) {
+__device__ __forceinline__ bool canon29(uint32_t (&t)[K], const Mod29<K> &M) {
   uint32_t c = 0;
 #pragma unroll
   for (int j = 0; j < K; ++j) {
@@ -401,6 +401,7 @@ __device__ __forceinline__ void canon29(uint32_t (&t)[K], const Mod29<K> &M) {
   }
   const bool neg = bcast_last<G>((b | bi) != 0u ? 1u : 0u) != 0u;
   select(t, neg, t, d);
+  return !neg;
 }
 
 // 32-bit limbs (K32 per lane, value below 2^(29 S29)) -> 29-bit limbs.

@@ -24,4 +24,23 @@ constexpr int limbs(int S, int v) {
 }
 constexpr int limbs_for_group(int S, int G) { return limbs(S, variant(G)); }
 
+// Residues mod N^2 as two digits base N (pair29.hpp): each digit is an
+// integer below 2N in S29 limbs held by g lanes.  Three roundings of the limb
+// count: 0 (multiple of 2: 1 or 2 lanes per digit), 1 (4 lanes), 2 (8 lanes).
+constexpr int kPairVariants = 3;
+constexpr int pair_variant(int g) { return g <= 2 ? 0 : (g == 4 ? 1 : 2); }
+constexpr int pair_limbs(int S, int v) {
+  const int m = (32 * S + 2 + kBits - 1) / kBits;
+  const int u = 2 << v;
+  return (m + u - 1) / u * u;
+}
+// Constants of the two-digit form, in pairs of 2 S29 words (first digit, then
+// second), one after the other; then N in S29 limbs.
+constexpr int kPairPieces = 4;                // input pieces of 32 S bits
+constexpr int kPairOne = kPairPieces;         // (1, 0): leaves the Montgomery domain
+constexpr int kPairUnscale = kPairOne + 1;    // (2^(29 (S29 - 1)) mod N, 0): drops the second digit's 2^29
+constexpr int kPairR = kPairUnscale + 1;      // R mod N^2: Montgomery form of 1
+constexpr int kPairN = kPairR + 1;            // N
+constexpr int pair_words(int S, int v) { return (2 * kPairN + 1) * pair_limbs(S, v); }
+
 }  // namespace he29
