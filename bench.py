@@ -60,7 +60,7 @@ MI355X_HBM_BPS = 8.0e12
 ENC_LAUNCH_TRAFFIC = {"bytes": 4.0915e10, "sources_sha256_16": "0c8bbee5b0c6da4e"}
 # the kernels and the host code that picks their launches and exponent schedules
 KERNEL_SOURCES = ("he_kernels.hip", "he_internal.hpp", "hist_bucket.hpp", "mont.hpp", "mont29.hpp",
-                  "radix29.hpp", "pair29.hpp", "pow_pair.hpp", "pow_lane16.hip", "pow_lane32.hip", "pow_twin32.hip",
+                  "radix29.hpp", "pair29.hpp", "hist_pair.hpp", "pow_pair.hpp", "pow_lane16.hip", "pow_lane32.hip", "pow_twin32.hip",
                   "pow_group.hip", "he_api.cpp", "keysetup.hpp")
 
 

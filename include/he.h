@@ -197,14 +197,14 @@ typedef struct he_hist_job {
  *   hist[f][b][t] = prod over i in sample_idx with bins[f][i] = b of
  *                   ct[i][t] mod n^2,   empty bins hold 1.
  * ct: device uint32[rows][2][2L] (g and h ciphertext of each row), in the
- *     form given by ct_form (HE_FORM_MONT avoids a conversion per call).
+ *     form given by ct_form (HE_FORM_MONT makes the conversion each call
+ *     starts with three times cheaper).
  * jobs: host array of n_jobs descriptors.  All jobs' (feature, bin, chunk)
  * work items run in one persistent launch; the result is independent of
  * batching, chunking and order (exact modular products).  Work shape: the
- * one he_hist_autotune found for the batch's shape class, else, at 2048-bit
- * keys for batches of at least 16384 items (estimated at 128 samples per
- * item), 8 lanes per ciphertext and items of up to 128 samples, and 16
- * lanes with items of up to 64 samples otherwise. */
+ * one he_hist_autotune found for the batch's shape class, else items of 8 to
+ * 256 samples in two runs, longer where the batch fills the device several
+ * times over. */
 int he_hist_aggregate(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form,
                       const he_hist_job *jobs, uint32_t n_jobs, hipStream_t stream);
 
@@ -218,11 +218,11 @@ int he_hist_aggregate_ex(const he_key *key, const uint32_t *ct, uint64_t rows, i
 
 /* Autotuner for the batched aggregation: times he_hist_aggregate on these
  * jobs (synchronising `stream`), first for work-item lengths of 16..512
- * samples (32..256 at 8 lanes) and one or two groups per (item, slot) at
- * each of the product kernel's lanes per ciphertext (16, and 8 at 2048-bit
- * keys), then, at the best items of each, for waves per SIMD (4, 3 or 2 by
- * reserving LDS, where that is below the kernel's own occupancy), and
- * remembers the fastest choice for the shape class (key
+ * samples (32..256 at 8 lanes), one or two groups per (item, slot) at each
+ * of the product kernel's lanes per sample (16, and 8 at 2048-bit keys: two
+ * or one times 4 lanes for each of its two ciphertexts, so 1, 2 or 4 runs per
+ * item and slot), then, at the best items of each, for waves per SIMD (where
+ * a cap is below the kernel's own occupancy of two), and remembers the fastest choice for the shape class (key
  * size, total contributions and job count rounded to powers of two, largest
  * bin count).  Later he_hist_aggregate calls and plans with chunk 0 in the
  * same class use it.  The histograms are written (correctly) several times.
@@ -274,8 +274,9 @@ int he_crt_set_shape(const he_key *key, uint32_t kind, uint64_t count, uint32_t 
 
 /* Work-count check of the aggregation: he_hist_aggregate_ex at an explicit
  * work shape -- work-item length (chunk, 0 = default), groups per item
- * (split, 1 or 2), lanes per ciphertext of the product kernel (lanes, 0 =
- * 16; 8 only at 2048-bit keys, else HE_ERR_ARG) and its waves per SIMD
+ * (split, 1 or 2), lanes per sample of the product kernel (lanes, 0 =
+ * 16; 8 only at 2048-bit keys, else HE_ERR_ARG; an item's samples are cut
+ * into split * lanes / 8 runs) and its waves per SIMD
  * (waves, 0 = own occupancy, at most 8) -- that also adds, into the device
  * counters mm_count[3] (not cleared):
  *   [0] the Montgomery products that join two partial products of real
@@ -284,7 +285,7 @@ int he_crt_set_shape(const he_key *key, uint32_t kind, uint64_t count, uint32_t 
  *   [1] the products the kernels executed, padding of uneven work items and
  *       the conversions out of Montgomery form included;
  *   [2] the conversions out of Montgomery form (one per histogram entry).
- * The conversion of canonical input rows into Montgomery form is not counted. */
+ * The conversion of the input rows into the kernels' form is not counted. */
 int he_hist_aggregate_counted(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form,
                               const he_hist_job *jobs, uint32_t n_jobs, uint32_t chunk, uint32_t split,
                               uint32_t lanes, uint32_t waves, uint64_t *mm_count, hipStream_t stream);

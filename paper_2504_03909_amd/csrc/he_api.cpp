@@ -687,15 +687,22 @@ struct HistLayout {
   std::vector<he::DJob> dj;
   uint64_t total_fb = 0, total_f = 0, total_blocks = 0, total_perm = 0, items_cap = 0;
   uint64_t contributions = 0, rows = 0;
-  size_t o_jobs = 0, o_counts = 0, o_offs = 0, o_cursor = 0, o_fch = 0, o_fitem = 0, o_border = 0, o_ftot = 0,
-         o_fbase = 0, o_nitems = 0, o_items = 0, o_perm = 0, o_part = 0, o_ctm = 0, bytes = 0;
-  uint32_t chunk = 64, split = 2;
-  int G = he::kHistGroup, waves = 0;  // product kernel: lanes per ciphertext, waves per SIMD cap (0: none)
-  bool convert = false;
+  size_t o_jobs = 0, o_counts = 0, o_offs = 0, o_cursor = 0, o_fch = 0, o_fitem = 0, o_border = 0, o_nitems = 0,
+         o_items = 0, o_perm = 0, o_part = 0, o_pairs = 0, bytes = 0;
+  uint32_t chunk = 64, runs = 1;
+  int waves = 0;          // product kernel: waves per SIMD cap (0: none)
+  uint64_t pairs = 0;     // ciphertext pairs converted: every row, or (gather) the jobs' samples
+  bool gather = false, mont = false;
 };
 
+// Work shapes callers may name: 16 lanes per sample, or 8 at 2048-bit keys.
+bool hist_shape_valid(int KP, int lanes) { return lanes == 16 || (lanes == 8 && KP == 2); }
+// Groups per (item, slot) of a work shape: `split` times one (8 lanes per
+// sample: 4 per ciphertext) or two (16 lanes).
+uint32_t hist_runs(uint32_t split, int lanes) { return split * (lanes == 8 ? 1u : 2u); }
+
 int plan_layout(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form, const he_hist_job *jobs,
-                uint32_t n_jobs, uint32_t chunk, uint32_t split, HistLayout &lay) {
+                uint32_t n_jobs, uint32_t chunk, uint32_t split, int lanes, HistLayout &lay) {
   if (!key) return fail(HE_ERR_ARG, "null key");
   if (!jobs) return fail(HE_ERR_ARG, "null jobs");
   if (ct_form != HE_FORM_CANONICAL && ct_form != HE_FORM_MONT) return fail(HE_ERR_ARG, "bad ct_form");
@@ -706,7 +713,9 @@ int plan_layout(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_for
   lay.dj.assign(n_jobs, he::DJob{});
   lay.rows = rows;
   lay.chunk = chunk;
-  lay.split = split;
+  lay.runs = hist_runs(split, lanes);
+  lay.mont = ct_form == HE_FORM_MONT;
+  uint64_t samples = 0;
   for (uint32_t j = 0; j < n_jobs; ++j) {
     const he_hist_job &J = jobs[j];
     const std::string tag = "job " + std::to_string(j) + ": ";
@@ -730,6 +739,8 @@ int plan_layout(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_for
     d.f_off = (uint32_t)lay.total_f;
     d.nblk = (uint32_t)((J.n_samples + he::kSampleBlock - 1) / he::kSampleBlock);
     d.n_bad = J.n_bad;
+    d.s_off = samples;
+    samples += d.n;
     lay.total_fb += (uint64_t)d.F * d.B;
     lay.total_f += d.F;
     lay.total_blocks += (uint64_t)d.F * d.nblk;
@@ -745,22 +756,22 @@ int plan_layout(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_for
     return o;
   };
   lay.o_jobs = take(n_jobs * sizeof(he::DJob));
-  lay.o_counts = take(lay.total_fb * 4);
+  lay.o_counts = take((lay.total_fb + he::kHistClasses + 1) * 4);
   lay.o_offs = take(lay.total_fb * 4);
   lay.o_cursor = take(lay.total_fb * 4);
   lay.o_fch = take(lay.total_fb * 4);
   lay.o_fitem = take(lay.total_fb * 4);
   lay.o_border = take(lay.total_fb * 4);
-  lay.o_ftot = take(lay.total_f * 4);
-  lay.o_fbase = take(lay.total_f * 4);
   lay.o_nitems = take(8);  // item count, then the product kernel's work counter
   lay.o_items = take(std::max<uint64_t>(lay.items_cap, 1) * sizeof(he::HistItem));
   lay.o_perm = take(std::max<uint64_t>(lay.total_perm, 1) * 4);
-  // partial products in the histogram kernels' 29-bit limbs
-  const uint64_t S29 = (uint64_t)he29::limbs_for_group((int)S, he::kHistGroup);
-  lay.o_part = take(std::max<uint64_t>(lay.items_cap, 1) * 2 * S29 * 4);
-  lay.convert = ct_form == HE_FORM_CANONICAL && rows > 0;
-  lay.o_ctm = lay.convert ? take(rows * 2 * S * 4) : 0;
+  // partial products and the ciphertexts in two digits of 29-bit limbs: every
+  // resident row, or where the jobs hold fewer samples those one by one
+  const uint64_t row = 2 * (uint64_t)he29::limbs_for_group((int)S, he::kHistGroup) * 4;
+  lay.o_part = take(std::max<uint64_t>(lay.items_cap, 1) * row);
+  lay.gather = samples < rows;
+  lay.pairs = lay.gather ? samples : rows;
+  lay.o_pairs = take(std::max<uint64_t>(lay.pairs, 1) * row);
   lay.bytes = off;
   return HE_OK;
 }
@@ -770,46 +781,42 @@ he::HistWs bind_layout(const HistLayout &lay, char *base) {
   ws.jobs = (he::DJob *)(base + lay.o_jobs);
   ws.n_jobs = (uint32_t)lay.dj.size();
   ws.counts = (uint32_t *)(base + lay.o_counts);
+  ws.cls = ws.counts + lay.total_fb;
+  ws.scanned = ws.cls + he::kHistClasses;
   ws.offs = (uint32_t *)(base + lay.o_offs);
   ws.cursor = (uint32_t *)(base + lay.o_cursor);
   ws.fch = (uint32_t *)(base + lay.o_fch);
   ws.fitem = (uint32_t *)(base + lay.o_fitem);
   ws.border = (uint32_t *)(base + lay.o_border);
-  ws.ftot = (uint32_t *)(base + lay.o_ftot);
-  ws.fbase = (uint32_t *)(base + lay.o_fbase);
   ws.n_items = (uint32_t *)(base + lay.o_nitems);
   ws.next = ws.n_items + 1;
   ws.items = (he::HistItem *)(base + lay.o_items);
   ws.perm = (uint32_t *)(base + lay.o_perm);
   ws.partials = (uint32_t *)(base + lay.o_part);
+  ws.pairs = (uint32_t *)(base + lay.o_pairs);
   ws.total_fb = lay.total_fb;
   ws.total_f = lay.total_f;
   ws.total_blocks = lay.total_blocks;
   ws.items_cap = lay.items_cap;
   ws.rows = lay.rows;
   ws.chunk = lay.chunk;
-  ws.split = lay.split;
+  ws.runs = lay.runs;
+  ws.gather = lay.gather ? 1u : 0u;
   return ws;
 }
 
 // Enqueues every kernel of one batch on `stream` (no allocation, no
 // memset: safe to capture into a graph).
-int enqueue_hist(const he_key *key, const uint32_t *ct, uint64_t rows, const HistLayout &lay, char *base,
-                 hipStream_t stream, uint64_t *mm_count = nullptr) {
+int enqueue_hist(const he_key *key, const uint32_t *ct, const HistLayout &lay, char *base, hipStream_t stream,
+                 uint64_t *mm_count = nullptr) {
   he::HistWs ws = bind_layout(lay, base);
   ws.mm_count = (unsigned long long *)mm_count;
   const int KP = kp_of(key);
-  const uint32_t *ctm = ct;
-  if (lay.convert) {
-    uint32_t *dst = (uint32_t *)(base + lay.o_ctm);
-    HE_TRY_HIP(he::launch_mont_convert(KP, key->dk, ct, rows * 2, dst, true, stream));
-    ctm = dst;
-  }
-  he::HistLaunch hl{lay.G, 0, 0};
-  if (!he::hist_shape_valid(KP, hl.G)) hl.G = he::kHistGroup;
-  hl.dyn = he::hist_dyn_lds(KP, hl.G, lay.waves);
-  hl.grid = he::hist_resident_blocks(KP, hl.G, hl.dyn);
-  HE_TRY_HIP(he::launch_hist(KP, key->dk, ctm, lay.dj.data(), ws, hl, stream));
+  he::HistLaunch hl{0, he::hist_dyn_lds(KP, lay.waves)};
+  // a wave takes 8 / runs items at a time
+  const uint64_t waves = (lay.items_cap * lay.runs + 7) / 8;
+  hl.grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(he::hist_resident_blocks(KP, hl.dyn), (waves + 3) / 4));
+  HE_TRY_HIP(he::launch_hist(KP, key->dk, ct, lay.mont, lay.pairs, lay.dj.data(), ws, hl, stream));
   return HE_OK;
 }
 
@@ -818,14 +825,13 @@ int hist_run(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form, 
              int G = he::kHistGroup, int waves = 0) {
   if (n_jobs == 0) return key ? HE_OK : fail(HE_ERR_ARG, "null key");
   HistLayout lay;
-  int rc = plan_layout(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, lay);
+  int rc = plan_layout(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, G, lay);
   if (rc) return rc;
-  lay.G = G;
   lay.waves = waves;
   Workspace *w = workspace(stream);
   rc = ensure(w->hist, lay.bytes, stream);
   if (rc) return rc;
-  return enqueue_hist(key, ct, rows, lay, (char *)w->hist.p, stream, mm_count);
+  return enqueue_hist(key, ct, lay, (char *)w->hist.p, stream, mm_count);
 }
 
 // Autotuner cache: best (chunk, split) per shape class.
@@ -862,20 +868,23 @@ TuneKey tune_key(const he_key *key, const he_hist_job *jobs, uint32_t n_jobs) {
   return TuneKey{key->n_bits, ilog2(contrib + 1), ilog2(n_jobs), mb};
 }
 
-// Work shape of an untuned batch (chunk 0, no autotuner entry for its
-// class): at 2048-bit keys, a batch with enough items to fill the device
-// several times over takes 8 lanes per ciphertext and items of up to 128
-// samples (two items per wave, fewer instructions per product); a smaller
-// one 16 lanes and items of up to 64 samples (one item per wave, so that
-// its few items spread over more waves).
-TuneVal default_hist_shape(const he_key *key, const he_hist_job *jobs, uint32_t n_jobs) {
-  constexpr uint64_t kLargeBatchItems = 16384;
-  uint64_t items = 0;
-  for (uint32_t j = 0; j < n_jobs; ++j)
-    items += (uint64_t)jobs[j].n_features *
-             ((jobs[j].n_samples + 127) / 128 + std::min<uint64_t>(jobs[j].n_bins, jobs[j].n_samples));
-  if (kp_of(key) == 2 && items >= kLargeBatchItems) return TuneVal{128, 2, 0.f, 8, 0};
-  return TuneVal{64, 2, 0.f, he::kHistGroup, 0};
+// Work shape of an untuned batch (chunk 0, no autotuner entry for its class):
+// two runs per (item, slot), joined in the wave, of at most `len` samples each.
+// A wave per SIMD holds 8,192 runs of both slots, so W samples x features make
+// W / (8192 len) rounds of them; about two to four rounds even out the ends
+// (the last round is the shortest items), longer runs save joins.  Below 8
+// samples the joins of the partials cost more than the rounds save, except
+// for the smallest batches, where nothing else fills the device.  Measured at
+// 2048 bits (ms at half, this and twice the length): W = 8,000 0.20 / 0.20 /
+// 0.24; 36,000 0.33 / 0.29 / 0.39; 168,000 0.73 / 0.62 / 0.74; 480,000 1.32 /
+// 1.13 / 1.14; 3,200,000 6.35 / 6.18 / 6.31; 14.7 M 46.2 / 45.4 / -.
+TuneVal default_hist_shape(const he_hist_job *jobs, uint32_t n_jobs) {
+  uint64_t w = 0;
+  for (uint32_t j = 0; j < n_jobs; ++j) w += (uint64_t)jobs[j].n_features * jobs[j].n_samples;
+  const uint32_t lo = w < 16000 ? 4 : 8, hi = w < 6000000 ? 64 : 128;
+  uint32_t len = lo;
+  while (len < hi && (uint64_t)len * 2 * 20000 <= w) len *= 2;
+  return TuneVal{2 * len, 2, 0.f, 8, 0};
 }
 
 }  // namespace
@@ -886,7 +895,7 @@ extern "C" int he_hist_aggregate_ex(const he_key *key, const uint32_t *ct, uint6
   uint32_t split = 2;
   int G = he::kHistGroup, waves = 0;
   if (chunk == 0 && key && jobs && n_jobs) {
-    TuneVal v = default_hist_shape(key, jobs, n_jobs);
+    TuneVal v = default_hist_shape(jobs, n_jobs);
     {
       std::lock_guard<std::mutex> lk(g_tune_mu);
       auto it = g_tune.find(tune_key(key, jobs, n_jobs));
@@ -907,7 +916,7 @@ extern "C" int he_hist_aggregate_counted(const he_key *key, const uint32_t *ct, 
   if (split != 1 && split != 2) return fail(HE_ERR_ARG, "split must be 1 or 2");
   if (!key) return fail(HE_ERR_ARG, "null key");
   if (lanes == 0) lanes = he::kHistGroup;
-  if (!he::hist_shape_valid(kp_of(key), (int)lanes))
+  if (!hist_shape_valid(kp_of(key), (int)lanes))
     return fail(HE_ERR_ARG, "lanes must be 16, or 8 at 2048-bit keys");
   if (waves > 8) return fail(HE_ERR_ARG, "waves must be 0 (own occupancy) to 8");
   return hist_run(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, stream, mm_count, (int)lanes, (int)waves);
@@ -947,7 +956,7 @@ extern "C" int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t 
   // best items differ), then waves per SIMD at the best items of each
   const int KP = kp_of(key);
   for (int G : {he::kHistGroup, 8}) {
-    if (rc || !he::hist_shape_valid(KP, G)) continue;
+    if (rc || !hist_shape_valid(KP, G)) continue;
     for (uint32_t split : {2u, 1u}) {
       for (uint32_t c : chunks) {
         if (G != he::kHistGroup && (c < 32 || c > 256)) continue;  // 8 lanes: the middle lengths only
@@ -957,10 +966,10 @@ extern "C" int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t 
     }
   }
   for (int G : {he::kHistGroup, 8}) {
-    if (rc || !he::hist_shape_valid(KP, G)) continue;
+    if (rc || !hist_shape_valid(KP, G)) continue;
     const TuneVal bg = best_g[G == he::kHistGroup ? 0 : 1];
     for (int waves : {4, 3, 2}) {
-      if (he::hist_dyn_lds(KP, G, waves) == 0) continue;  // no cap needed: same as its own occupancy
+      if (he::hist_dyn_lds(KP, waves) == 0) continue;  // no cap needed: same as its own occupancy
       if ((rc = trial(bg.chunk, bg.split, G, waves))) break;
     }
   }
@@ -1149,7 +1158,7 @@ extern "C" int he_hist_plan_create(const he_key *key, const uint32_t *ct, uint64
   if (!key || !jobs || n_jobs == 0) return fail(HE_ERR_ARG, "need a key and at least one job");
   int G = he::kHistGroup, waves = 0;
   if (chunk == 0) {
-    TuneVal v = default_hist_shape(key, jobs, n_jobs);
+    TuneVal v = default_hist_shape(jobs, n_jobs);
     {
       std::lock_guard<std::mutex> lk(g_tune_mu);
       auto it = g_tune.find(tune_key(key, jobs, n_jobs));
@@ -1164,12 +1173,11 @@ extern "C" int he_hist_plan_create(const he_key *key, const uint32_t *ct, uint64
   he_hist_plan *p = new (std::nothrow) he_hist_plan();
   if (!p) return fail(HE_ERR_OOM, "out of host memory");
   p->key = key;
-  int rc = plan_layout(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, p->lay);
+  int rc = plan_layout(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, G, p->lay);
   if (rc) {
     delete p;
     return rc;
   }
-  p->lay.G = G;
   p->lay.waves = waves;
   if (hipMalloc(&p->ws, std::max<size_t>(p->lay.bytes, 256)) != hipSuccess) {
     hipGetLastError();
@@ -1179,7 +1187,7 @@ extern "C" int he_hist_plan_create(const he_key *key, const uint32_t *ct, uint64
   // resident block counts and LDS caps are queried before capture
   // (occupancy calls are not stream work, but keep capture free of anything
   // but launches)
-  (void)he::hist_resident_blocks(kp_of(key), G, he::hist_dyn_lds(kp_of(key), G, waves));
+  (void)he::hist_resident_blocks(kp_of(key), he::hist_dyn_lds(kp_of(key), waves));
   hipStream_t cs;
   if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) {
     he_hist_plan_free(p);
@@ -1187,7 +1195,7 @@ extern "C" int he_hist_plan_create(const he_key *key, const uint32_t *ct, uint64
   }
   hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
-    rc = enqueue_hist(key, ct, rows, p->lay, (char *)p->ws, cs);
+    rc = enqueue_hist(key, ct, p->lay, (char *)p->ws, cs);
     hipError_t e2 = hipStreamEndCapture(cs, &p->graph);
     if (rc == HE_OK && e2 != hipSuccess) rc = fail(HE_ERR_DEVICE, std::string("capture: ") + hipGetErrorString(e2));
   } else {

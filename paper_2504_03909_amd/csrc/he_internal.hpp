@@ -98,6 +98,7 @@ struct DJob {
   uint32_t f_off;      // first (job, feature) entry
   uint32_t nblk;       // sample blocks per feature
   uint32_t *n_bad;     // optional: skipped (sample, feature) pairs, device counter
+  uint64_t s_off;      // first of this job's samples among the batch's (gathered pairs)
 };
 
 struct HistItem {      // one chunk of one (feature, bin): perm[start .. start+len)
@@ -107,29 +108,34 @@ struct HistItem {      // one chunk of one (feature, bin): perm[start .. start+l
 };
 
 // Flat device workspace of one histogram batch.
+constexpr int kHistClasses = 1024;  // item lengths told apart in the items' order
 struct HistWs {
   DJob *jobs;
   uint32_t n_jobs;
-  uint32_t *counts, *offs, *cursor, *fch, *fitem;  // [total_fb]
+  uint32_t *counts;                                // [total_fb], then the classes and the scan's block count
+  uint32_t *cls;                                   // [kHistClasses] items per length, then each length's next item
+  uint32_t *scanned;                               // (job, feature) pairs scanned
+  uint32_t *offs, *cursor, *fch, *fitem;           // [total_fb]
   uint32_t *border;                                // [total_fb]: per (job, feature), its bins by decreasing count
-  uint32_t *ftot, *fbase;                          // [total_f]
   uint32_t *n_items;                               // device scalar
   uint32_t *next;                                  // device scalar: the product kernel's next wave unit
   HistItem *items;                                 // [items_cap]
-  uint32_t *perm;                                  // [total_perm]
-  uint32_t *partials;                              // [items_cap][2][S29], 29-bit limbs
+  uint32_t *perm;                                  // [total_perm]: index into pairs
+  uint32_t *pairs;                                 // [rows or samples][2][2 S29]: the ciphertexts in two digits
+  uint32_t *partials;                              // [items_cap][2][2 S29]
   uint64_t total_fb, total_f, total_blocks, items_cap;
   uint64_t rows;                                   // resident ciphertext rows
   uint32_t chunk;                                  // most samples per item
-  uint32_t split;                                  // groups per (item, slot): 1 or 2
+  uint32_t runs;                                   // groups per (item, slot): 1, 2 or 4
+  uint32_t gather;                                 // pairs holds the jobs' samples, not every row
   unsigned long long *mm_count;                    // optional debug counters [3], else null
 };
 
 constexpr int kWindowBits = 5;     // exponent window width (see mont.hpp)
 constexpr int kSampleBlock = 4096;   // samples per bucketing block
 constexpr int kBlockThreads = 256;   // 4 waves
-constexpr int kHistGroup = 16;      // lanes per integer in the histogram kernels
-constexpr int kHistWaves = 5;       // waves per SIMD asked of the histogram product kernel
+constexpr int kHistGroup = 16;      // lanes per integer of the Montgomery form the histograms take (its R')
+constexpr int kHistLanes = 4;       // lanes per ciphertext in the histogram products
 
 // ---- launchers (he_kernels.hip) ------------------------------------------------
 // KP = limbs per lane of a prime: 1 for 1024-bit keys, 2 for 2048-bit keys.
@@ -193,23 +199,18 @@ hipError_t launch_pow_kind(int KP, const DKey &k, int kind, const uint32_t *in, 
 hipError_t launch_dec(int KP, const DKey &k, const uint32_t *ct, uint64_t count,
                       uint32_t *xpq, int64_t *m, uint32_t *raw, uint32_t *n_overflow,
                       uint32_t *tab, const PowPlan &p, hipStream_t s);
-// Launch shape of the histogram product kernel: lanes per ciphertext (16,
-// or 8 at 2048-bit keys), grid, and dynamic LDS reserved only to cap its
-// blocks per compute unit.
+// Launch shape of the histogram product kernel: grid, and dynamic LDS reserved
+// only to cap its blocks per compute unit.
 struct HistLaunch {
-  int G;
   uint32_t grid;
   uint32_t dyn;
 };
-bool hist_shape_valid(int KP, int G);
-uint32_t hist_resident_blocks(int KP, int G, uint32_t dyn);
-uint32_t hist_dyn_lds(int KP, int G, int waves);
-hipError_t launch_hist(int KP, const DKey &k, const uint32_t *ctm, const DJob *host_jobs,
+uint32_t hist_resident_blocks(int KP, uint32_t dyn);
+uint32_t hist_dyn_lds(int KP, int waves);
+// ct: the resident ciphertexts (mont: HE_FORM_MONT); pairs: how many of them
+// (or of the jobs' samples) ws.pairs holds.
+hipError_t launch_hist(int KP, const DKey &k, const uint32_t *ct, bool mont, uint64_t pairs, const DJob *host_jobs,
                        const HistWs &ws, const HistLaunch &l, hipStream_t s);
-// Work items are equal parts (at most `chunk` samples) of one (feature, bin)'s
-// sample run, laid out by decreasing bin count in each feature; with
-// split 2 one wave takes one item (two groups per slot, halves combined),
-// with split 1 one wave takes two items (one group per slot).
 hipError_t launch_fill(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_probe_mul(uint64_t iters, uint32_t grid, uint32_t *sink, hipStream_t s);
 

@@ -15,6 +15,7 @@
 
 #include "he_internal.hpp"
 #include "hist_bucket.hpp"
+#include "hist_pair.hpp"
 #include "mont.hpp"
 #include "mont29.hpp"
 
@@ -804,8 +805,11 @@ constexpr int kJobsPerSetup = 24;
 struct JobPack {
   DJob j[kJobsPerSetup];
 };
-__global__ void k_job_setup(JobPack pack, uint32_t n, DJob *dst) {
-  if (threadIdx.x < n) dst[threadIdx.x] = pack.j[threadIdx.x];
+// n jobs from the kernel's arguments to dst, and `words` words at zero cleared.
+__global__ __launch_bounds__(256) void k_job_setup(JobPack pack, uint32_t n, DJob *dst, uint32_t *zero,
+                                                   uint64_t words) {
+  if (blockIdx.x == 0 && threadIdx.x < n) dst[threadIdx.x] = pack.j[threadIdx.x];
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (uint64_t)gridDim.x * 256) zero[i] = 0;
 }
 
 __device__ __forceinline__ uint32_t find_job_by_blk(const DJob *jobs, uint32_t n_jobs, uint64_t blk) {
@@ -853,14 +857,20 @@ __global__ __launch_bounds__(256) void k_hist_count(HistWs ws) {
   if (threadIdx.x == 0 && nbad && J.n_bad) atomicAdd(J.n_bad, nbad);
 }
 
+// The length class of a bin's items (the longest class first in their order).
+__device__ __forceinline__ uint32_t item_class(uint32_t cnt, uint32_t nch) {
+  return min((cnt + nch - 1) / nch, (uint32_t)kHistClasses - 1u);
+}
+
 // Per (job, feature): exclusive scan of the bin counts (the bins' sample runs
-// in bin order), chunk counts per bin and their local prefix, taken over the
-// bins in decreasing order of their counts (ties: lower bin first), so that
-// consecutive work items have about the same length and the waves that take
-// several items at once pad little; ftot = chunks of this feature; border =
-// the feature's bins in that order (k_hist_final's entry order).
+// in bin order), the bins in decreasing order of their counts (border,
+// k_hist_final's entry order; ties: lower bin first), each bin's items and
+// their length's class count.  The last block to finish turns the class
+// counts into each class's first item, longest first, so that the items of the
+// whole batch run from long to short: a wave's consecutive items are of equal
+// length, and the launch ends on its shortest ones.
 __global__ __launch_bounds__(256) void k_hist_scan(HistWs ws) {
-  __shared__ uint32_t sc[256], sh[256], cn[256];
+  __shared__ uint32_t sc[256], cn[256], last;
   const uint64_t jf = blockIdx.x;
   const uint32_t jn = find_job_by_f(ws.jobs, ws.n_jobs, jf);
   const DJob J = ws.jobs[jn];
@@ -870,95 +880,96 @@ __global__ __launch_bounds__(256) void k_hist_scan(HistWs ws) {
   const uint32_t cnt = t < J.B ? ws.counts[e] : 0u;
   const uint32_t nch = (cnt + ws.chunk - 1) / ws.chunk;
   cn[t] = cnt;
+  sc[t] = cnt;
   __syncthreads();
-  // this bin's place in the item order (bins past J.B keep their own index,
-  // which no bin below J.B takes)
-  uint32_t rank = t;
-  if (t < J.B) {
-    rank = 0;
+  uint32_t rank = 0;
+  if (t < J.B)
     for (uint32_t b = 0; b < J.B; ++b) {
       const uint32_t c = cn[b];
       rank += (c > cnt || (c == cnt && b < t)) ? 1u : 0u;
     }
-  }
-  sc[t] = cnt;
-  sh[rank] = nch;
-  __syncthreads();
-  for (uint32_t d = 1; d < 256; d <<= 1) {  // inclusive Hillis-Steele scans
-    const uint32_t a = t >= d ? sc[t - d] : 0u, b = t >= d ? sh[t - d] : 0u;
+  for (uint32_t d = 1; d < 256; d <<= 1) {  // inclusive Hillis-Steele scan
+    const uint32_t a = t >= d ? sc[t - d] : 0u;
     __syncthreads();
     sc[t] += a;
-    sh[t] += b;
     __syncthreads();
   }
   if (t < J.B) {
     ws.offs[e] = sc[t] - cnt;
     ws.cursor[e] = sc[t] - cnt;
     ws.fch[e] = nch;
-    ws.fitem[e] = sh[rank] - nch;  // local; made global by k_hist_items
-    ws.border[e - t + rank] = t;   // the bins in rank order, for the final kernel
+    ws.border[e - t + rank] = t;
+    if (nch) atomicAdd(&ws.cls[item_class(cnt, nch)], nch);
   }
-  if (t == 255) ws.ftot[jf] = sh[255];
-}
-
-// Exclusive scan of ftot over all (job, feature) pairs; total item count.
-__global__ __launch_bounds__(1024) void k_hist_base(HistWs ws) {
-  __shared__ uint32_t s[1024];
-  __shared__ uint32_t carry;
-  if (threadIdx.x == 0) carry = 0;
+  __threadfence();
   __syncthreads();
-  for (uint64_t b0 = 0; b0 < ws.total_f; b0 += 1024) {
-    const uint64_t i = b0 + threadIdx.x;
-    const uint32_t v = i < ws.total_f ? ws.ftot[i] : 0u;
-    s[threadIdx.x] = v;
+  if (t == 0) last = atomicAdd(ws.scanned, 1u) + 1u == (uint32_t)ws.total_f ? 1u : 0u;
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  // thread t: classes kHistClasses - 1 - 4 t and the three below it
+  uint32_t v[4], sum = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v[i] = atomicAdd(&ws.cls[kHistClasses - 1 - 4 * t - i], 0u);
+    sum += v[i];
+  }
+  sc[t] = sum;
+  __syncthreads();
+  for (uint32_t d = 1; d < 256; d <<= 1) {
+    const uint32_t a = t >= d ? sc[t - d] : 0u;
     __syncthreads();
-    for (uint32_t d = 1; d < 1024; d <<= 1) {
-      const uint32_t a = threadIdx.x >= d ? s[threadIdx.x - d] : 0u;
-      __syncthreads();
-      s[threadIdx.x] += a;
-      __syncthreads();
-    }
-    if (i < ws.total_f) ws.fbase[i] = carry + s[threadIdx.x] - v;
-    __syncthreads();
-    if (threadIdx.x == 1023) carry += s[1023];
+    sc[t] += a;
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    *ws.n_items = carry;
+  uint32_t first = sc[t] - sum;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    ws.cls[kHistClasses - 1 - 4 * t - i] = first;
+    first += v[i];
+  }
+  if (t == 255) {
+    *ws.n_items = sc[255];
     *ws.next = 0;  // k_hist_chunk's work counter
   }
 }
 
 // Items of one (job, feature): every bin's sample run split into its nch
-// chunks of equal length (to one sample), each at most `chunk` samples.
-__global__ __launch_bounds__(256) void k_hist_items(HistWs ws) {
-  const uint64_t jf = blockIdx.x;
-  const uint32_t jn = find_job_by_f(ws.jobs, ws.n_jobs, jf);
-  const DJob J = ws.jobs[jn];
+// chunks of equal length (to one sample), each at most `chunk` samples, at the
+// next free items of its length's class.
+__device__ __forceinline__ void hist_items(const HistWs &ws, uint64_t jf) {
+  __shared__ uint32_t at[256];
+  const DJob J = ws.jobs[find_job_by_f(ws.jobs, ws.n_jobs, jf)];
   const uint32_t f = (uint32_t)(jf - J.f_off);
-  const uint32_t b = threadIdx.x;
-  if (b >= J.B) return;
-  const uint64_t e = J.fb_off + (uint64_t)f * J.B + b;
-  const uint32_t first = ws.fbase[jf] + ws.fitem[e];
-  ws.fitem[e] = first;
-  const uint32_t nch = ws.fch[e], cnt = ws.counts[e];
-  const uint64_t start = J.perm_off + (uint64_t)f * J.n + ws.offs[e];
-  for (uint32_t c = 0; c < nch; ++c) {
-    const uint32_t lo = (uint32_t)((uint64_t)c * cnt / nch), hi = (uint32_t)((uint64_t)(c + 1) * cnt / nch);
-    HistItem it;
-    it.start = start + lo;
-    it.len = hi - lo;
-    it.pad = 0;
-    ws.items[first + c] = it;
+  const uint64_t e0 = J.fb_off + (uint64_t)f * J.B;
+  if (threadIdx.x < J.B) {
+    const uint32_t cnt = ws.counts[e0 + threadIdx.x], nch = ws.fch[e0 + threadIdx.x];
+    const uint32_t first = nch ? atomicAdd(&ws.cls[item_class(cnt, nch)], nch) : 0u;
+    ws.fitem[e0 + threadIdx.x] = first;
+    at[threadIdx.x] = first;
+  }
+  __syncthreads();
+  for (uint32_t b = threadIdx.x >> 6; b < J.B; b += 4) {  // a wave per bin
+    const uint32_t nch = ws.fch[e0 + b], cnt = ws.counts[e0 + b], first = at[b];
+    const uint64_t start = J.perm_off + (uint64_t)f * J.n + ws.offs[e0 + b];
+    for (uint32_t c = threadIdx.x & 63u; c < nch; c += 64) {
+      const uint32_t lo = (uint32_t)((uint64_t)c * cnt / nch), hi = (uint32_t)((uint64_t)(c + 1) * cnt / nch);
+      ws.items[first + c] = HistItem{start + lo, hi - lo, 0};
+    }
   }
 }
 
-// Scatter of sample rows into per-(feature, bin) runs of perm, skipping the
-// samples k_hist_count skipped (bucket_sample), so each run receives exactly
-// the samples counted for its bin.
+// Scatter of the samples' pairs (their row, or their place among the gathered
+// ones) into per-(feature, bin) runs of perm, skipping the samples k_hist_count
+// skipped (bucket_sample), so each run receives exactly the samples counted for
+// its bin.  The first total_f blocks write the work items.
 __global__ __launch_bounds__(256) void k_hist_scatter(HistWs ws) {
+  if (blockIdx.x < ws.total_f) {
+    hist_items(ws, blockIdx.x);
+    return;
+  }
   __shared__ uint32_t h[256], base[256];
-  const uint64_t blk = blockIdx.x;
+  const uint64_t blk = blockIdx.x - ws.total_f;
   const uint32_t jn = find_job_by_blk(ws.jobs, ws.n_jobs, blk);
   const DJob J = ws.jobs[jn];
   uint32_t f;
@@ -974,6 +985,7 @@ __global__ __launch_bounds__(256) void k_hist_scatter(HistWs ws) {
   for (int k = 0; k < kPer; ++k) {
     const uint64_t s = s0 + threadIdx.x + (uint64_t)k * 256;
     ok[k] = s < s1 && bucket_sample(J.idx, bf, ws.rows, J.B, s, rows[k], bn[k]);
+    if (ws.gather) rows[k] = (uint32_t)(J.s_off + s);
     if (ok[k]) rk[k] = atomicAdd(&h[bn[k]], 1u);
   }
   __syncthreads();
@@ -984,126 +996,6 @@ __global__ __launch_bounds__(256) void k_hist_scatter(HistWs ws) {
 #pragma unroll
   for (int k = 0; k < kPer; ++k)
     if (ok[k]) pf[bucket_slot(base[bn[k]], rk[k])] = rows[k];
-}
-
-// Product of the ciphertexts of one item (chunk) per (item, slot), in
-// groups of G lanes (GW = 64 / G groups per wave; bit 0 of a group's index is
-// the slot g/h).  With split 2 an item is taken by four groups: bit 1 of the
-// group index picks the first or second half of the chunk, the halves are
-// combined at the end, and a wave takes GW / 4 items.  With split 1 a wave
-// takes GW / 2 items, one group per (item, slot).  The gathered rows are in
-// the radix-2^29 Montgomery form x R' mod n^2 (32-bit limbs); each is moved
-// to 29-bit limbs through the group's LDS row and multiplied into the
-// accumulator, which stays in 29-bit limbs; partials are stored settled in
-// 29-bit limbs (S29 words).  Every loop bound is the maximum over the wave's
-// items, so the cross-lane steps of the arithmetic always run on the whole
-// wave.
-template <int KP, int G>
-__global__ __launch_bounds__(kBlockThreads, G == 16 ? kHistWaves : 3) void k_hist_chunk(DKey key,
-                                                                                    const uint32_t *__restrict__ ctm,
-                                                                      HistWs ws) {
-  constexpr int S = 64 * KP, K32 = S / G, GW = 64 / G;
-  constexpr int S29 = he29::limbs_for_group(S, G), K = S29 / G, ROW = S29 > S ? S29 : S;
-  __shared__ __align__(16) uint32_t lds_all[(kBlockThreads / 64) * GW * ROW];
-  const uint32_t g = (threadIdx.x & 63u) / G;
-  const uint32_t wrow = wave_in_block() * GW;
-  uint32_t *lds = lds_all + (wrow + g) * ROW;
-  const uint32_t slot = g & 1u;
-  const bool split = ws.split == 2;
-  const uint32_t half = (g >> 1) & 1u;
-  const Mod29<K> M = load_mod29<K, G>(key.n2);
-  const uint32_t *one29 = key.n2.R1_29[he29::variant(G)];  // Montgomery form of 1
-  const uint64_t n_items = *ws.n_items;
-  const uint64_t per_wave = split ? GW / 4 : GW / 2;
-  // wave units (per_wave consecutive items) are claimed from a counter, so a
-  // wave that finishes early takes the next unit and the waves end together
-  // to within about one unit; the items come longest first within each
-  // feature
-  for (uint64_t w0 = claim_unit(ws.next) * per_wave; w0 < n_items; w0 = claim_unit(ws.next) * per_wave) {
-    // this group's sample run and the wave-wide trip count
-    const uint64_t it = w0 + (split ? (g >> 2) : (g >> 1));
-    const bool valid = it < n_items;
-    const HistItem item = ws.items[valid ? it : n_items - 1];
-    uint32_t trip = 0;
-    for (uint64_t w = w0; w < w0 + per_wave && w < n_items; ++w) {
-      const uint32_t l = ws.items[w].len;
-      trip = max(trip, split ? (l + 1) >> 1 : l);
-    }
-    uint64_t start;
-    uint32_t my_len;
-    if (split) {
-      const uint32_t len_lo = (item.len + 1) >> 1;
-      my_len = valid ? (half ? item.len >> 1 : len_lo) : 0u;
-      start = item.start + (half ? len_lo : 0u);
-    } else {
-      my_len = valid ? item.len : 0u;
-      start = item.start;
-    }
-    const uint32_t *pp = ws.perm + start;
-    // a group with nothing (more) to do reads row 0 (in bounds) and takes
-    // the Montgomery one in its place
-    const uint32_t last = my_len ? my_len - 1 : 0u;
-    const uint32_t *base = ctm + (uint64_t)slot * S;
-    uint32_t acc[K];
-    {
-      uint32_t x[K32];
-      ld<K32, G>(x, base + (my_len ? (uint64_t)pp[0] * 2 * S : 0));
-      to29<K32, K, G>(acc, x, lds);
-      uint32_t one[K];
-      ld29<K, G>(one, one29);
-      select(acc, my_len != 0u, acc, one);
-    }
-    // the row of each product is loaded at the top of its iteration (no
-    // prefetch: the registers go to the columns; the other waves of the SIMD
-    // cover the gather)
-#pragma unroll 1
-    for (uint32_t k = 1; k < trip; ++k) {
-      // past the end of this group's run the multiplier is the Montgomery
-      // form of 1, so the product leaves the accumulator's value as it is
-      uint32_t x[K32], a[K];
-      ld<K32, G>(x, base + (my_len ? (uint64_t)pp[min(k, last)] * 2 * S : 0));
-      to29<K32, K, G>(a, x, lds);
-      if (k >= my_len) ld29<K, G>(a, one29);
-      mm29<K, G>(acc, a, acc, M, lds);
-    }
-    if (split) {
-      // combine the two halves
-      st29<K, G>(lds, acc);
-      __builtin_amdgcn_wave_barrier();
-      uint32_t other[K];
-      ld29<K, G>(other, lds_all + (wrow + (g ^ 2u)) * ROW);
-      __builtin_amdgcn_wave_barrier();
-      mm29<K, G>(acc, acc, other, M, lds);
-      if (half == 0 && valid) st29<K, G>(ws.partials + (it * 2 + slot) * S29, acc);
-    } else if (valid) {
-      st29<K, G>(ws.partials + (it * 2 + slot) * S29, acc);
-    }
-    if (ws.mm_count && glane<G>() == 0) {
-      // products joining two real partials (the algorithm's count) and
-      // products this group executed, masked padding included
-      uint64_t real = my_len ? my_len - 1 : 0, done = trip ? trip - 1 : 0;
-      if (split) {
-        done += 1;
-        real += (half == 0 && my_len >= 1 && item.len >= 2) ? 1 : 0;
-      }
-      atomicAdd(&ws.mm_count[0], (unsigned long long)real);
-      atomicAdd(&ws.mm_count[1], (unsigned long long)done);
-    }
-  }
-}
-
-// Out of Montgomery form (a product with 1), exact, back to 32-bit limbs;
-// stored by the groups with `store`.
-template <int G, int K, int K32>
-__device__ __forceinline__ void final_out(uint32_t (&acc)[K], const Mod29<K> &M, uint32_t *lds, uint32_t *dst,
-                                          bool store) {
-  uint32_t one[K];
-  set_small<K, G>(one, 1u);
-  mm29<K, G>(acc, acc, one, M, lds);
-  canon29<K, G>(acc, M);
-  uint32_t y[K32];
-  to32<K, K32, G>(y, acc, lds);
-  if (store) st<K32, G>(dst, y);
 }
 
 // Ranks (within a feature, by decreasing bin count) that k_hist_final takes
@@ -1122,18 +1014,41 @@ constexpr uint32_t kFinalSolo = 8;
 //    nch / 2), and the P products are joined in log2(P) levels through LDS.
 //  * A wave's entry: its 4 groups are (slot) x (first or second half of the
 //    partials), the halves joined at the end.
-template <int KP, int G>
-__global__ __launch_bounds__(kBlockThreads, 4) void k_hist_final(DKey key, HistWs ws) {
-  static_assert(G == 16, "four groups per wave: two slots x two parts");
-  constexpr int S = 64 * KP, K32 = S / G, GW = 64 / G, kWaves = kBlockThreads / 64, kParts = 2 * kWaves;
-  constexpr int S29 = he29::limbs_for_group(S, G), K = S29 / G, ROW = S29 > S ? S29 : S;
-  __shared__ __align__(16) uint32_t lds_all[kWaves * GW * ROW];
+template <int KP>
+__global__ __launch_bounds__(kBlockThreads, 2) void k_hist_final(DPair pc, HistWs ws) {
+  using E = GroupPair<32 * KP, 8>;
+  constexpr int S = E::S, K = E::K, ROW = 2 * S, S2 = 64 * KP, GW = 4, kWaves = kBlockThreads / 64, kParts = 2 * kWaves;
+  __shared__ __align__(16) uint32_t lds_all[kWaves * GW * E::kLds + S];
+  uint32_t *const zeros = lds_all + kWaves * GW * E::kLds;
+  zero_lds(zeros, S);
   const uint32_t wv = wave_in_block();
-  const uint32_t g = (threadIdx.x & 63u) / G;
-  uint32_t *lds = lds_all + (wv * GW + g) * ROW;
+  const uint32_t g = (threadIdx.x & 63u) / 16u;
+  uint32_t *lds = lds_all + (wv * GW + g) * E::kLds;
   const uint32_t slot = g & 1u, half = g >> 1, part = 2 * wv + half;
-  const Mod29<K> M = load_mod29<K, G>(key.n2);
-  const uint32_t *one29 = key.n2.R1_29[he29::variant(G)];  // Montgomery form of 1
+  const uint32_t *consts = pc.c[kHistVariant];
+  E eng(UnitArgs{consts, pc.ninv, nullptr}, lds, zeros);
+  const uint32_t *one = consts + 2 * he29::kPairR * S;  // Montgomery form of 1
+  // product over n partials from the p0-th on, `trip` of them for the wave;
+  // past this group's n the multiplier is the Montgomery form of 1
+  auto chain = [&](uint64_t p0, uint32_t n, uint32_t trip) __attribute__((always_inline)) {
+    auto at = [&](uint32_t k) { return k < n ? ws.partials + ((p0 + k) * 2 + slot) * ROW : one; };
+    ld29<K, 16>(eng.r, at(0));
+#pragma unroll 1
+    for (uint32_t k = 1; k < trip; ++k) {
+      const uint32_t *p = at(k);
+      ld29<K, 16>(eng.y, p);
+      ld29<K, 8>(eng.z, p);
+      eng.mul();
+    }
+  };
+  // r <- r times the pair in LDS row `other`, where `keep`
+  auto join_row = [&](bool keep) __attribute__((always_inline)) {
+    uint32_t old[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) old[j] = eng.r[j];
+    eng.mul();
+    select(eng.r, keep, eng.r, old);
+  };
   const uint64_t solo = ws.total_f * kFinalSolo;
   const uint64_t units = solo + ws.total_f * ((256 - kFinalSolo) / kWaves);  // ranks past a job's bins are skipped
   for (uint64_t u = blockIdx.x; u < units; u += gridDim.x) {
@@ -1156,49 +1071,34 @@ __global__ __launch_bounds__(kBlockThreads, 4) void k_hist_final(DKey key, HistW
       const uint32_t maxlen = (nch + P - 1) / P;
       const bool wave_on = 2 * wv < P;  // wave-uniform: the wave holds a run
       uint64_t done = 0;
-      uint32_t acc[K];
       if (wave_on) {
-        // past this group's run the multiplier is the Montgomery form of 1;
-        // each partial is loaded one product ahead of its use
-        const uint64_t p0 = (uint64_t)first + lo;
-        uint32_t b[K], nb[K];
-        ld29<K, G>(acc, len ? ws.partials + (p0 * 2 + slot) * S29 : one29);
-        ld29<K, G>(nb, 1 < len ? ws.partials + ((p0 + 1) * 2 + slot) * S29 : one29);
-#pragma unroll 1
-        for (uint32_t k = 1; k < maxlen; ++k) {
-#pragma unroll
-          for (int j = 0; j < K; ++j) b[j] = nb[j];
-          if (k + 1 < maxlen) ld29<K, G>(nb, k + 1 < len ? ws.partials + ((p0 + k + 1) * 2 + slot) * S29 : one29);
-          mm29<K, G>(acc, b, acc, M, lds);
-        }
+        chain((uint64_t)first + lo, len, maxlen);
         done += maxlen ? maxlen - 1 : 0;
       }
       // level d joins run p with run p + d for p a multiple of 2d; only the
       // even runs (half 0 of a wave) ever join, so a wave joins or not as a
       // whole
       for (uint32_t d = 1; d < P; d <<= 1) {  // block-uniform
-        if (wave_on) st29<K, G>(lds, acc);
+        if (wave_on) st29<K, 16>(lds, eng.r);
         __syncthreads();
         const bool wave_join = (2 * wv) % (2 * d) == 0 && 2 * wv + d < P;
-        uint32_t other[K];
         if (wave_join) {
           const uint32_t q = part + d;  // in range for the joining (even) runs
           const uint32_t qr = half == 0 ? (q >> 1) * GW + ((q & 1u) << 1 | slot) : wv * GW + g;
-          ld29<K, G>(other, lds_all + qr * ROW);
+          ld29<K, 16>(eng.y, lds_all + qr * E::kLds);
+          ld29<K, 8>(eng.z, lds_all + qr * E::kLds);
         }
         __syncthreads();
         if (wave_join) {
-          uint32_t t[K];
-          mm29<K, G>(t, acc, other, M, lds);
-          select(acc, half == 0, t, acc);
+          join_row(half == 0);
           ++done;
         }
       }
       if (wv == 0) {
-        final_out<G, K, K32>(acc, M, lds, J.hist + ((fb_f + bin) * 2 + slot) * S, half == 0);
+        eng.finish(J.hist + ((fb_f + bin) * 2 + slot) * S2, half == 0);
         ++done;
       }
-      if (ws.mm_count && glane<G>() == 0) {
+      if (ws.mm_count && glane<16>() == 0) {
         if (wave_on) atomicAdd(&ws.mm_count[1], (unsigned long long)done);
         if (wv == 0 && half == 0) {
           atomicAdd(&ws.mm_count[0], (unsigned long long)(nch ? nch - 1 : 0));
@@ -1211,30 +1111,17 @@ __global__ __launch_bounds__(kBlockThreads, 4) void k_hist_final(DKey key, HistW
       const uint64_t e = J.fb_off + fb_f + bin;
       const uint32_t nch = ws.fch[e], first = ws.fitem[e];
       const uint32_t n_lo = (nch + 1) >> 1, n_hi = nch >> 1;
-      const uint32_t my_n = half ? n_hi : n_lo;
-      const uint64_t p0 = (uint64_t)first + (half ? n_lo : 0u);
-      uint32_t acc[K], b[K], nb[K];
-      ld29<K, G>(acc, my_n ? ws.partials + (p0 * 2 + slot) * S29 : one29);
-      ld29<K, G>(nb, 1 < my_n ? ws.partials + ((p0 + 1) * 2 + slot) * S29 : one29);
-#pragma unroll 1
-      for (uint32_t k = 1; k < n_lo; ++k) {
-#pragma unroll
-        for (int j = 0; j < K; ++j) b[j] = nb[j];
-        if (k + 1 < n_lo) ld29<K, G>(nb, k + 1 < my_n ? ws.partials + ((p0 + k + 1) * 2 + slot) * S29 : one29);
-        mm29<K, G>(acc, b, acc, M, lds);
-      }
+      chain((uint64_t)first + (half ? n_lo : 0u), half ? n_hi : n_lo, n_lo);
       if (n_hi) {  // wave-uniform: join the halves
-        st29<K, G>(lds, acc);
+        st29<K, 16>(lds, eng.r);
         __builtin_amdgcn_wave_barrier();
-        uint32_t other[K];
-        ld29<K, G>(other, lds_all + (wv * GW + (g ^ 2u)) * ROW);
+        ld29<K, 16>(eng.y, lds_all + (wv * GW + (g ^ 2u)) * E::kLds);
+        ld29<K, 8>(eng.z, lds_all + (wv * GW + (g ^ 2u)) * E::kLds);
         __builtin_amdgcn_wave_barrier();
-        uint32_t t[K];
-        mm29<K, G>(t, acc, other, M, lds);
-        select(acc, half == 0, t, acc);
+        join_row(half == 0);
       }
-      final_out<G, K, K32>(acc, M, lds, J.hist + ((fb_f + bin) * 2 + slot) * S, half == 0);
-      if (ws.mm_count && glane<G>() == 0) {
+      eng.finish(J.hist + ((fb_f + bin) * 2 + slot) * S2, half == 0);
+      if (ws.mm_count && glane<16>() == 0) {
         const uint64_t done = (n_lo ? n_lo - 1 : 0) + (n_hi ? 1 : 0) + 1;
         atomicAdd(&ws.mm_count[1], (unsigned long long)done);
         if (half == 0) {
@@ -1554,41 +1441,34 @@ hipError_t launch_fill(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s) {
 }
 
 template <int KP>
-static hipError_t hist(const DKey &k, const uint32_t *ctm, const DJob *host_jobs, const HistWs &ws,
-                       const HistLaunch &l, hipStream_t s) {
-  hipError_t e = launch_fill(ws.counts, ws.total_fb, 0u, s);
-  if (e != hipSuccess) return e;
+static hipError_t hist(const DKey &k, const uint32_t *ct, bool mont, uint64_t pairs, const DJob *host_jobs,
+                       const HistWs &ws, const HistLaunch &l, hipStream_t s) {
+  constexpr int G = kHistLanes;
   for (uint32_t j0 = 0; j0 < ws.n_jobs; j0 += kJobsPerSetup) {
     JobPack pack;
     const uint32_t n = std::min<uint32_t>(kJobsPerSetup, ws.n_jobs - j0);
     for (uint32_t j = 0; j < n; ++j) pack.j[j] = host_jobs[j0 + j];
-    hipLaunchKernelGGL(k_job_setup, dim3(1), dim3(64), 0, s, pack, n, ws.jobs + j0);
+    const uint64_t words = j0 ? 0 : ws.total_fb + kHistClasses + 1;  // counts, classes, the scan's block count
+    hipLaunchKernelGGL(k_job_setup, dim3(j0 ? 1 : (uint32_t)std::min<uint64_t>(blocks_for(words, 1024), 1024)),
+                       dim3(256), 0, s, pack, n, ws.jobs + j0, ws.counts, words);
   }
   if (ws.total_blocks)
     hipLaunchKernelGGL(k_hist_count, dim3((uint32_t)ws.total_blocks), dim3(256), 0, s, ws);
   hipLaunchKernelGGL(k_hist_scan, dim3((uint32_t)ws.total_f), dim3(256), 0, s, ws);
-  hipLaunchKernelGGL(k_hist_base, dim3(1), dim3(1024), 0, s, ws);
-  hipLaunchKernelGGL(k_hist_items, dim3((uint32_t)ws.total_f), dim3(256), 0, s, ws);
-  if (ws.total_blocks)
-    hipLaunchKernelGGL(k_hist_scatter, dim3((uint32_t)ws.total_blocks), dim3(256), 0, s, ws);
-  bool narrow = false;
-  if constexpr (KP == 2) {
-    if (l.G == 8) {
-      hipLaunchKernelGGL((k_hist_chunk<KP, 8>), dim3(l.grid), dim3(kBlockThreads), l.dyn, s, k, ctm, ws);
-      narrow = true;
-    }
+  hipLaunchKernelGGL(k_hist_scatter, dim3((uint32_t)(ws.total_f + ws.total_blocks)), dim3(256), 0, s, ws);
+  if (ws.total_blocks) {
+    hipLaunchKernelGGL((k_hist_pairs<KP, G>), dim3(blocks_for(pairs, kBlockThreads / (2 * G))), dim3(kBlockThreads), 0,
+                       s, k.pair_n, ct, (int)mont, ws, pairs);
+    hipLaunchKernelGGL((k_hist_chunk<KP, G>), dim3(l.grid), dim3(kBlockThreads), l.dyn, s, k.pair_n, ws);
   }
-  if (!narrow)
-    hipLaunchKernelGGL((k_hist_chunk<KP, kHistGroup>), dim3(l.grid), dim3(kBlockThreads), l.dyn, s, k, ctm, ws);
   const uint64_t final_units = ws.total_f * (kFinalSolo + (256 - kFinalSolo) / 4);
   const uint32_t fgrid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(final_units, 1u << 20));
-  hipLaunchKernelGGL((k_hist_final<KP, kHistGroup>), dim3(fgrid), dim3(kBlockThreads), 0, s, k, ws);
+  hipLaunchKernelGGL(k_hist_final<KP>, dim3(fgrid), dim3(kBlockThreads), 0, s, k.pair_n, ws);
   return hipGetLastError();
 }
-hipError_t launch_hist(int KP, const DKey &k, const uint32_t *ctm, const DJob *host_jobs,
+hipError_t launch_hist(int KP, const DKey &k, const uint32_t *ct, bool mont, uint64_t pairs, const DJob *host_jobs,
                        const HistWs &ws, const HistLaunch &l, hipStream_t s) {
-  if (!hist_shape_valid(KP, l.G)) return hipErrorInvalidValue;
-  return KP == 1 ? hist<1>(k, ctm, host_jobs, ws, l, s) : hist<2>(k, ctm, host_jobs, ws, l, s);
+  return KP == 1 ? hist<1>(k, ct, mont, pairs, host_jobs, ws, l, s) : hist<2>(k, ct, mont, pairs, host_jobs, ws, l, s);
 }
 
 hipError_t launch_probe_mul(uint64_t iters, uint32_t grid, uint32_t *sink, hipStream_t s) {
@@ -1653,32 +1533,25 @@ uint32_t pow_dyn_lds(int KP, int kind, int G, int waves) {
                      (int)(pow_resident_blocks(KP, kind, G, 0) / (uint32_t)device_cus()), waves);
 }
 
-// Histogram product kernel shapes: 16-lane groups, or 8-lane groups where
-// their Montgomery form is the 16-lane one (2048-bit keys: S29 = 144 for
-// both; at 1024 bits the 8-lane R' differs).
-bool hist_shape_valid(int KP, int G) { return G == 16 || (G == 8 && KP == 2); }
-static const void *hist_kernel(int KP, int G) {
-  if (KP == 2 && G == 8) return (const void *)k_hist_chunk<2, 8>;
-  return KP == 1 ? (const void *)k_hist_chunk<1, kHistGroup> : (const void *)k_hist_chunk<2, kHistGroup>;
+static const void *hist_kernel(int KP) {
+  return KP == 1 ? (const void *)k_hist_chunk<1, kHistLanes> : (const void *)k_hist_chunk<2, kHistLanes>;
 }
-uint32_t hist_resident_blocks(int KP, int G, uint32_t dyn) {
+uint32_t hist_resident_blocks(int KP, uint32_t dyn) {
   static std::mutex mu;
-  static std::map<std::tuple<int, int, uint32_t>, uint32_t> cache;
+  static std::map<std::pair<int, uint32_t>, uint32_t> cache;
   std::lock_guard<std::mutex> lk(mu);
-  auto it = cache.find({KP, G, dyn});
+  auto it = cache.find({KP, dyn});
   if (it != cache.end()) return it->second;
   int nb = 0;
-  if (!hist_shape_valid(KP, G) ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, hist_kernel(KP, G), kBlockThreads, dyn) != hipSuccess ||
-      nb < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, hist_kernel(KP), kBlockThreads, dyn) != hipSuccess || nb < 1)
     nb = 1;
   const uint32_t r = (uint32_t)(nb * device_cus());
-  cache[{KP, G, dyn}] = r;
+  cache[{KP, dyn}] = r;
   return r;
 }
-uint32_t hist_dyn_lds(int KP, int G, int waves) {
-  if (waves <= 0 || !hist_shape_valid(KP, G)) return 0;
-  return cap_dyn_lds(hist_kernel(KP, G), (int)(hist_resident_blocks(KP, G, 0) / (uint32_t)device_cus()), waves);
+uint32_t hist_dyn_lds(int KP, int waves) {
+  return waves <= 0 ? 0
+                    : cap_dyn_lds(hist_kernel(KP), (int)(hist_resident_blocks(KP, 0) / (uint32_t)device_cus()), waves);
 }
 
 uint64_t table_bytes_per_block(int KP, int kind, int G) {

@@ -357,13 +357,11 @@ __device__ __forceinline__ void mm29_mem(uint32_t (&t)[K], const uint32_t *a, co
   mm29<K, G>(t, v, b, M, lds);
 }
 
-// Settled t below 2N -> exact 29-bit limbs of t mod N.  One carry pass in
-// the lane (every carry is 0 or 1: only the second limb can exceed 2^29), a
-// ballot carry-lookahead across the group, then d = t - N the same way (in
-// the lane, then a borrow lookahead); t is replaced by d unless the
-// subtraction borrows out of the group's top limb.  True if N was subtracted.
+// Settled t -> exact 29-bit limbs of the same integer: one carry pass in the
+// lane (every carry is 0 or 1: only the second limb can exceed 2^29) and a
+// ballot carry-lookahead across the group.
 template <int K, int G>
-__device__ __forceinline__ bool canon29(uint32_t (&t)[K], const Mod29<K> &M) {
+__device__ __forceinline__ void carry29(uint32_t (&t)[K]) {
   uint32_t c = 0;
 #pragma unroll
   for (int j = 0; j < K; ++j) {
@@ -381,6 +379,14 @@ __device__ __forceinline__ bool canon29(uint32_t (&t)[K], const Mod29<K> &M) {
     t[j] = s & kMask29;
     ci = s >> he29::kBits;
   }
+}
+
+// Settled t below 2N -> exact 29-bit limbs of t mod N: exact limbs, then d = t -
+// N the same way (in the lane, then a borrow lookahead); t is replaced by d unless the
+// subtraction borrows out of the group's top limb.  True if N was subtracted.
+template <int K, int G>
+__device__ __forceinline__ bool canon29(uint32_t (&t)[K], const Mod29<K> &M) {
+  carry29<K, G>(t);
   uint32_t d[K];
   uint32_t b = 0;
 #pragma unroll

@@ -630,6 +630,29 @@ struct GroupPair {
     for (int j = 0; j < K; ++j) C[j] = (uint64_t)r[j] + t[j];
     settle(r, C);
   }
+  // The reduction's part of a step: the quotient digit of the lowest column,
+  // the shift by one limb and (HAND) the first digit's q into the second's
+  // next column.
+  template <bool HAND>
+  __device__ __forceinline__ void reduce_step(uint64_t (&C)[K], uint32_t &top) const {
+    const uint32_t q = bcast_first_m29<G>(mul_lo32((uint32_t)C[0], M.ninv), M.mask);
+#pragma unroll
+    for (int j = 0; j < K; ++j) C[j] += (uint64_t)q * M.n[j];
+    top = rotate_next_m29<G>((uint32_t)C[0], M.mask);
+    C[1] += C[0] >> he29::kBits;
+    if constexpr (HAND) {
+      uint32_t h;  // the first digit's q, in the second digit's first lane
+      asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
+          : "=v"(h) : "v"(q), "v"(hand));
+      uint64_t kk;
+      asm("v_mad_u64_u32 %0, %1, %2, 1, %0" : "+v"(C[1]), "=s"(kk) : "v"(h));
+    }
+#pragma unroll
+    for (int j = 0; j + 1 < K; ++j) C[j] = C[j + 1];
+#pragma unroll
+    for (int j = 0; j + 1 < K; ++j) asm("" : "+v"(C[j]));
+    asm("" : "+v"(top));
+  }
   // r = (u Y + v Z + q n, ...) over all steps: u the first digit's limbs, v
   // (TWO) this lane's second multiplier row (zeros in the first digit's lanes)
   template <bool TWO>
@@ -670,21 +693,7 @@ struct GroupPair {
 #pragma unroll
           for (int j = 0; j < K; ++j) C[j] += (uint64_t)v * z[j];
         }
-        const uint32_t q = bcast_first_m29<G>(mul_lo32((uint32_t)C[0], M.ninv), M.mask);
-#pragma unroll
-        for (int j = 0; j < K; ++j) C[j] += (uint64_t)q * M.n[j];
-        top = rotate_next_m29<G>((uint32_t)C[0], M.mask);
-        uint32_t h;  // the first digit's q, in the second digit's first lane
-        asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-            : "=v"(h) : "v"(q), "v"(hand));
-        C[1] += C[0] >> he29::kBits;
-        uint64_t kk;
-        asm("v_mad_u64_u32 %0, %1, %2, 1, %0" : "+v"(C[1]), "=s"(kk) : "v"(h));
-#pragma unroll
-        for (int j = 0; j + 1 < K; ++j) C[j] = C[j + 1];
-#pragma unroll
-        for (int j = 0; j + 1 < K; ++j) asm("" : "+v"(C[j]));
-        asm("" : "+v"(top));
+        reduce_step<true>(C, top);
       });
     }
     C[K - 1] = top;
@@ -707,16 +716,13 @@ struct GroupPair {
 #pragma unroll
     for (int j = 0; j < K; ++j) r[j] = second_digit ? 0u : r[j];
   }
-  __device__ __forceinline__ void out(uint32_t *o, bool valid) {
-    // valid in the first digit's lanes; the others compute along
-    ld29<K, G>(z, slot(0));
-    const bool sub = canon29<K, G>(z, M);
-    canon29<K, G>(r, M);
-    // N - b + sub, a borrow pass in the lane and one across the group
-    uint32_t d[K], b = 0;
+  // d = (f - t) mod N for t in [0, N): N - t + f, a borrow pass in the lane and
+  // one across the group
+  __device__ __forceinline__ void negate(uint32_t (&d)[K], const uint32_t (&t)[K], bool f) const {
+    uint32_t b = 0;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      const uint32_t s = M.n[j] - r[j] - b;
+      const uint32_t s = M.n[j] - t[j] - b;
       d[j] = s & kMask29;
       b = s >> 31;
     }
@@ -730,8 +736,85 @@ struct GroupPair {
       d[j] = s & kMask29;
       bi = s >> 31;
     }
-    if (glane<G>() == 0 && sub) d[0] += 1u;
+    if (glane<G>() == 0 && f) d[0] += 1u;
     canon29<K, G>(d, M);
+  }
+  // X of the pair of X R, canonical mod N^2, as 2 SN 32-bit limbs at o.  Two
+  // reductions side by side leave the Montgomery form (no product), one more
+  // step divides the second digit by 2^29, and a + e N is one plain product.
+  __device__ __forceinline__ void finish(uint32_t *o, bool valid) {
+    uint64_t C[K];
+    uint32_t top = r[K - 1], t[K], e[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) C[j] = r[j];
+#pragma unroll 1
+    for (int i = 0; i < S; ++i) {
+      C[K - 1] = top;
+      reduce_step<true>(C, top);
+    }
+    C[K - 1] = top;
+    settle(r, C);
+#pragma unroll
+    for (int j = 0; j < K; ++j) C[j] = r[j];
+    top = r[K - 1];
+    reduce_step<false>(C, top);
+    C[K - 1] = top;
+    settle(t, C);
+#pragma unroll
+    for (int j = 0; j < K; ++j) r[j] = second_digit ? t[j] : r[j];
+    const bool sub = canon29<K, G>(r, M);
+    // the first digit's subtraction, in the second digit's lanes
+    const uint32_t f = (uint32_t)__builtin_amdgcn_update_dpp(0, sub ? 1 : 0, 0x110 + G, 0xF, 0xF, true);
+    negate(e, r, f != 0u);
+#pragma unroll
+    for (int j = 0; j < K; ++j) t[j] = second_digit ? e[j] : r[j];
+    st29<K, 2 * G>(lds, t);
+    __builtin_amdgcn_wave_barrier();
+    const bool first_lane = (lane_id() & (uint32_t)(kLanes - 1)) == 0;
+#pragma unroll
+    for (int j = 0; j < K; ++j) C[j] = r[j];
+    top = r[K - 1];
+#pragma unroll 1
+    for (int i = 0; i < S; ++i) {
+      const uint32_t u = lds[S + i];
+      C[K - 1] = top;
+#pragma unroll
+      for (int j = 0; j < K; ++j) C[j] += (uint64_t)u * M.n[j];
+      const uint32_t low = (uint32_t)C[0] & kMask29;
+      if (first_lane) lds[i] = low;  // limb i of the result
+      top = from_next<G>(low);
+      C[1] += C[0] >> he29::kBits;
+#pragma unroll
+      for (int j = 0; j + 1 < K; ++j) C[j] = C[j + 1];
+    }
+    C[K - 1] = top;
+    settle(t, C);
+    carry29<K, G>(t);
+    __builtin_amdgcn_wave_barrier();
+    if (!second_digit) {
+#pragma unroll
+      for (int j = 0; j < K; ++j) lds[S + glane<G>() * K + j] = t[j];
+    }
+    __builtin_amdgcn_wave_barrier();
+    constexpr int W = 2 * SN / kLanes;
+    uint32_t w[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+      const uint32_t bit = 32u * (glane<2 * G>() * W + j);
+      const uint32_t k0 = bit / he29::kBits, sh = bit % he29::kBits;
+      const uint64_t l0 = lds[k0], l1 = k0 + 1 < 2 * S ? lds[k0 + 1] : 0u, l2 = k0 + 2 < 2 * S ? lds[k0 + 2] : 0u;
+      w[j] = (uint32_t)((l0 | (l1 << he29::kBits) | (l2 << (2 * he29::kBits))) >> sh);
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (valid) st<W, 2 * G>(o, w);
+  }
+  __device__ __forceinline__ void out(uint32_t *o, bool valid) {
+    // valid in the first digit's lanes; the others compute along
+    ld29<K, G>(z, slot(0));
+    const bool sub = canon29<K, G>(z, M);
+    canon29<K, G>(r, M);
+    uint32_t d[K];
+    negate(d, r, sub);
     uint32_t w[K32];
     to32<K, K32, G>(w, z, digit_row());
     if (valid && !second_digit) st<K32, G>(o, w);

@@ -336,12 +336,13 @@ class GpuBackend(Backend):
             n = p["ct"].numel() // (2 * L)
             return n * (8 + L * 4) + (64 << 20)
         S = 2 * L
+        pair = 4 * 4 * (72 if L == 64 else 40)   # a sample's two ciphertexts in two digits of 29-bit limbs
         tot = 0
         B = self.bins[(req.key_id, req.party)][1]
         for (idx, F) in p["jobs"]:
             n = idx.numel()
-            items = F * ((n + 63) // 64 + min(B, n))
-            tot += F * B * 2 * S * 4 + F * n * 4 + items * (16 + 2 * S * 4) + F * B * 20
+            items = F * ((n + 15) // 16 + min(B, n))
+            tot += F * B * 2 * S * 4 + F * n * 4 + n * pair + items * (16 + pair) + F * B * 24
         return tot + (16 << 20)
 
     def launch(self, kind: str, key_id: str, reqs: Sequence[Request], slot: int):
