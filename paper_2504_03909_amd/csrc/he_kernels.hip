@@ -372,6 +372,42 @@ __global__ __launch_bounds__(kBlockThreads) void k_enc_obf(DKey key, const int64
   if (valid) st<KN2>(ct + i * SN2, x);
 }
 
+// J = Q^-1 R mod n^2 for Q < n^2; false (group-uniform) where Q is no unit.  The
+// inverse is taken mod n only -- half the limbs and half the steps of the serial
+// binary algorithm, about a quarter of its time -- and lifted: with y = Q^-1 mod
+// n, Q^-1 = y (2 - Q y) mod n^2, four products.  Q is a unit mod n^2 where it is
+// one mod n.
+template <int KP>
+__device__ __forceinline__ bool inverse_n2(uint32_t (&J)[4 * KP], const uint32_t (&Q)[4 * KP], const DKey &key,
+                                           const Mod<4 * KP> &M, uint32_t *lds, bool active) {
+  constexpr int KN = 2 * KP, KN2 = 4 * KP, L = 32 * KP;
+  bool ok;
+  uint32_t t[KN2], u[KN2], c2[KN2];
+  {
+    const Mod<KN> Mn = load_mod<KN>(key.n.N, key.n.ninv);
+    uint32_t lo[KN], hi[KN], c[KN];
+    relayout<KN2, KN>(lo, Q, lds);
+    relayout<KN2, KN>(hi, Q, lds, L);
+    ld<KN>(c, key.n.R1);
+    mont_mul<KN>(lo, lo, c, Mn, lds);
+    ld<KN>(c, key.n.R2);
+    mont_mul<KN>(hi, hi, c, Mn, lds);
+    add_mod<KN>(lo, lo, hi, Mn);  // Q mod n
+    ok = mont_inverse<KN>(hi, lo, Mn, key.n.R2, lds, active);
+    set_small<KN>(c, 1u);
+    mont_mul<KN>(hi, hi, c, Mn, lds);
+    relayout<KN, KN2>(t, hi, lds);  // y
+  }
+  ld<KN2>(c2, key.n2.R2);
+  mont_mul<KN2>(t, t, c2, M, lds);  // y R
+  mont_mul<KN2>(J, Q, t, M, lds);   // Q y
+  set_small<KN2>(u, 2u);
+  sub_mod<KN2>(u, u, J, M);
+  mont_mul<KN2>(u, u, c2, M, lds);
+  mont_mul<KN2>(J, t, u, M, lds);
+  return ok;
+}
+
 // ------------------------------------------------------ ciphertext division
 // out[i] = num[i] den[i]^-1 mod n^2, i.e. an encryption of m_num - m_den.
 // Montgomery's batch-inversion trick per group of `batch` consecutive
@@ -412,7 +448,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_ct_div(DKey key, const uint32
   }
 
   uint32_t J[KN2];
-  const bool ok = mont_inverse<KN2>(J, Q, M, key.n2.R2, lds, len > 0u);
+  const bool ok = inverse_n2<KP>(J, Q, key, M, lds, len > 0u);
 
   // backward
   uint32_t p[KN2], ainv[KN2];
@@ -444,7 +480,7 @@ __global__ __launch_bounds__(kBlockThreads) void k_ct_div(DKey key, const uint32
         ld<KN2>(a, den + (first + j) * SN2);
         ld<KN2>(p, num + (first + j) * SN2);
       }
-      const bool ok1 = mont_inverse<KN2>(J, a, M, key.n2.R2, lds, v);
+      const bool ok1 = inverse_n2<KP>(J, a, key, M, lds, v);
       mont_mul<KN2>(p, p, J, M, lds);
       if (!ok1) set_zero(p);
       if (v) st<KN2>(out + (first + j) * SN2, p);
