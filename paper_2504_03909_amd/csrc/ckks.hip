@@ -14,8 +14,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/he.h"
@@ -29,21 +29,17 @@ constexpr int kPrimeBits = 30;
 constexpr int kEta = 21;         // centered binomial parameter
 constexpr uint64_t kKeyEBase = 1ull << 40;
 constexpr uint64_t kKeyABase = 1ull << 41;
-constexpr int kNttThreads = 1024;
-constexpr int kFftThreads = 1024;
 
 struct Prime {
   uint32_t q, qinv;       // qinv = -q^-1 mod 2^32
-  uint32_t r2;            // 2^64 mod q (into Montgomery form)
+  uint32_t r1, r2;        // 2^32 and 2^64 mod q (into Montgomery form)
   uint32_t ninv, ninv_s;  // N^-1 mod q and its Shoup companion
 };
 
 struct Tables {
   Prime p[kL];
-  const uint32_t *psi;    // [L][N] psi^bitrev(i)
-  const uint32_t *psi_s;  // Shoup companions floor(w 2^32 / q)
-  const uint32_t *ipsi;   // [L][N] psi^-bitrev(i)
-  const uint32_t *ipsi_s;
+  const uint2 *psi;   // [L][N] psi^bitrev(i) and its Shoup companion floor(w 2^32 / q)
+  const uint2 *ipsi;  // [L][N] psi^-bitrev(i), the same way
 };
 
 // ---- modular helpers (q < 2^30) -------------------------------------------
@@ -67,87 +63,287 @@ __device__ __forceinline__ uint32_t mont_q(uint32_t a, uint32_t b, uint32_t q, u
   const uint32_t r = (uint32_t)((t + (uint64_t)m * q) >> 32);
   return r >= q ? r - q : r;
 }
-__device__ __forceinline__ uint32_t to_residue(int64_t v, uint32_t q) {
-  const int64_t r = v % (int64_t)q;
-  return (uint32_t)(r < 0 ? r + q : r);
+// a mod q for a < 2q.
+__device__ __forceinline__ uint32_t once(uint32_t a, uint32_t q) { return a >= q ? a - q : a; }
+// x w mod q in [0, 2q) for any x.
+__device__ __forceinline__ uint32_t mul_lazy(uint32_t x, uint2 w, uint32_t q) { return x * w.x - __umulhi(x, w.y) * q; }
+// v mod q by two Montgomery products (|v| = hi 2^32 + lo; a product by 2^32
+// resp. 2^64 mod q stays below q 2^32, so one subtraction reduces it).
+__device__ __forceinline__ uint32_t to_residue(int64_t v, const Prime &P) {
+  const uint64_t m = v < 0 ? (uint64_t)0 - (uint64_t)v : (uint64_t)v;
+  const uint32_t r =
+      add_q(mont_q((uint32_t)(m >> 32), P.r2, P.q, P.qinv), mont_q((uint32_t)m, P.r1, P.q, P.qinv), P.q);
+  return v < 0 && r ? P.q - r : r;
 }
 
 // ---- sampling ---------------------------------------------------------------
-// kind 0: ternary (word mod 3 - 1); 1: centered binomial (popcount of bits
-// 0..20 minus popcount of bits 21..41); 2: uniform mod q_i, with the counter
-// base advanced by i N for prime i.  out: [polys][L][N]; poly p uses counter
-// base + p * stride.
-__global__ void k_sample(int kind, uint64_t seed, uint64_t base, uint64_t stride, uint32_t n, uint32_t polys,
-                         Tables T, uint32_t *out) {
-  const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (uint64_t)polys * n) return;
-  const uint64_t p = idx / n, j = idx % n;
-  uint32_t *o = out + p * kL * n + j;
-  if (kind == 2) {
-    for (int i = 0; i < kL; ++i)
-      o[(uint64_t)i * n] = (uint32_t)(he::splitmix64(seed, base + p * stride + (uint64_t)i * n + j) % T.p[i].q);
-    return;
+// Ternary (word mod 3 - 1) and centered binomial (popcount of bits 0..20 minus
+// popcount of bits 21..41) values of one stream word.
+__device__ __forceinline__ uint32_t ternary(uint64_t w, uint32_t q) {
+  const uint32_t t = (uint32_t)(w % 3);
+  return t ? t - 1u : q - 1u;
+}
+__device__ __forceinline__ uint32_t binomial(uint64_t w, uint32_t shift) {  // value + shift
+  const uint32_t mask = (1u << kEta) - 1u;
+  return shift + __popc((uint32_t)w & mask) - __popc((uint32_t)(w >> kEta) & mask);
+}
+// kind 0: ternary; 1: centered binomial; 2: uniform mod q_i, with the counter
+// base advanced by i N for prime i.  out: [L][N].
+__global__ void k_sample(int kind, uint64_t seed, uint64_t base, uint32_t n, Tables T, uint32_t *out) {
+  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= n) return;
+  for (int i = 0; i < kL; ++i) {
+    const uint64_t w = he::splitmix64(seed, base + (kind == 2 ? (uint64_t)i * n : 0ull) + j);
+    const uint32_t q = T.p[i].q;
+    out[(uint64_t)i * n + j] = kind == 0 ? ternary(w, q) : (kind == 1 ? once(binomial(w, q), q) : (uint32_t)(w % q));
   }
-  const uint64_t w = he::splitmix64(seed, base + p * stride + j);
-  int64_t v;
-  if (kind == 0) {
-    v = (int64_t)(w % 3) - 1;
-  } else {
-    const uint32_t mask = (1u << kEta) - 1u;
-    v = (int64_t)__popc((uint32_t)w & mask) - (int64_t)__popc((uint32_t)(w >> kEta) & mask);
-  }
-  for (int i = 0; i < kL; ++i) o[(uint64_t)i * n] = to_residue(v, T.p[i].q);
 }
 
 // ---- negacyclic NTT ------------------------------------------------------------
-// One block per (polynomial, prime), the polynomial in LDS.  Forward:
-// Cooley-Tukey with psi powers in bit-reversed order (natural order in,
-// bit-reversed out); inverse: Gentleman-Sande with inverse powers, then
-// N^-1 (Longa & Naehrig, CANS 2016, Algorithms 1 and 2).
-// Block b works on polynomial b / L, prime b % L; polynomials are `sin` and
-// `sout` words apart in the input and output.
-__global__ __launch_bounds__(kNttThreads) void k_ntt(const uint32_t *in, uint64_t sin, uint32_t *out, uint64_t sout,
-                                                     uint32_t n, uint32_t log_n, Tables T, int inverse) {
-  extern __shared__ uint32_t a[];
-  const uint32_t i = blockIdx.x % kL;
-  const uint64_t p = blockIdx.x / kL;
-  const uint32_t *x = in + p * sin + (uint64_t)i * n;
-  uint32_t *y = out + p * sout + (uint64_t)i * n;
-  const uint32_t q = T.p[i].q;
-  for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) a[j] = x[j];
-  __syncthreads();
-  const uint32_t half = n >> 1;
-  if (!inverse) {
-    const uint32_t *w = T.psi + (uint64_t)i * n, *ws = T.psi_s + (uint64_t)i * n;
-    for (uint32_t m = 1, t = half; m < n; m <<= 1, t >>= 1) {
-      for (uint32_t b = threadIdx.x; b < half; b += blockDim.x) {
-        const uint32_t grp = b / t, k = b % t;
-        const uint32_t j = 2 * grp * t + k;
-        const uint32_t s = w[m + grp], ss = ws[m + grp];
-        const uint32_t u = a[j], v = mul_shoup(a[j + t], s, ss, q);
-        a[j] = add_q(u, v, q);
-        a[j + t] = sub_q(u, v, q);
-      }
-      __syncthreads();
+// One block of N / 16 threads per (polynomial, prime).  Forward: Cooley-Tukey
+// with psi powers in bit-reversed order (natural order in, bit-reversed out);
+// inverse: Gentleman-Sande with inverse powers, then N^-1 (Longa & Naehrig, CANS
+// 2016, Algorithms 1 and 2).  A thread holds 16 values and runs up to four
+// stages on them in registers, so the polynomial crosses LDS three times
+// instead of once per stage (14 at N = 2^14); values stay below 4q between
+// stages (Harvey's lazy butterflies, q < 2^30).  Few polynomials are in flight
+// at a time, so what one block issues bounds it: a transform of 2^14 took 37-44 us
+// stage by stage and takes about 11 inside the kernels below.
+//
+// Register c of thread t holds, before the forward and after the inverse
+// transform, coefficient t + c T (T threads); in between it holds position
+// ntt_pos(c) of the bit-reversed order.
+template <int LOGN>
+struct Ntt {
+  static constexpr uint32_t N = 1u << LOGN, T = N / 16;
+  static constexpr int R = LOGN - 12;  // stages of the short pass
+  static constexpr uint32_t kLds = N + N / 16;  // words, 4 of padding after every 64
+};
+__device__ __forceinline__ uint32_t pad(uint32_t i) { return i + ((i >> 6) << 2); }
+template <int LOGN>
+__device__ __forceinline__ uint32_t ntt_pos(int c) {
+  constexpr int R = Ntt<LOGN>::R;
+  if constexpr (R == 0) return 16 * threadIdx.x + c;
+  return ((threadIdx.x + Ntt<LOGN>::T * (c >> R)) << R) + (c & ((1 << R) - 1));
+}
+// Stages s .. s + RR - 1 of the forward transform on the 2^RR values of group
+// `grp` (of 2^s) in v[at ..].
+template <int RR>
+__device__ __forceinline__ void fwd_stages(uint32_t (&v)[16], int at, int s, uint32_t grp, const uint2 *w, uint32_t q) {
+#pragma unroll
+  for (int i = 0; i < RR; ++i) {
+    __builtin_amdgcn_sched_barrier(0);  // not all stages' twiddles at once
+    const uint2 *ws = w + ((1u + grp) << i) + ((((1u << s) - 1u)) << i);
+#pragma unroll
+    for (int c = 0; c < (1 << RR); ++c) {
+      const int h = 1 << (RR - 1 - i);
+      if (c & h) continue;
+      const uint2 t = ws[c >> (RR - i)];
+      uint32_t u = v[at + c];
+      u = u >= 2 * q ? u - 2 * q : u;
+      const uint32_t x = mul_lazy(v[at + c + h], t, q);
+      v[at + c] = u + x;
+      v[at + c + h] = u - x + 2 * q;
     }
-  } else {
-    const uint32_t *w = T.ipsi + (uint64_t)i * n, *ws = T.ipsi_s + (uint64_t)i * n;
-    for (uint32_t m = n, t = 1; m > 1; m >>= 1, t <<= 1) {
-      const uint32_t h = m >> 1;
-      for (uint32_t b = threadIdx.x; b < half; b += blockDim.x) {
-        const uint32_t grp = b / t, k = b % t;
-        const uint32_t j = 2 * grp * t + k;
-        const uint32_t s = w[h + grp], ss = ws[h + grp];
-        const uint32_t u = a[j], v = a[j + t];
-        a[j] = add_q(u, v, q);
-        a[j + t] = mul_shoup(sub_q(u, v, q), s, ss, q);
-      }
-      __syncthreads();
-    }
-    for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) a[j] = mul_shoup(a[j], T.p[i].ninv, T.p[i].ninv_s, q);
-    __syncthreads();
   }
-  for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) y[j] = a[j];
+}
+// Stages with half-lengths 2^e .. 2^(e + RR - 1) of the inverse transform.
+template <int LOGN, int RR>
+__device__ __forceinline__ void inv_stages(uint32_t (&v)[16], int at, int e, uint32_t grp, const uint2 *w, uint32_t q) {
+#pragma unroll
+  for (int i = 0; i < RR; ++i) {
+    __builtin_amdgcn_sched_barrier(0);
+    const uint2 *ws = w + (Ntt<LOGN>::N >> (e + i + 1)) + (grp << (RR - 1 - i));
+#pragma unroll
+    for (int c = 0; c < (1 << RR); ++c) {
+      if (c & (1 << i)) continue;
+      const uint2 t = ws[c >> (i + 1)];
+      const uint32_t u = v[at + c], x = v[at + c + (1 << i)];
+      const uint32_t y = u + x;
+      v[at + c] = y >= 2 * q ? y - 2 * q : y;
+      v[at + c + (1 << i)] = mul_lazy(u - x + 2 * q, t, q);
+    }
+  }
+}
+// Set of 16 values `stride` apart: thread t's set starts at set_base.
+__device__ __forceinline__ uint32_t set_base(uint32_t stride) {
+  return (threadIdx.x / stride) * (16 * stride) + threadIdx.x % stride;
+}
+__device__ __forceinline__ void to_lds(uint32_t *a, const uint32_t (&v)[16], uint32_t base, uint32_t stride) {
+#pragma unroll
+  for (int c = 0; c < 16; ++c) a[pad(base + c * stride)] = v[c];
+}
+__device__ __forceinline__ void from_lds(uint32_t (&v)[16], const uint32_t *a, uint32_t base, uint32_t stride) {
+#pragma unroll
+  for (int c = 0; c < 16; ++c) v[c] = a[pad(base + c * stride)];
+}
+template <int LOGN>
+__device__ __forceinline__ void ntt_forward(uint32_t (&v)[16], uint32_t *a, const uint2 *w, uint32_t q) {
+  using C = Ntt<LOGN>;
+  constexpr uint32_t S1 = C::T, S2 = C::N >> 8, S3 = C::N >> 12;
+  fwd_stages<4>(v, 0, 0, 0, w, q);
+  to_lds(a, v, threadIdx.x, S1);
+  __syncthreads();
+  from_lds(v, a, set_base(S2), S2);
+  fwd_stages<4>(v, 0, 4, threadIdx.x / S2, w, q);
+  to_lds(a, v, set_base(S2), S2);
+  __syncthreads();
+  from_lds(v, a, set_base(S3), S3);
+  fwd_stages<4>(v, 0, 8, threadIdx.x / S3, w, q);
+  if constexpr (C::R > 0) {
+    to_lds(a, v, set_base(S3), S3);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 16; ++c) v[c] = a[pad(ntt_pos<LOGN>(c))];
+#pragma unroll
+    for (int k = 0; k < (16 >> C::R); ++k) fwd_stages<C::R>(v, k << C::R, 12, threadIdx.x + C::T * k, w, q);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    const uint32_t x = v[c] >= 2 * q ? v[c] - 2 * q : v[c];
+    v[c] = x >= q ? x - q : x;
+  }
+}
+template <int LOGN>
+__device__ __forceinline__ void ntt_inverse(uint32_t (&v)[16], uint32_t *a, const uint2 *w, const Prime &P) {
+  using C = Ntt<LOGN>;
+  constexpr uint32_t S1 = C::T, S2 = C::N >> 8, S3 = C::N >> 12;
+  const uint32_t q = P.q;
+  if constexpr (C::R > 0) {
+#pragma unroll
+    for (int k = 0; k < (16 >> C::R); ++k) inv_stages<LOGN, C::R>(v, k << C::R, 0, threadIdx.x + C::T * k, w, q);
+#pragma unroll
+    for (int c = 0; c < 16; ++c) a[pad(ntt_pos<LOGN>(c))] = v[c];
+    __syncthreads();
+    from_lds(v, a, set_base(S3), S3);
+  }
+  inv_stages<LOGN, 4>(v, 0, C::R, threadIdx.x / S3, w, q);
+  to_lds(a, v, set_base(S3), S3);
+  __syncthreads();
+  from_lds(v, a, set_base(S2), S2);
+  inv_stages<LOGN, 4>(v, 0, C::R + 4, threadIdx.x / S2, w, q);
+  to_lds(a, v, set_base(S2), S2);
+  __syncthreads();
+  from_lds(v, a, threadIdx.x, S1);
+  inv_stages<LOGN, 4>(v, 0, C::R + 8, 0, w, q);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    const uint32_t x = mul_lazy(v[c], make_uint2(P.ninv, P.ninv_s), q);
+    v[c] = x >= q ? x - q : x;
+  }
+}
+
+// Forward transform in place of the L polynomials at x (key generation).
+template <int LOGN>
+__global__ __launch_bounds__(Ntt<LOGN>::T) void k_ntt(uint32_t *x, Tables T) {
+  extern __shared__ uint32_t a[];
+  x += (uint64_t)blockIdx.x * Ntt<LOGN>::N;
+  uint32_t v[16];
+#pragma unroll
+  for (int c = 0; c < 16; ++c) v[c] = x[threadIdx.x + c * Ntt<LOGN>::T];
+  ntt_forward<LOGN>(v, a, T.psi + (uint64_t)blockIdx.x * Ntt<LOGN>::N, T.p[blockIdx.x].q);
+#pragma unroll
+  for (int c = 0; c < 16; ++c) x[ntt_pos<LOGN>(c)] = v[c];
+}
+
+// Samples of ciphertext t from counters (offset + t) 3N + {0, N, 2N} (u, e0, e1),
+// one byte each, four coefficients per thread.  They go into the ciphertext's
+// own buffer: the region of (part k, prime i), N words, first holds the N bytes
+// of u and then those of e_k, which only the block that later writes the region
+// reads.  Sampled once here and not in each of the six blocks of a ciphertext:
+// ten ciphertexts at N = 2^14 took 52 us with the sampling in those blocks and
+// take 29 (4 of them here).
+__global__ __launch_bounds__(256) void k_sample_enc(uint64_t seed, uint64_t offset, uint32_t log_n, uint64_t quads,
+                                                    uint32_t *ct) {
+  const uint64_t id = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (id >= quads) return;
+  const uint64_t t = id >> (log_n - 2), N = 1ull << log_n, j = id & (N / 4 - 1);
+  const uint64_t base = (offset + t) * 3 * N + 4 * j;
+  uint32_t u = 0, e[2] = {0, 0};
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    u |= (uint32_t)(he::splitmix64(seed, base + b) % 3) << (8 * b);  // value + 1
+#pragma unroll
+    for (int k = 0; k < 2; ++k) e[k] |= binomial(he::splitmix64(seed, base + (k + 1) * N + b), kEta) << (8 * b);
+  }
+#pragma unroll
+  for (int r = 0; r < 2 * kL; ++r) {
+    uint32_t *o = ct + (t * 2 * kL + r) * N + j;
+    o[0] = u;
+    o[N / 4] = r < kL ? e[0] : e[1];
+  }
+}
+
+// Part k of ciphertext t for one prime: INTT(b u) + e0 + m or INTT(a u) + e1, from
+// the samples k_sample_enc left in its region of ct.  With it two launches
+// instead of nine: transforms, product and sums stay in registers.  Each part
+// transforms u again: a block that made both from one transform had to hold it
+// beside the inverse's values and spilled, and took 1.14 ms for 1,000
+// ciphertexts at N = 2^14 where this takes 0.8 (2.1 with a launch per step); for
+// ten the parts also spread over twice the compute units (105 -> 34 us).
+template <int LOGN>
+__global__ __launch_bounds__(Ntt<LOGN>::T) void k_encrypt(const uint32_t *pt, Tables T, const uint32_t *keys,
+                                                          uint32_t *ct) {
+  using C = Ntt<LOGN>;
+  extern __shared__ uint32_t lds[];
+  const uint32_t i = blockIdx.x % kL, k = (blockIdx.x / kL) & 1u;
+  const uint64_t t = blockIdx.x / (2 * kL);
+  const Prime P = T.p[i];
+  uint32_t *o = ct + ((t * 2 + k) * kL + i) * C::N;
+  const uint8_t *su = (const uint8_t *)o, *se = su + C::N;
+  // part 0 uses b (the third key polynomial set), part 1 a
+  const uint32_t *key = keys + ((uint64_t)(2 - k) * kL + i) * C::N;
+  uint32_t v[16];
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    const uint32_t x = su[threadIdx.x + c * C::T];
+    v[c] = x ? x - 1u : P.q - 1u;
+  }
+  ntt_forward<LOGN>(v, lds, T.psi + (uint64_t)i * C::N, P.q);
+#pragma unroll
+  for (int c = 0; c < 16; ++c) v[c] = mont_q(key[ntt_pos<LOGN>(c)], v[c], P.q, P.qinv);
+  ntt_inverse<LOGN>(v, lds, T.ipsi + (uint64_t)i * C::N, P);
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    const uint32_t x = se[threadIdx.x + c * C::T];
+    v[c] = add_q(v[c], x >= kEta ? x - kEta : P.q + x - kEta, P.q);
+  }
+  if (k == 0) {
+    const uint32_t *m = pt + (t * kL + i) * C::N;
+#pragma unroll
+    for (int c = 0; c < 16; ++c) v[c] = add_q(v[c], m[threadIdx.x + c * C::T], P.q);
+  }
+  __syncthreads();  // every sample of the region is read
+#pragma unroll
+  for (int c = 0; c < 16; ++c) o[threadIdx.x + c * C::T] = v[c];
+}
+
+// pt = c0 + INTT(NTT(c1) s) for one (ciphertext, prime), one launch instead of
+// four.
+template <int LOGN>
+__global__ __launch_bounds__(Ntt<LOGN>::T) void k_decrypt(const uint32_t *ct, Tables T, const uint32_t *s, uint32_t *pt) {
+  using C = Ntt<LOGN>;
+  extern __shared__ uint32_t lds[];
+  const uint32_t i = blockIdx.x % kL;
+  const uint64_t t = blockIdx.x / kL;
+  const Prime P = T.p[i];
+  const uint32_t *c0 = ct + (t * 2 * kL + i) * C::N, *c1 = c0 + (uint64_t)kL * C::N;
+  const uint32_t *key = s + (uint64_t)i * C::N;
+  uint32_t v[16];
+#pragma unroll
+  for (int c = 0; c < 16; ++c) v[c] = c1[threadIdx.x + c * C::T];
+  ntt_forward<LOGN>(v, lds, T.psi + (uint64_t)i * C::N, P.q);
+#pragma unroll
+  for (int c = 0; c < 16; ++c) v[c] = mont_q(key[ntt_pos<LOGN>(c)], v[c], P.q, P.qinv);
+  ntt_inverse<LOGN>(v, lds, T.ipsi + (uint64_t)i * C::N, P);
+  uint32_t *o = pt + (t * kL + i) * C::N;
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    const uint32_t j = threadIdx.x + c * C::T;
+    o[j] = add_q(v[c], c0[j], P.q);
+  }
 }
 
 // ---- pointwise ----------------------------------------------------------------
@@ -166,29 +362,20 @@ __global__ void k_keygen_finish(uint32_t n, Tables T, uint32_t *s, uint32_t *a, 
   s[idx] = sm;
 }
 
-// out[p] = key (Montgomery, NTT domain) * x[p] (NTT domain), for `polys`
-// polynomials [L][N] with strides sx and so (in words) between them.
-__global__ void k_mul_key(uint32_t n, uint32_t polys, Tables T, const uint32_t *key, const uint32_t *x, uint64_t sx,
-                          uint32_t *out, uint64_t so) {
-  const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t per = (uint64_t)kL * n;
-  if (idx >= (uint64_t)polys * per) return;
-  const uint64_t p = idx / per, r = idx % per;
-  const Prime P = T.p[r / n];
-  out[p * so + r] = mont_q(key[r], x[p * sx + r], P.q, P.qinv);
-}
-
-// out = a + b + c (c optional), [polys][L][N] with independent strides.
-__global__ void k_add3(uint32_t n, uint64_t polys, Tables T, const uint32_t *a, uint64_t sa, const uint32_t *b,
-                       uint64_t sb, const uint32_t *c, uint64_t sc, uint32_t *out, uint64_t so) {
-  const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t per = (uint64_t)kL * n;
-  if (idx >= polys * per) return;
-  const uint64_t p = idx / per, r = idx % per;
-  const uint32_t q = T.p[r / n].q;
-  uint32_t v = add_q(a[p * sa + r], b[p * sb + r], q);
-  if (c) v = add_q(v, c[p * sc + r], q);
-  out[p * so + r] = v;
+// out = x + y over sets of L residue polynomials of N = 2^log_n: `n` groups of
+// four coefficients (VEC: 16-byte aligned buffers) or single ones per thread.
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_add(uint32_t log_n, uint64_t n, Tables T, const uint32_t *x, const uint32_t *y,
+                                             uint32_t *out) {
+  const uint64_t idx = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= n) return;
+  const uint32_t q = T.p[(idx >> (VEC ? log_n - 2 : log_n)) % kL].q;
+  if constexpr (VEC) {
+    const uint4 a = ((const uint4 *)x)[idx], b = ((const uint4 *)y)[idx];
+    ((uint4 *)out)[idx] = make_uint4(add_q(a.x, b.x, q), add_q(a.y, b.y, q), add_q(a.z, b.z, q), add_q(a.w, b.w, q));
+  } else {
+    out[idx] = add_q(x[idx], y[idx], q);
+  }
 }
 
 // ---- encoding FFT ---------------------------------------------------------------
@@ -202,55 +389,103 @@ struct Cx {
 };
 __device__ __forceinline__ Cx cmul(Cx a, Cx b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
 
-// In-place radix-2 DIT FFT of length n (power of two) in LDS; sign +1 for
-// sum x_j w^(t j), -1 for the conjugate.  tw[k] = e^(2 pi i k / n), k < n/2.
-__device__ __forceinline__ void fft_lds(Cx *x, uint32_t n, uint32_t log_n, const Cx *tw, int sign) {
-  for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) {
-    const uint32_t r = __brev(j) >> (32 - log_n);
-    if (r > j) {
-      const Cx t = x[j];
-      x[j] = x[r];
-      x[r] = t;
+// Radix-2 DIT FFT of length n = 2^LOG (bit-reversed order in, natural out) by
+// n / 8 threads; sign +1 for sum x_j w^(t j), -1 for the conjugate.  tw[k] =
+// e^(2 pi i k / n), k < n/2.  Each thread runs up to three stages on eight
+// values in registers: the vector crosses LDS every three stages instead of
+// every one (13 at n = 2^13), by the same butterflies on the same values.  The
+// values come from LDS and end in registers: value k of thread t is x[fft_pos(k)].
+// One block per vector, so what a block issues bounds it: encoding and decoding
+// a vector of 2^13 slots took 83 and 78 us and take 25 and 27.
+template <int LOG>
+struct Fft {
+  static constexpr uint32_t n = 1u << LOG, T = n / 8;
+  static constexpr int kLast = LOG % 3 == 0 ? 3 : 2;  // stages of the last pass (and of the one before, LOG % 3 == 1)
+  static constexpr uint32_t kLds = n + n / 8;         // one value of padding after every 8
+};
+__device__ __forceinline__ uint32_t pad8(uint32_t i) { return i + (i >> 3); }
+// Pass of R stages from half-length 2^E on: set k of 8 >> R per thread.
+template <int LOG, int R, int E>
+__device__ __forceinline__ uint32_t fft_base(int set) {
+  const uint32_t id = threadIdx.x + Fft<LOG>::T * set;
+  return ((id >> E) << (E + R)) + (id & ((1u << E) - 1u));
+}
+template <int LOG, int R, int E>
+__device__ __forceinline__ void fft_pass(Cx (&v)[8], const Cx *x, const Cx *tw, int sign) {
+#pragma unroll
+  for (int set = 0; set < (8 >> R); ++set) {
+    const uint32_t base = fft_base<LOG, R, E>(set), off = base & ((1u << E) - 1u);
+    Cx *p = v + (set << R);
+#pragma unroll
+    for (int c = 0; c < (1 << R); ++c) p[c] = x[pad8(base + (c << E))];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+#pragma unroll
+      for (int c = 0; c < (1 << R); ++c) {
+        if (c & (1 << i)) continue;
+        const uint32_t k = off + ((uint32_t)(c & ((1 << i) - 1)) << E);
+        Cx w = tw[k << (LOG - E - i - 1)];
+        if (sign < 0) w.im = -w.im;
+        const Cx y = cmul(p[c + (1 << i)], w), u = p[c];
+        p[c] = {u.re + y.re, u.im + y.im};
+        p[c + (1 << i)] = {u.re - y.re, u.im - y.im};
+      }
     }
   }
+}
+template <int LOG, int R, int E>
+__device__ __forceinline__ void fft_store(const Cx (&v)[8], Cx *x) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k) x[pad8(fft_base<LOG, R, E>(k >> R) + ((k & ((1 << R) - 1)) << E))] = v[k];
+}
+template <int LOG>
+__device__ __forceinline__ uint32_t fft_pos(int k) {
+  constexpr int R = Fft<LOG>::kLast, E = LOG - R;
+  return fft_base<LOG, R, E>(k >> R) + ((k & ((1 << R) - 1)) << E);
+}
+template <int LOG, int E = 0>
+__device__ __forceinline__ void fft_lds(Cx (&v)[8], Cx *x, const Cx *tw, int sign) {
+  constexpr int left = LOG - E, R = left == 2 || left == 4 ? 2 : 3;
   __syncthreads();
-  for (uint32_t len = 2; len <= n; len <<= 1) {
-    const uint32_t h = len >> 1, step = n / len;
-    for (uint32_t b = threadIdx.x; b < n / 2; b += blockDim.x) {
-      const uint32_t grp = b / h, k = b % h;
-      const uint32_t j = grp * len + k;
-      Cx w = tw[k * step];
-      if (sign < 0) w.im = -w.im;
-      const Cx v = cmul(x[j + h], w), u = x[j];
-      x[j] = {u.re + v.re, u.im + v.im};
-      x[j + h] = {u.re - v.re, u.im - v.im};
-    }
-    __syncthreads();
+  fft_pass<LOG, R, E>(v, x, tw, sign);
+  if constexpr (left > R) {
+    // a thread stores where it has read, so no other thread's values are lost
+    fft_store<LOG, R, E>(v, x);
+    fft_lds<LOG, E + R>(v, x, tw, sign);
   }
 }
 
 // z: [count][n_values] doubles (n_values <= N/2) -> pt [count][L][N].
-__global__ __launch_bounds__(kFftThreads) void k_encode(const double *z, uint32_t n_values, uint32_t N,
-                                                        uint32_t log_n, double scale, const uint32_t *perm,
-                                                        const Cx *tw, const Cx *zeta, Tables T, uint32_t *pt) {
+template <int LOGN>
+__global__ __launch_bounds__(Fft<LOGN - 1>::T) void k_encode(const double *z, uint32_t n_values, double scale,
+                                                             const uint32_t *perm, const Cx *tw, const Cx *zeta,
+                                                             Tables T, uint32_t *pt) {
+  constexpr int LOG = LOGN - 1;
+  constexpr uint32_t N = 1u << LOGN, n = N / 2;
   extern __shared__ Cx x[];
-  const uint32_t n = N / 2;
   const double *zz = z + (uint64_t)blockIdx.x * n_values;
-  for (uint32_t k = threadIdx.x; k < n; k += blockDim.x) x[perm[k]] = {k < n_values ? zz[k] * scale : 0.0, 0.0};
-  __syncthreads();
-  fft_lds(x, n, log_n - 1, tw, -1);
+#pragma unroll
+  for (int k8 = 0; k8 < 8; ++k8) {
+    const uint32_t k = threadIdx.x + k8 * Fft<LOG>::T;
+    x[pad8(__brev(perm[k]) >> (32 - LOG))] = {k < n_values ? zz[k] * scale : 0.0, 0.0};
+  }
+  Cx v[8];
+  fft_lds<LOG>(v, x, tw, -1);
   uint32_t *o = pt + (uint64_t)blockIdx.x * kL * N;
   const double inv_n = 1.0 / (double)n;
-  for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) {
-    Cx c = x[j];
+#pragma unroll
+  for (int k8 = 0; k8 < 8; ++k8) {
+    const uint32_t j = fft_pos<LOG>(k8);
+    Cx c = v[k8];
     c.re *= inv_n;
     c.im *= inv_n;
     const Cx zc = {zeta[j].re, -zeta[j].im};  // zeta^-j
     const Cx u = cmul(c, zc);
     const int64_t lo = (int64_t)rint(u.re), hi = (int64_t)rint(u.im);
+#pragma unroll
     for (int i = 0; i < kL; ++i) {
-      o[(uint64_t)i * N + j] = to_residue(lo, T.p[i].q);
-      o[(uint64_t)i * N + j + n] = to_residue(hi, T.p[i].q);
+      o[(uint64_t)i * N + j] = to_residue(lo, T.p[i]);
+      o[(uint64_t)i * N + j + n] = to_residue(hi, T.p[i]);
     }
   }
 }
@@ -259,18 +494,20 @@ __global__ __launch_bounds__(kFftThreads) void k_encode(const double *z, uint32_
 // Garner's mixed-radix digits, the integer x = d0 + q0 (d1 + q1 d2) in 128
 // bits, x - Q when x > Q/2.
 struct Crt {
-  uint32_t q0q1_inv_q2;  // (q0 q1)^-1 mod q2
-  uint32_t q0_inv_q1, q0_inv_q2;
+  uint32_t q0_inv_q1;    // q0^-1 2^32 mod q1
+  uint32_t q0q1_inv_q2;  // (q0 q1)^-1 2^32 mod q2
+  uint32_t q0_q2;        // q0 2^32 mod q2
   uint64_t Q_lo, Q_hi;
 };
 __device__ __forceinline__ double crt_center(uint32_t r0, uint32_t r1, uint32_t r2, const Tables &T, const Crt &C) {
+  // the primes lie between 2^29 and 2^30, so a residue of one is below twice another
   const uint32_t q0 = T.p[0].q, q1 = T.p[1].q, q2 = T.p[2].q;
   const uint32_t d0 = r0;
-  const uint32_t d1 = (uint32_t)((uint64_t)sub_q(r1, d0 % q1, q1) * C.q0_inv_q1 % q1);
+  const uint32_t d1 = mont_q(sub_q(r1, once(d0, q1), q1), C.q0_inv_q1, q1, T.p[1].qinv);
   // d2 = ((r2 - d0) q0^-1 - d1) q1^-1 mod q2 = (r2 - d0 - q0 d1) (q0 q1)^-1
-  const uint64_t t = ((uint64_t)q0 % q2) * d1 % q2;
-  const uint32_t v = sub_q(sub_q(r2, d0 % q2, q2), (uint32_t)t, q2);
-  const uint32_t d2 = (uint32_t)((uint64_t)v * C.q0q1_inv_q2 % q2);
+  const uint32_t t = mont_q(once(d1, q2), C.q0_q2, q2, T.p[2].qinv);
+  const uint32_t v = sub_q(sub_q(r2, once(d0, q2), q2), t, q2);
+  const uint32_t d2 = mont_q(v, C.q0q1_inv_q2, q2, T.p[2].qinv);
   const unsigned __int128 x =
       (unsigned __int128)d0 + (unsigned __int128)q0 * ((unsigned __int128)d1 + (unsigned __int128)q1 * d2);
   const unsigned __int128 Q = ((unsigned __int128)C.Q_hi << 64) | C.Q_lo;
@@ -281,21 +518,29 @@ __device__ __forceinline__ double crt_center(uint32_t r0, uint32_t r1, uint32_t 
 }
 
 // pt [count][L][N] -> z [count][n_values].
-__global__ __launch_bounds__(kFftThreads) void k_decode(const uint32_t *pt, uint32_t n_values, uint32_t N,
-                                                        uint32_t log_n, double inv_scale, const uint32_t *perm,
-                                                        const Cx *tw, const Cx *zeta, Tables T, Crt C, double *z) {
+template <int LOGN>
+__global__ __launch_bounds__(Fft<LOGN - 1>::T) void k_decode(const uint32_t *pt, uint32_t n_values, double inv_scale,
+                                                             const uint32_t *perm, const Cx *tw, const Cx *zeta,
+                                                             Tables T, Crt C, double *z) {
+  constexpr int LOG = LOGN - 1;
+  constexpr uint32_t N = 1u << LOGN, n = N / 2;
   extern __shared__ Cx x[];
-  const uint32_t n = N / 2;
   const uint32_t *p = pt + (uint64_t)blockIdx.x * kL * N;
-  for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) {
+#pragma unroll
+  for (int k8 = 0; k8 < 8; ++k8) {
+    const uint32_t j = threadIdx.x + k8 * Fft<LOG>::T;
     const double lo = crt_center(p[j], p[N + j], p[2 * N + j], T, C);
     const double hi = crt_center(p[j + n], p[N + j + n], p[2 * N + j + n], T, C);
-    x[j] = cmul({lo * inv_scale, hi * inv_scale}, zeta[j]);
+    x[pad8(__brev(j) >> (32 - LOG))] = cmul({lo * inv_scale, hi * inv_scale}, zeta[j]);
   }
+  Cx v[8];
+  fft_lds<LOG>(v, x, tw, +1);
   __syncthreads();
-  fft_lds(x, n, log_n - 1, tw, +1);
+#pragma unroll
+  for (int k8 = 0; k8 < 8; ++k8) x[pad8(fft_pos<LOG>(k8))] = v[k8];
+  __syncthreads();
   double *zz = z + (uint64_t)blockIdx.x * n_values;
-  for (uint32_t k = threadIdx.x; k < n_values; k += blockDim.x) zz[k] = x[perm[k]].re;
+  for (uint32_t k = threadIdx.x; k < n_values; k += Fft<LOG>::T) zz[k] = x[pad8(perm[k])].re;
 }
 
 // ---- host -----------------------------------------------------------------------
@@ -358,41 +603,23 @@ struct he_ckks {
   uint64_t seed = 0;
   Tables T{};
   Crt C{};
-  uint32_t *d_tab = nullptr;   // psi, psi_s, ipsi, ipsi_s: 4 [L][N]
+  uint32_t *d_tab = nullptr;   // psi and ipsi, each with its Shoup companion: 2 [L][N][2]
   uint32_t *d_keys = nullptr;  // s, a, b: 3 [L][N] (NTT domain, Montgomery form)
   uint32_t *d_perm = nullptr;  // t_k for k < N/2
   Cx *d_tw = nullptr;          // e^(2 pi i k / (N/2)), k < N/4
   Cx *d_zeta = nullptr;        // zeta^j, j < N/2
-  std::mutex mu;
-  uint32_t *d_scratch = nullptr;  // encryption/decryption temporaries
-  size_t scratch_words = 0;
 };
 
 namespace {
 
-int scratch(he_ckks *c, size_t words, uint32_t **out) {
-  if (c->scratch_words < words) {
-    if (c->d_scratch) CK_TRY(hipFree(c->d_scratch));
-    c->d_scratch = nullptr;
-    c->scratch_words = 0;
-    if (hipMalloc(&c->d_scratch, words * 4) != hipSuccess) return fail(HE_ERR_OOM, "out of device memory");
-    c->scratch_words = words;
-  }
-  *out = c->d_scratch;
-  return HE_OK;
-}
-
 inline uint32_t blocks(uint64_t n, uint32_t per) { return (uint32_t)((n + per - 1) / per); }
 
-// polys polynomials [L][N], sin / sout words apart (0: packed), in -> out
-// (may be the same buffer).
-hipError_t ntt(const he_ckks *c, const uint32_t *in, uint32_t *out, uint64_t polys, bool inverse, hipStream_t s,
-               uint64_t sin = 0, uint64_t sout = 0) {
-  if (!polys) return hipSuccess;
-  const uint64_t per = (uint64_t)kL * c->n;
-  hipLaunchKernelGGL(k_ntt, dim3((uint32_t)(polys * kL)), dim3(kNttThreads), c->n * 4, s, in, sin ? sin : per, out,
-                     sout ? sout : per, c->n, c->log_n, c->T, (int)inverse);
-  return hipGetLastError();
+// f(integral_constant<log_n>) for this context's ring.
+template <typename F>
+void for_ring(uint32_t log_n, F f) {
+  if (log_n == 12) f(std::integral_constant<int, 12>{});
+  else if (log_n == 13) f(std::integral_constant<int, 13>{});
+  else f(std::integral_constant<int, 14>{});
 }
 
 }  // namespace
@@ -425,6 +652,7 @@ int he_ckks_create(uint32_t log_n, uint32_t scale_bits, uint64_t seed, he_ckks *
     uint32_t inv = 1;  // q^-1 mod 2^32 by Newton
     for (int k = 0; k < 5; ++k) inv *= 2u - (uint32_t)q * inv;
     P.qinv = 0u - inv;
+    P.r1 = (uint32_t)((1ull << 32) % q);
     P.r2 = (uint32_t)(((unsigned __int128)1 << 64) % q);
     P.ninv = (uint32_t)pow_mod(N, q - 2, q);
     P.ninv_s = (uint32_t)(((uint64_t)P.ninv << 32) / q);
@@ -440,17 +668,19 @@ int he_ckks_create(uint32_t log_n, uint32_t scale_bits, uint64_t seed, he_ckks *
     for (uint32_t k = 0; k < N; ++k) {
       const uint32_t e = bitrev(k, log_n);
       const uint64_t w = pow_mod(psi, e, q), iw = pow_mod(ipsi, e, q);
-      tab[(0ull * kL + i) * N + k] = (uint32_t)w;
-      tab[(1ull * kL + i) * N + k] = (uint32_t)((w << 32) / q);
-      tab[(2ull * kL + i) * N + k] = (uint32_t)iw;
-      tab[(3ull * kL + i) * N + k] = (uint32_t)((iw << 32) / q);
+      uint32_t *t = &tab[2 * ((uint64_t)i * N + k)], *it = t + 2ull * kL * N;
+      t[0] = (uint32_t)w;
+      t[1] = (uint32_t)((w << 32) / q);
+      it[0] = (uint32_t)iw;
+      it[1] = (uint32_t)((iw << 32) / q);
     }
   }
   {
     const uint64_t q0 = qs[0], q1 = qs[1], q2 = qs[2];
-    c->C.q0_inv_q1 = (uint32_t)pow_mod(q0 % q1, q1 - 2, q1);
-    c->C.q0_inv_q2 = (uint32_t)pow_mod(q0 % q2, q2 - 2, q2);
-    c->C.q0q1_inv_q2 = (uint32_t)pow_mod((unsigned __int128)q0 * q1 % q2, q2 - 2, q2);
+    // in Montgomery form
+    c->C.q0_inv_q1 = (uint32_t)((pow_mod(q0 % q1, q1 - 2, q1) << 32) % q1);
+    c->C.q0q1_inv_q2 = (uint32_t)((pow_mod((unsigned __int128)q0 * q1 % q2, q2 - 2, q2) << 32) % q2);
+    c->C.q0_q2 = (uint32_t)((q0 % q2 << 32) % q2);
     const unsigned __int128 Q = (unsigned __int128)q0 * q1 * q2;
     c->C.Q_lo = (uint64_t)Q;
     c->C.Q_hi = (uint64_t)(Q >> 64);
@@ -471,14 +701,18 @@ int he_ckks_create(uint32_t log_n, uint32_t scale_bits, uint64_t seed, he_ckks *
     he_ckks_free(c);
     return rc;
   };
-  // The N/2-point FFT holds up to 128 KiB of LDS, the NTT up to 64 KiB: ask
+  // The N/2-point FFT holds up to 144 KiB of LDS, the NTT up to 68 KiB: ask
   // for that much dynamic LDS (best effort; a size the device refuses shows
   // up as a launch error of the kernel).
-  (void)hipFuncSetAttribute((const void *)k_encode, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)((N / 2) * sizeof(Cx)));
-  (void)hipFuncSetAttribute((const void *)k_decode, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)((N / 2) * sizeof(Cx)));
-  (void)hipFuncSetAttribute((const void *)k_ntt, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(N * 4));
+  for_ring(log_n, [](auto ln) {
+    constexpr int LN = decltype(ln)::value;
+    const int fft = (int)(Fft<LN - 1>::kLds * sizeof(Cx)), ntt = (int)(Ntt<LN>::kLds * 4);
+    (void)hipFuncSetAttribute((const void *)k_encode<LN>, hipFuncAttributeMaxDynamicSharedMemorySize, fft);
+    (void)hipFuncSetAttribute((const void *)k_decode<LN>, hipFuncAttributeMaxDynamicSharedMemorySize, fft);
+    (void)hipFuncSetAttribute((const void *)k_ntt<LN>, hipFuncAttributeMaxDynamicSharedMemorySize, ntt);
+    (void)hipFuncSetAttribute((const void *)k_encrypt<LN>, hipFuncAttributeMaxDynamicSharedMemorySize, ntt);
+    (void)hipFuncSetAttribute((const void *)k_decrypt<LN>, hipFuncAttributeMaxDynamicSharedMemorySize, ntt);
+  });
   (void)hipGetLastError();
   if (hipMalloc(&c->d_tab, tab.size() * 4) != hipSuccess || hipMalloc(&c->d_keys, 3ull * kL * N * 4) != hipSuccess ||
       hipMalloc(&c->d_perm, n * 4) != hipSuccess || hipMalloc(&c->d_tw, tw.size() * sizeof(Cx)) != hipSuccess ||
@@ -489,20 +723,21 @@ int he_ckks_create(uint32_t log_n, uint32_t scale_bits, uint64_t seed, he_ckks *
       hipMemcpy(c->d_tw, tw.data(), tw.size() * sizeof(Cx), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(c->d_zeta, zeta.data(), n * sizeof(Cx), hipMemcpyHostToDevice) != hipSuccess)
     return cleanup(fail(HE_ERR_DEVICE, "copy of the tables failed"));
-  c->T.psi = c->d_tab;
-  c->T.psi_s = c->d_tab + 1ull * kL * N;
-  c->T.ipsi = c->d_tab + 2ull * kL * N;
-  c->T.ipsi_s = c->d_tab + 3ull * kL * N;
+  c->T.psi = (const uint2 *)c->d_tab;
+  c->T.ipsi = c->T.psi + (uint64_t)kL * N;
   // keys: s (ternary), e (centered binomial), a (uniform); b = -a s + e
   uint32_t *s = c->d_keys, *a = s + kL * N, *b = a + kL * N, *ek = nullptr;
   if (hipMalloc(&ek, (size_t)kL * N * 4) != hipSuccess) return cleanup(fail(HE_ERR_OOM, "out of device memory"));
   const uint32_t g = blocks(N, 256);
-  hipLaunchKernelGGL(k_sample, dim3(g), dim3(256), 0, 0, 0, seed, 0ull, 0ull, N, 1u, c->T, s);
-  hipLaunchKernelGGL(k_sample, dim3(g), dim3(256), 0, 0, 1, seed, kKeyEBase, 0ull, N, 1u, c->T, ek);
-  hipLaunchKernelGGL(k_sample, dim3(g), dim3(256), 0, 0, 2, seed, kKeyABase, 0ull, N, 1u, c->T, a);
-  hipError_t err = ntt(c, s, s, 1, false, 0);
-  if (err == hipSuccess) err = ntt(c, a, a, 1, false, 0);
-  if (err == hipSuccess) err = ntt(c, ek, ek, 1, false, 0);
+  hipLaunchKernelGGL(k_sample, dim3(g), dim3(256), 0, 0, 0, seed, 0ull, N, c->T, s);
+  hipLaunchKernelGGL(k_sample, dim3(g), dim3(256), 0, 0, 1, seed, kKeyEBase, N, c->T, ek);
+  hipLaunchKernelGGL(k_sample, dim3(g), dim3(256), 0, 0, 2, seed, kKeyABase, N, c->T, a);
+  for_ring(log_n, [&](auto ln) {
+    constexpr int LN = decltype(ln)::value;
+    for (uint32_t *x : {s, a, ek})
+      hipLaunchKernelGGL(k_ntt<LN>, dim3(kL), dim3(Ntt<LN>::T), Ntt<LN>::kLds * 4, 0, x, c->T);
+  });
+  hipError_t err = hipGetLastError();
   if (err == hipSuccess) {
     hipLaunchKernelGGL(k_keygen_finish, dim3(blocks((uint64_t)kL * N, 256)), dim3(256), 0, 0, N, c->T, s, a, ek, b);
     err = hipGetLastError();
@@ -521,7 +756,6 @@ void he_ckks_free(he_ckks *c) {
   hipFree(c->d_perm);
   hipFree(c->d_tw);
   hipFree(c->d_zeta);
-  hipFree(c->d_scratch);
   delete c;
 }
 
@@ -541,8 +775,11 @@ int he_ckks_encode(const he_ckks *c, const double *z, uint64_t count, uint32_t n
   if (count == 0) return HE_OK;
   if (!pt || (n_values && !z)) return fail(HE_ERR_ARG, "null z or pt");
   if (count > 0x7FFFFFFFull) return fail(HE_ERR_ARG, "count too large");
-  hipLaunchKernelGGL(k_encode, dim3((uint32_t)count), dim3(kFftThreads), (c->n / 2) * sizeof(Cx), s, z, n_values,
-                     c->n, c->log_n, std::ldexp(1.0, (int)c->scale_bits), c->d_perm, c->d_tw, c->d_zeta, c->T, pt);
+  for_ring(c->log_n, [&](auto ln) {
+    constexpr int LN = decltype(ln)::value;
+    hipLaunchKernelGGL(k_encode<LN>, dim3((uint32_t)count), dim3(Fft<LN - 1>::T), Fft<LN - 1>::kLds * sizeof(Cx), s, z,
+                       n_values, std::ldexp(1.0, (int)c->scale_bits), c->d_perm, c->d_tw, c->d_zeta, c->T, pt);
+  });
   CK_TRY(hipGetLastError());
   return HE_OK;
 }
@@ -554,9 +791,12 @@ int he_ckks_decode(const he_ckks *c, const uint32_t *pt, uint64_t count, uint32_
   if (count == 0 || n_values == 0) return HE_OK;
   if (!pt || !z) return fail(HE_ERR_ARG, "null pt or z");
   if (count > 0x7FFFFFFFull) return fail(HE_ERR_ARG, "count too large");
-  hipLaunchKernelGGL(k_decode, dim3((uint32_t)count), dim3(kFftThreads), (c->n / 2) * sizeof(Cx), s, pt, n_values,
-                     c->n, c->log_n, std::ldexp(1.0, -(int)c->scale_bits), c->d_perm, c->d_tw, c->d_zeta, c->T,
-                     c->C, z);
+  for_ring(c->log_n, [&](auto ln) {
+    constexpr int LN = decltype(ln)::value;
+    hipLaunchKernelGGL(k_decode<LN>, dim3((uint32_t)count), dim3(Fft<LN - 1>::T), Fft<LN - 1>::kLds * sizeof(Cx), s,
+                       pt, n_values, std::ldexp(1.0, -(int)c->scale_bits), c->d_perm, c->d_tw, c->d_zeta, c->T, c->C,
+                       z);
+  });
   CK_TRY(hipGetLastError());
   return HE_OK;
 }
@@ -566,34 +806,14 @@ int he_ckks_encrypt(he_ckks *c, const uint32_t *pt, uint64_t count, uint64_t see
   if (!c) return fail(HE_ERR_ARG, "null context");
   if (count == 0) return HE_OK;
   if (!pt || !ct) return fail(HE_ERR_ARG, "null pt or ct");
-  const uint32_t N = c->n;
-  const uint64_t per = (uint64_t)kL * N;
-  if (count * 2 * kL > 0x7FFFFFFFull || count * N > 0xFFFFFFFFull) return fail(HE_ERR_ARG, "count too large");
-  std::lock_guard<std::mutex> lk(c->mu);
-  uint32_t *tmp = nullptr;
-  int rc = scratch(c, 3 * count * per, &tmp);  // u, e0, e1 of every ciphertext
-  if (rc) return rc;
-  uint32_t *u = tmp, *e0 = tmp + count * per, *e1 = e0 + count * per;
-  const uint32_t g = blocks(count * N, 256);
-  // ciphertext t: u, e0, e1 at counters (offset + t) 3N + {0, N, 2N}
-  hipLaunchKernelGGL(k_sample, dim3(g), dim3(256), 0, s, 0, seed, offset * 3 * N, 3ull * N, N, (uint32_t)count,
-                     c->T, u);
-  hipLaunchKernelGGL(k_sample, dim3(g), dim3(256), 0, s, 1, seed, offset * 3 * N + N, 3ull * N, N,
-                     (uint32_t)count, c->T, e0);
-  hipLaunchKernelGGL(k_sample, dim3(g), dim3(256), 0, s, 1, seed, offset * 3 * N + 2 * N, 3ull * N, N,
-                     (uint32_t)count, c->T, e1);
-  CK_TRY(hipGetLastError());
-  CK_TRY(ntt(c, u, u, count, false, s));
-  const uint32_t *a = c->d_keys + per, *b = a + per;
-  // ct[t] = (INTT(b u) + e0 + m, INTT(a u) + e1); ct is [count][2][L][N]
-  const uint32_t gp = blocks(count * per, 256);
-  hipLaunchKernelGGL(k_mul_key, dim3(gp), dim3(256), 0, s, N, (uint32_t)count, c->T, b, u, per, ct, 2 * per);
-  hipLaunchKernelGGL(k_mul_key, dim3(gp), dim3(256), 0, s, N, (uint32_t)count, c->T, a, u, per, ct + per, 2 * per);
-  CK_TRY(hipGetLastError());
-  CK_TRY(ntt(c, ct, ct, 2 * count, true, s));
-  hipLaunchKernelGGL(k_add3, dim3(gp), dim3(256), 0, s, N, count, c->T, ct, 2 * per, e0, per, pt, per, ct, 2 * per);
-  hipLaunchKernelGGL(k_add3, dim3(gp), dim3(256), 0, s, N, count, c->T, ct + per, 2 * per, e1, per,
-                     (const uint32_t *)nullptr, 0ull, ct + per, 2 * per);
+  if (count * 2 * kL > 0x7FFFFFFFull || count * c->n > 0xFFFFFFFFull) return fail(HE_ERR_ARG, "count too large");
+  const uint64_t quads = count * (c->n / 4);
+  hipLaunchKernelGGL(k_sample_enc, dim3(blocks(quads, 256)), dim3(256), 0, s, seed, offset, c->log_n, quads, ct);
+  for_ring(c->log_n, [&](auto ln) {
+    constexpr int LN = decltype(ln)::value;
+    hipLaunchKernelGGL(k_encrypt<LN>, dim3((uint32_t)(count * kL * 2)), dim3(Ntt<LN>::T), Ntt<LN>::kLds * 4, s, pt,
+                       c->T, c->d_keys, ct);
+  });
   CK_TRY(hipGetLastError());
   return HE_OK;
 }
@@ -603,9 +823,11 @@ int he_ckks_add(const he_ckks *c, const uint32_t *x, const uint32_t *y, uint64_t
   if (!c) return fail(HE_ERR_ARG, "null context");
   if (count == 0) return HE_OK;
   if (!x || !y || !out) return fail(HE_ERR_ARG, "null x, y or out");
-  const uint64_t per = (uint64_t)kL * c->n;
-  hipLaunchKernelGGL(k_add3, dim3(blocks(2 * count * per, 256)), dim3(256), 0, s, c->n, 2 * count, c->T, x, per, y,
-                     per, (const uint32_t *)nullptr, 0ull, out, per);
+  const uint64_t words = 2 * count * kL * (uint64_t)c->n;
+  if ((((uintptr_t)x | (uintptr_t)y | (uintptr_t)out) & 15u) == 0)
+    hipLaunchKernelGGL(k_add<true>, dim3(blocks(words / 4, 256)), dim3(256), 0, s, c->log_n, words / 4, c->T, x, y, out);
+  else
+    hipLaunchKernelGGL(k_add<false>, dim3(blocks(words, 256)), dim3(256), 0, s, c->log_n, words, c->T, x, y, out);
   CK_TRY(hipGetLastError());
   return HE_OK;
 }
@@ -614,16 +836,12 @@ int he_ckks_decrypt(const he_ckks *c, const uint32_t *ct, uint64_t count, uint32
   if (!c) return fail(HE_ERR_ARG, "null context");
   if (count == 0) return HE_OK;
   if (!ct || !pt) return fail(HE_ERR_ARG, "null ct or pt");
-  const uint64_t per = (uint64_t)kL * c->n;
   if (count * kL > 0x7FFFFFFFull) return fail(HE_ERR_ARG, "count too large");
-  // pt = c0 + INTT(NTT(c1) s): NTT of every c1 into pt (strided input)
-  CK_TRY(ntt(c, ct + per, pt, count, false, s, 2 * per, per));
-  const uint32_t gp = blocks(count * per, 256);
-  hipLaunchKernelGGL(k_mul_key, dim3(gp), dim3(256), 0, s, c->n, (uint32_t)count, c->T, c->d_keys, pt, per, pt, per);
-  CK_TRY(hipGetLastError());
-  CK_TRY(ntt(c, pt, pt, count, true, s));
-  hipLaunchKernelGGL(k_add3, dim3(gp), dim3(256), 0, s, c->n, count, c->T, pt, per, ct, 2 * per,
-                     (const uint32_t *)nullptr, 0ull, pt, per);
+  for_ring(c->log_n, [&](auto ln) {
+    constexpr int LN = decltype(ln)::value;
+    hipLaunchKernelGGL(k_decrypt<LN>, dim3((uint32_t)(count * kL)), dim3(Ntt<LN>::T), Ntt<LN>::kLds * 4, s, ct, c->T,
+                       c->d_keys, pt);
+  });
   CK_TRY(hipGetLastError());
   return HE_OK;
 }
