@@ -258,18 +258,19 @@ uint64_t plan_table_bytes(int KP, int kind, const he::PowPlan &p) {
 // with the rest in a second launch at a wider one.
 // The constants are milliseconds measured at one and at several waves per
 // SIMD (MI355X, about 2.15 GHz under this load); only their ratios matter.
-// E.g. 200,000 lifts at 2048 bits: 81 ms for 196,608 at one lane and 3.3 ms for
-// the rest at 8 lanes, against 90 ms in one launch and 105 ms at 8 lanes.
+// E.g. 200,000 lifts at 2048 bits: 81.3 ms for 196,608 at one lane and 2.9 ms
+// for the rest at 8 lanes; in one launch 83.7-95 ms at one lane (an uneven last
+// wave), 93 ms at 2 and 104 ms at 8.
 struct PowCost {
   int G;
   double first, more;
 };
 const std::vector<PowCost> &pow_costs(int KP, int kind) {
-  static const std::vector<PowCost> mod16 = {{1, .87, .83}, {2, .88, .59}, {4, .63, .37}, {8, .745, .34}, {16, 1.13, .37}};
-  static const std::vector<PowCost> mod32 = {{1, 5.65, 5.85}, {2, 3.8, 2.9}, {4, 2.55, 1.73}, {8, 2.33, 1.32}, {16, 2.6, 1.15}};
-  static const std::vector<PowCost> pair16 = {{1, 2.03, 1.85}, {2, 1.29, 1.0}, {4, .88, .58}, {8, .80, .41}, {16, .866, .39}};
-  static const std::vector<PowCost> pair32 = {{1, 14.1, 13.5}, {2, 8.0, 7.4}, {4, 5.1, 3.9}, {8, 3.25, 2.16}, {16, 2.86, 1.62}};
-  static const std::vector<PowCost> pair64 = {{8, 19.2, 13.3}, {16, 12.45, 8.1}};
+  static const std::vector<PowCost> mod16 = {{1, .89, .73}, {2, .88, .55}, {4, .63, .34}, {8, .72, .32}, {16, 1.13, .35}};
+  static const std::vector<PowCost> mod32 = {{1, 5.8, 5.3}, {2, 3.75, 2.85}, {4, 2.37, 1.65}, {8, 2.26, 1.22}, {16, 2.4, 1.12}};
+  static const std::vector<PowCost> pair16 = {{1, 1.93, 1.72}, {2, 1.2, .98}, {4, .88, .55}, {8, .72, .41}, {16, .78, .38}};
+  static const std::vector<PowCost> pair32 = {{1, 13.1, 12.1}, {2, 7.95, 7.1}, {4, 4.7, 3.6}, {8, 2.9, 2.1}, {16, 2.58, 1.53}};
+  static const std::vector<PowCost> pair64 = {{8, 17.1, 13.7}, {16, 11.1, 8.0}};
   if (kind == 4) return KP == 1 ? mod16 : mod32;
   if (kind == 1) return KP == 1 ? pair32 : pair64;
   return KP == 1 ? pair16 : pair32;

@@ -30,7 +30,7 @@ struct SeqPair {
   __device__ __forceinline__ SeqPair(const DPair &c, uint32_t *row) : lds(row) {
     ld29<K, G>(M.n, c.c[kHistVariant] + 2 * he29::kPairN * S);
     M.ninv = c.ninv & kMask29;
-    M.mask = kMask29;
+    M.mask = mask_vgpr();
     if (glane<G>() == 0) lds[kM] = 0;
   }
   __device__ __forceinline__ void settle(uint32_t (&t)[K], const uint64_t (&C)[K]) const {

@@ -59,7 +59,7 @@ __device__ __forceinline__ uint32_t bcast_first(uint32_t v) {
   if constexpr (G == 16) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x150, 0xF, 0xF, false);
   } else if constexpr (G == 8) {
-    const int t = __builtin_amdgcn_update_dpp(0, (int)v, 0x150, 0xF, 0x3, false);
+    const int t = __builtin_amdgcn_mov_dpp((int)v, 0x150, 0xF, 0x3, false);  // the other banks come next
     return (uint32_t)__builtin_amdgcn_update_dpp(t, (int)v, 0x158, 0xF, 0xC, false);
   } else if constexpr (G == 4) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x00, 0xF, 0xF, false);

@@ -90,56 +90,36 @@ __device__ __forceinline__ void st29(uint32_t *p, const uint32_t (&x)[K]) {
   }
 }
 
+// 2^29 - 1 in a VGPR, opaque so that it is not turned back into a literal (which
+// a DPP instruction cannot hold).
+__device__ __forceinline__ uint32_t mask_vgpr() {
+  uint32_t m = kMask29;
+  asm("" : "+v"(m));
+  return m;
+}
+
 template <int K, int G>
 __device__ __forceinline__ Mod29<K> load_mod29(const DMod &D) {
   Mod29<K> m;
   ld29<K, G>(m.n, D.N29[he29::variant(G)]);
   m.ninv = D.ninv & kMask29;
-  m.mask = kMask29;
+  m.mask = mask_vgpr();
   return m;
 }
 
-
 // x from the group's first lane (resp. the next lane, the last lane reading
-// the first), masked to 29 bits, in one v_and_b32_dpp (two, each writing one
-// half of the row, for the 8-lane broadcast; the 8-lane hand-down uses
-// row_shl:1, see rotate_next).  The s_nop gives the DPP read of x the two
-// wait states it needs after the VALU write of x; it costs this wave an issue
-// cycle, not a VALU slot.
+// the first), masked to 29 bits.  Written as a move and an AND: the compiler
+// folds them into one v_and_b32_dpp and puts other instructions in the two wait
+// states a DPP read needs after the write of x.  As one asm statement it had an
+// s_nop 1 in every step: 512 decryptions at 1024 bits 800 -> 700 us, 3,000
+// encryptions at 2048 bits 5.33 -> 4.91 ms without it.
 template <int G>
 __device__ __forceinline__ uint32_t bcast_first_m29(uint32_t x, uint32_t mask) {
-  uint32_t r;
-  if constexpr (G == 2)
-    asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 quad_perm:[0,0,2,2] row_mask:0xf bank_mask:0xf"
-        : "=v"(r) : "v"(x), "v"(mask));
-  else if constexpr (G == 4)
-    asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 quad_perm:[0,0,0,0] row_mask:0xf bank_mask:0xf"
-        : "=v"(r) : "v"(x), "v"(mask));
-  else if constexpr (G == 16)
-    asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf"
-        : "=v"(r) : "v"(x), "v"(mask));
-  else
-    asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0x3\n\t"
-        "v_and_b32_dpp %0, %1, %2 row_newbcast:8 row_mask:0xf bank_mask:0xc"
-        : "=&v"(r) : "v"(x), "v"(mask));
-  return r;
+  return bcast_first<G>(x) & mask;
 }
 template <int G>
 __device__ __forceinline__ uint32_t rotate_next_m29(uint32_t x, uint32_t mask) {
-  uint32_t r;
-  if constexpr (G == 2)
-    asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf"
-        : "=v"(r) : "v"(x), "v"(mask));
-  else if constexpr (G == 4)
-    asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 quad_perm:[1,2,3,0] row_mask:0xf bank_mask:0xf"
-        : "=v"(r) : "v"(x), "v"(mask));
-  else if constexpr (G == 16)
-    asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 row_ror:15 row_mask:0xf bank_mask:0xf"
-        : "=v"(r) : "v"(x), "v"(mask));
-  else
-    asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 row_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-        : "=v"(r) : "v"(x), "v"(mask));
-  return r;
+  return rotate_next<G>(x) & mask;
 }
 
 // One step for multiplier limb ai (see the header comment).  The lane's new

@@ -26,35 +26,48 @@
 // engines are for batches too small for 64 integers per wave.
 //
 // Measured (2048-bit key, against the same powers as one integer mod P^2 at 4
-// to 16 lanes): 200,000 lifts 131 -> 85 ms, 16,384 decryptions 12.2 -> 8.1 ms,
-// 2,006 lifts 4.4 -> 2.9 ms, 2,501 pairs of powers mod n^2 28.5 -> 19.3 ms.
-// What bounds it: VALU issue (a LanePair square is 4,554 multiply-adds in 5,467
-// instructions, 4.2 cycles each); below a wave per SIMD, the latency of a step.
+// to 16 lanes): 200,000 lifts 131 -> 84 ms, 16,384 decryptions 12.2 -> 8.0 ms,
+// 2,006 lifts 4.4 -> 2.6 ms, 2,501 pairs of powers mod n^2 28.5 -> 17.0 ms.
+// What bounds it: VALU issue (a LanePair square is 4,554 multiply-adds of 4.2
+// cycles); below a wave per SIMD, the latency of a step.
 #pragma once
 #include "mont29.hpp"
 
 namespace he {
 
 __device__ __forceinline__ uint64_t mad(uint32_t x, uint32_t y, uint64_t acc) { return (uint64_t)x * y + acc; }
-// a 2^s + b, s in 0..4 per lane
+// acc + x P: one instruction where an addition needs x extended to 64
+// bits first
+template <int P>
+__device__ __forceinline__ uint64_t add_mul(uint32_t x, uint64_t acc) {
+  uint64_t k;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, %0" : "+v"(acc), "=s"(k) : "v"(x), "n"(P));
+  return acc;
+}
+// a 2^s + b: s per lane, or SH
 __device__ __forceinline__ uint64_t shl_add(uint64_t a, uint32_t s, uint64_t b) {
   uint64_t r;
   asm("v_lshl_add_u64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(s), "v"(b));
   return r;
 }
-
-// One column's sum total = P 2^sh + Q, below 2^64 unless `WIDE`; low holds
-// total mod 2^29 in its low bits and low / 2^29 + high is the carry.  A column
-// of cnt limb products each below 2^58 sums to less than cnt 2^58, so the
-// caller sets WIDE where the products weighted by 2^sh count 64 or more.
-template <bool WIDE>
-__device__ __forceinline__ void join(uint64_t P, uint32_t sh, uint64_t Q, uint64_t &low, uint64_t &high) {
-  if constexpr (WIDE) {
-    low = shl_add((uint64_t)((uint32_t)P & kMask29), sh, Q);
-    high = shl_add(P >> he29::kBits, sh, high);
-  } else {
-    low = shl_add(P, sh, Q);
-  }
+template <int SH>
+__device__ __forceinline__ uint64_t shl_add(uint64_t a, uint64_t b) {
+  uint64_t r;
+  asm("v_lshl_add_u64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "n"(SH), "v"(b));
+  return r;
+}
+// One column's sum total = P 2^SH + Q, below 2^64 unless `WIDE`: then the part of
+// P above its low 29 bits joins the carry instead (carry_wide).  A column of cnt
+// limb products each below 2^58 sums to less than cnt 2^58, so the caller sets
+// WIDE where the products weighted by 2^SH count 64 or more.
+template <bool WIDE, int SH>
+__device__ __forceinline__ uint64_t join(uint64_t P, uint64_t Q) {
+  if constexpr (WIDE) return add_mul<1 << SH>((uint32_t)P & kMask29, Q);
+  else return shl_add<SH>(P, Q);
+}
+template <bool WIDE, int SH>
+__device__ __forceinline__ void carry_wide(uint64_t P, uint64_t &carry) {
+  if constexpr (WIDE) carry = shl_add<SH>(P >> he29::kBits, carry);
 }
 
 template <int S, int k>
@@ -65,8 +78,8 @@ struct Col {
 // Ends column k of a reduction: below S its quotient digit q[k], which clears
 // the column's low 29 bits; from S on the result's limb k - S.
 template <int S, int k>
-__device__ __forceinline__ uint32_t end_col(uint64_t low, uint64_t high, uint32_t (&q)[S], const uint32_t (&n)[S],
-                                            uint32_t ninv, uint64_t &carry) {
+__device__ __forceinline__ uint32_t end_col(uint64_t low, uint32_t (&q)[S], const uint32_t (&n)[S], uint32_t ninv,
+                                            uint64_t &carry) {
   uint32_t r = 0;
   if constexpr (k < S) {
     q[k] = ((uint32_t)low * ninv) & kMask29;
@@ -74,8 +87,7 @@ __device__ __forceinline__ uint32_t end_col(uint64_t low, uint64_t high, uint32_
   } else {
     r = (uint32_t)low & kMask29;
   }
-  carry = (low >> he29::kBits) + high;
-  asm("" : "+v"(carry));
+  carry = low >> he29::kBits;
   return r;
 }
 
@@ -244,23 +256,24 @@ struct LanePair {
     static_for<0, 2 * S - 1>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
       using C = Col<S, k>;
-      uint64_t Q = ca, P = 0, Q2 = cb, P2 = 0, low, low2, high = 0, high2 = 0;
+      constexpr bool wide1 = 2 * C::cnt >= 64, wide2 = 3 * C::cnt >= 63;
+      uint64_t Q = ca, P = 0, Q2 = cb, P2 = 0;
       static_for<C::lo, C::hi + 1>([&](auto ic) {
         constexpr int i = decltype(ic)::value, j = k - i;
         if constexpr (i < j) P = mad(a[i], a[j], P);
-        if constexpr (i == j) Q = mad(a[i], a[i], Q);
         if constexpr (k >= S || i < k) Q = mad(q[i], n[j], Q);
+        if constexpr (i == j) Q = mad(a[i], a[i], Q);
       });
-      join<(2 * C::cnt >= 64)>(P, 1, Q, low, high);
-      const uint32_t ra = end_col<S, k>(low, high, q, n, ninv, ca);
+      const uint32_t ra = end_col<S, k>(join<wide1, 1>(P, Q), q, n, ninv, ca);
+      carry_wide<wide1, 1>(P, ca);
+      if constexpr (k >= 1 && k <= S) Q2 = add_mul<1>(q[k >= 1 && k <= S ? k - 1 : 0], Q2);
       static_for<C::lo, C::hi + 1>([&](auto ic) {
         constexpr int i = decltype(ic)::value, j = k - i;
         P2 = mad(a[i], b[j], P2);
         if constexpr (k >= S || i < k) Q2 = mad(p[i], n[j], Q2);
       });
-      if constexpr (k >= 1 && k <= S) Q2 += q[k >= 1 && k <= S ? k - 1 : 0];
-      join<(3 * C::cnt >= 63)>(P2, 1, Q2, low2, high2);
-      const uint32_t rb = end_col<S, k>(low2, high2, p, n, ninv, cb);
+      const uint32_t rb = end_col<S, k>(join<wide2, 1>(P2, Q2), p, n, ninv, cb);
+      carry_wide<wide2, 1>(P2, cb);
       if constexpr (k >= S) {
         a[k - S] = ra;
         b[k - S] = rb;
@@ -277,24 +290,25 @@ struct LanePair {
       constexpr int k = decltype(kc)::value;
       using C = Col<S, k>;
       constexpr bool wide = 3 * C::cnt >= 63;
-      uint64_t Q = ca, P = 0, Q2 = cb, P2 = 0, P3 = 0, low, low2, high = 0, high2 = 0;
+      constexpr bool wide1 = 2 * C::cnt >= 64;
+      uint64_t Q = ca, P = 0, Q2 = cb, P2 = 0, P3 = 0;
       static_for<C::lo, C::hi + 1>([&](auto ic) {
         constexpr int i = decltype(ic)::value, j = k - i;
         P = mad(a[i], c[j], P);
         if constexpr (k >= S || i < k) Q = mad(q[i], n[j], Q);
       });
-      join<(2 * C::cnt >= 64)>(P, 0, Q, low, high);
-      const uint32_t ra = end_col<S, k>(low, high, q, n, ninv, ca);
+      const uint32_t ra = end_col<S, k>(join<wide1, 0>(P, Q), q, n, ninv, ca);
+      carry_wide<wide1, 0>(P, ca);
+      if constexpr (k >= 1 && k <= S) Q2 = add_mul<1>(q[k >= 1 && k <= S ? k - 1 : 0], Q2);
       static_for<C::lo, C::hi + 1>([&](auto ic) {
         constexpr int i = decltype(ic)::value, j = k - i;
         P2 = mad(a[i], d[j], P2);
         P3 = mad(b[i], c[j], P3);
         if constexpr (k >= S || i < k) Q2 = mad(p[i], n[j], Q2);
       });
-      if constexpr (k >= 1 && k <= S) Q2 += q[k >= 1 && k <= S ? k - 1 : 0];
-      join<wide>(P2, 0, Q2, low2, high2);
-      join<wide>(P3, 0, low2, low2, high2);
-      const uint32_t rb = end_col<S, k>(low2, high2, p, n, ninv, cb);
+      const uint32_t rb = end_col<S, k>(join<wide, 0>(P3, join<wide, 0>(P2, Q2)), p, n, ninv, cb);
+      carry_wide<wide, 0>(P2, cb);
+      carry_wide<wide, 0>(P3, cb);
       if constexpr (k >= S) {
         a[k - S] = ra;
         b[k - S] = rb;
@@ -371,16 +385,18 @@ struct LaneMod {
     static_for<0, 2 * S - 1>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
       using C = Col<S, k>;
-      uint64_t Q = ca, P = 0, low, high = 0;
+      constexpr bool wide = 2 * C::cnt >= 64;
+      constexpr int sh = SQ ? 1 : 0;
+      uint64_t Q = ca, P = 0;
       static_for<C::lo, C::hi + 1>([&](auto ic) {
         constexpr int i = decltype(ic)::value, j = k - i;
         if constexpr (!SQ) P = mad(a[i], c[j], P);
         if constexpr (SQ && i < j) P = mad(a[i], a[j], P);
-        if constexpr (SQ && i == j) Q = mad(a[i], a[i], Q);
         if constexpr (k >= S || i < k) Q = mad(q[i], n[j], Q);
+        if constexpr (SQ && i == j) Q = mad(a[i], a[i], Q);
       });
-      join<(2 * C::cnt >= 64)>(P, SQ ? 1 : 0, Q, low, high);
-      const uint32_t r = end_col<S, k>(low, high, q, n, ninv, ca);
+      const uint32_t r = end_col<S, k>(join<wide, sh>(P, Q), q, n, ninv, ca);
+      carry_wide<wide, sh>(P, ca);
       if constexpr (k >= S) a[k - S] = r;
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -404,7 +420,7 @@ struct TwinPair {
   uint32_t n[S], ninv, x[S], r[S], y[S], z[S];  // y: own digit of the operand, z: its first digit
   const uint32_t *k;
   uint32_t *tab;
-  uint32_t odd, hand;  // 1 (resp. 2^29 - 1) in odd lanes
+  uint32_t odd, hand;  // 1 and 2^29 - 1 in odd lanes
 
   __device__ __forceinline__ TwinPair(const UnitArgs &u, uint32_t *, uint32_t *) : ninv(u.ninv), k(u.consts), tab(u.tab) {
 #pragma unroll
@@ -471,27 +487,26 @@ struct TwinPair {
     share();
   }
   // the even lane's quotient digit, in the odd lane (0 in the even one)
-  __device__ __forceinline__ uint64_t handed(uint32_t q) const {
-    uint32_t t;
-    asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 quad_perm:[0,0,2,2] row_mask:0xf bank_mask:0xf"
-        : "=v"(t) : "v"(q), "v"(hand));
-    return t;
-  }
+  __device__ __forceinline__ uint32_t handed(uint32_t q) const { return bcast_first<2>(q) & hand; }
   __device__ __forceinline__ void sq() {
     uint32_t q[S];
     uint64_t c = 0;
     static_for<0, 2 * S - 1>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
       using C = Col<S, k>;
-      uint64_t Q = c, P = 0, low, high = 0;
+      constexpr bool wide = 3 * C::cnt >= 63;
+      uint64_t Q = c, P = 0;
       if constexpr (k >= 1 && k <= S) Q += handed(q[k >= 1 && k <= S ? k - 1 : 0]);
       static_for<C::lo, C::hi + 1>([&](auto ic) {
         constexpr int i = decltype(ic)::value, j = k - i;
         P = mad(x[i], r[j], P);
         if constexpr (k >= S || i < k) Q = mad(q[i], n[j], Q);
       });
-      join<(3 * C::cnt >= 63)>(P, odd, Q, low, high);
-      const uint32_t t = end_col<S, k>(low, high, q, n, ninv, c);
+      const uint64_t low = shl_add(wide ? (uint64_t)((uint32_t)P & kMask29) : P, odd, Q);
+      const uint64_t high = wide ? shl_add(P >> he29::kBits, odd, 0) : 0;
+      const uint32_t t = end_col<S, k>(low, q, n, ninv, c);
+      if constexpr (wide) c += high;
+      asm("" : "+v"(c));  // the columns stay apart (one wave per SIMD: 3% over letting the compiler merge them)
       if constexpr (k >= S) r[k - S] = t;
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -507,7 +522,7 @@ struct TwinPair {
       constexpr int k = decltype(kc)::value;
       using C = Col<S, k>;
       constexpr bool wide = 3 * C::cnt >= 63;
-      uint64_t Q = c, P = 0, P2 = 0, low, high = 0;
+      uint64_t Q = c, P = 0, P2 = 0;
       if constexpr (k >= 1 && k <= S) Q += handed(q[k >= 1 && k <= S ? k - 1 : 0]);
       static_for<C::lo, C::hi + 1>([&](auto ic) {
         constexpr int i = decltype(ic)::value, j = k - i;
@@ -515,9 +530,16 @@ struct TwinPair {
         P2 = mad(r[i], z[j], P2);
         if constexpr (k >= S || i < k) Q = mad(q[i], n[j], Q);
       });
-      join<wide>(P, 0, Q, low, high);
-      join<wide>(P2, 0, low, low, high);
-      const uint32_t t = end_col<S, k>(low, high, q, n, ninv, c);
+      uint64_t low = Q, high = 0;
+      if constexpr (wide) {
+        low = shl_add<0>((uint32_t)P2 & kMask29, shl_add<0>((uint32_t)P & kMask29, Q));
+        high = shl_add<0>(P2 >> he29::kBits, P >> he29::kBits);
+      } else {
+        low = shl_add<0>(P2, shl_add<0>(P, Q));
+      }
+      const uint32_t t = end_col<S, k>(low, q, n, ninv, c);
+      if constexpr (wide) c += high;
+      asm("" : "+v"(c));  // the columns stay apart (one wave per SIMD: 3% over letting the compiler merge them)
       if constexpr (k >= S) r[k - S] = t;
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -564,7 +586,7 @@ struct GroupPair {
       : k(u.consts), lds(row), zeros(zero_row) {
     ld29<K, G>(M.n, k + 2 * he29::kPairN * S);
     M.ninv = u.ninv & kMask29;
-    M.mask = kMask29;
+    M.mask = mask_vgpr();
     tab = u.tab + (lane_id() / kLanes) * 2 * S;
     second_digit = lane_id() & (uint32_t)G;
     hand = (lane_id() & (uint32_t)(kLanes - 1)) == (uint32_t)G ? kMask29 : 0u;
@@ -641,9 +663,8 @@ struct GroupPair {
     top = rotate_next_m29<G>((uint32_t)C[0], M.mask);
     C[1] += C[0] >> he29::kBits;
     if constexpr (HAND) {
-      uint32_t h;  // the first digit's q, in the second digit's first lane
-      asm("s_nop 1\n\tv_and_b32_dpp %0, %1, %2 row_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-          : "=v"(h) : "v"(q), "v"(hand));
+      // the first digit's q, in the second digit's first lane
+      const uint32_t h = (uint32_t)__builtin_amdgcn_mov_dpp((int)q, 0x111, 0xF, 0xF, true) & hand;
       uint64_t kk;
       asm("v_mad_u64_u32 %0, %1, %2, 1, %0" : "+v"(C[1]), "=s"(kk) : "v"(h));
     }
