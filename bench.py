@@ -18,9 +18,8 @@ latency) and the CPU oracle baseline.
                     [--no-batched] [--no-served] [--no-tree] [--chunk C | --fixed-shapes]
 
 --chunk C fixes the histogram's items (16 lanes, at most C samples per item);
---fixed-shapes skips both autotuners (the library's default histogram shape,
-pinned exponentiation shapes) so that separate profiler passes run the same
-kernels.
+--fixed-shapes skips both autotuners (the library's default histogram shape
+and launch plans) so that separate profiler passes run the same kernels.
 
 Other workloads (each prints its own JSON line; not the default):
     --workload tree      2048-bit, 1,000,000 samples, 64 x 256 Zipf bins, depth-6
@@ -52,16 +51,16 @@ KEY_SEED, R_SEED, DATA_SEED = 2, 2024, 1
 # (v_mad_u64_u32) per lane per clock.
 PEAK_MUL32_PER_S = 256 * 64 * 2.4e9
 MI355X_HBM_BPS = 8.0e12
-# HBM-side bytes of one encryption launch (k_enc_r + k_pow mod p + k_pow lift
-# + k_enc_crt_b over 200,000 ciphertexts), from rocprofv3 FETCH_SIZE and WRITE_SIZE passes
+# HBM-side bytes of one encryption launch (k_enc_r + k_pow_joint + k_enc_crt_b
+# over 200,000 ciphertexts), from rocprofv3 FETCH_SIZE and WRITE_SIZE passes
 # scaled by a 256 MiB copy (profiles/enc_crt_2048_100k_counters.md), and the
 # digest of the kernel sources those passes ran on (kernel_sources_digest()).
 # The figure is reported only while the sources still have that digest.
 ENC_LAUNCH_TRAFFIC = {"bytes": 4.0915e10, "sources_sha256_16": "0c8bbee5b0c6da4e"}
 # the kernels and the host code that picks their launches and exponent schedules
 KERNEL_SOURCES = ("he_kernels.hip", "he_internal.hpp", "hist_bucket.hpp", "mont.hpp", "mont29.hpp",
-                  "radix29.hpp", "pair29.hpp", "hist_pair.hpp", "pow_pair.hpp", "pow_lane16.hip", "pow_lane32.hip", "pow_twin32.hip",
-                  "pow_group.hip", "he_api.cpp", "keysetup.hpp")
+                  "radix29.hpp", "pair29.hpp", "hist_pair.hpp", "pow_pair.hpp", "pow_lane16.hip",
+                  "pow_lane32.hip", "pow_twin32.hip", "pow_group.hip", "he_api.cpp", "keysetup.hpp")
 
 
 def _code_only(text: str) -> str:
@@ -109,12 +108,6 @@ def mm_products(s: int) -> int:
     return 2 * s * s + s
 
 
-def sq_products(s: int) -> int:
-    """32x32->64 products of one s-limb Montgomery squaring: the s (s + 1) / 2
-    distinct products a_i a_j of the square plus the s^2 + s of the reduction."""
-    return s * (s + 1) // 2 + s * s + s
-
-
 def nwin(e: int) -> int:
     return max(1, -(-e.bit_length() // 5))
 
@@ -142,43 +135,80 @@ def sliding_ops(e: int, width: int = 6):
     return mults, sqs
 
 
-def modexp_products(e: int, s: int) -> int:
-    """Products of one exponentiation mod an s-limb modulus as the kernels
-    run it without constant-time table reads (sliding windows of up to 6
-    bits): general products at 2s^2 + s, squarings at s(s+1)/2 + s^2 + s."""
+def mm2_products(s: int) -> int:
+    """32x32->64 products of one Montgomery product mod N^2 in two digits base
+    an s-limb N: three digit products and two reductions."""
+    return 3 * s * s + 2 * (s * s + s)
+
+
+def sq2_products(s: int) -> int:
+    """As mm2_products for a square: the distinct products of the first digit's
+    square, one digit product (doubled) and two reductions."""
+    return s * (s + 1) // 2 + s * s + 2 * (s * s + s)
+
+
+def modexp2_products(e: int, s: int) -> int:
+    """Products of one exponentiation mod N^2 in two digits base an s-limb N
+    without constant-time table reads (sliding windows of up to 6 bits)."""
     mults, sqs = sliding_ops(e)
-    return mults * mm_products(s) + sqs * sq_products(s)
+    return mults * mm2_products(s) + sqs * sq2_products(s)
+
+
+def joint_ops(f: int, e: int, width: int = 5):
+    """(general products, squarings) of x^f and x^e sharing their squarings,
+    right to left: windows of `width` bits whose lowest bit is 1 multiply x^(2^i)
+    into one of 2^(width-1) buckets of their exponent (the first into a bucket
+    is a copy), then per exponent the buckets are joined."""
+    mults, last = 0, 0
+    for x in (f, e):
+        used, i = set(), 0
+        while i < x.bit_length():
+            if not (x >> i) & 1:
+                i += 1
+                continue
+            k = ((x >> i) & (2 ** width - 1)) >> 1
+            mults += k in used
+            used.add(k)
+            last = max(last, i)
+            i += width
+        top = max(used)
+        if top:
+            # suffix products of the buckets below the top, the product of those
+            # down to bucket 1, its square times the product of all
+            mults += len(used - {top}) + top - 1 + 1
+            last += 1  # that square
+    return mults, last
 
 
 def crt_encrypt_products(p: int, q: int, L: int) -> int:
-    """Products of the CRT encryption kernel (phase A) for one ciphertext."""
+    """Products of the CRT encryption for one ciphertext."""
     sp = L // 2
     tot = 0
     for P, Q in ((p, q), (q, p)):
-        # mod P: r reduction (3), exponentiation, from_mont, m Q (2)
-        tot += (3 + 2) * mm_products(sp) + modexp_products(Q % (P - 1), sp)
-        # mod P^2: to_mont, lift, (1 + m n), product
-        tot += (1 + 2) * mm_products(2 * sp) + modexp_products(P, 2 * sp)
+        # mod P: r reduction (3), m Q (2)
+        tot += (3 + 2) * mm_products(sp)
+        # mod P^2: in, the powers P - 1 and Q mod (P - 1), their joining (2), out (2)
+        mults, sqs = joint_ops(P - 1, Q % (P - 1))
+        tot += (mults + 5) * mm2_products(sp) + sqs * sq2_products(sp)
     return tot
 
 
 def crt_decrypt_products(p: int, q: int, L: int) -> int:
-    """Products of CRT decryption (both phases) for one ciphertext."""
+    """Products of CRT decryption for one ciphertext."""
     sp = L // 2
     tot = 0
     for P in (p, q):
-        # c mod P^2 (2 MM + add), exponentiation, from_mont, exact division
-        # (low-half product), m_P = k h_P
-        tot += (2 + 1) * mm_products(2 * sp) + modexp_products(P - 1, 2 * sp) + sp * sp + mm_products(sp)
-    return tot + 4 * mm_products(sp) + mm_products(L)
+        # c mod P^2 (4 pieces), exponentiation, out (2), m_P = k h_P
+        tot += (4 + 2) * mm2_products(sp) + modexp2_products(P - 1, sp) + mm_products(sp)
+    return tot + mm_products(sp)
 
 
 def hist_products(n_contrib: int, n_slots: int, rows: int, L: int) -> int:
-    """Products of one canonical-input histogram call: conversion of every
-    row, one product per contribution beyond the first of each slot, the
-    combines, and the conversion out of Montgomery form (bounded above by
-    one product per contribution plus two per slot)."""
-    return (2 * rows + n_contrib + 2 * n_slots) * mm_products(2 * L)
+    """Products of one canonical-input histogram call in two digits base n:
+    conversion of every row, one product per contribution beyond the first of
+    each slot, and the conversion out (bounded above by one product per
+    contribution plus two per slot)."""
+    return (2 * rows + n_contrib + 2 * n_slots) * mm2_products(L)
 
 
 def percentile(xs, q):
@@ -264,7 +294,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=1)
     ap.add_argument("--chunk", type=int, default=0)
     ap.add_argument("--fixed-shapes", action="store_true",
-                    help="no autotuners: default histogram shape, pinned exponentiation shapes (profiler passes)")
+                    help="no autotuners: default histogram shape and launch plans (profiler passes)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-batched", action="store_true", help="leave the 64-job batched comparison out of the line")
     ap.add_argument("--no-served", action="store_true", help="leave the served request loop out of the line")
@@ -338,15 +368,10 @@ def main():
     # histogram work shape for this shape class (used by every step below).
     he.encrypt(key, he.encode(grads), seed=R_SEED, out=ct.view(-1, 2 * L))
     if args.fixed_shapes:
-        # no autotuner: the library's default histogram shape at this size
-        # (8 lanes per ciphertext, items of up to 128 samples, two groups per
-        # item) and pinned exponentiation shapes, so that every profiler pass
-        # runs the same kernels
-        hist_tune = he.HistTune(128, 2, 8, 0, None)
+        # no autotuner: the library's default histogram shape and launch plans,
+        # so that every profiler pass runs the same kernels
+        hist_tune = he.HistTune(0, 2, 8, 0, None)
         exp_shapes = {}
-        for kind, count, lanes, tail in (("mod_p", 2 * M, 2, 0), ("lift", 2 * M, 4, 0), ("decrypt", J * K * 2, 4, 0)):
-            he.crt_set_shape(key, kind, count, lanes, 0, tail)
-            exp_shapes[kind] = he.PowTune(lanes, 0, tail, 0.0)
     else:
         hist_tune = (he.hist_autotune(key, ct, [he.Job(idx, bins, K)]) if args.chunk == 0
                      else he.HistTune(args.chunk, 2, 16, 0, None))
@@ -413,9 +438,8 @@ def main():
     torch.cuda.synchronize()
     pub_same = bool(torch.equal(ct_pub, ct.view(-1, 2 * L)[:n_pub]))
     t_pub = pub_marks[0].elapsed_time(pub_marks[1])
-    # x mod n^2 (2 products), into and out of the exponentiation's form (2),
-    # the exponentiation by n, f = 1 + m n and the product with it (3)
-    pub_products = modexp_products(n, 2 * L) + 7 * mm_products(2 * L)
+    # in, the exponentiation by n mod n^2 in two digits base n, out (2)
+    pub_products = modexp2_products(n, L) + 3 * mm2_products(L)
     del ct_pub, pub
     # Beside the step: packed decryption of the same 16,384 histogram
     # ciphertexts (the passive party folds 4 per ciphertext).
@@ -481,7 +505,7 @@ def main():
             "key_bits": KEY_BITS, "samples": M, "features": J, "bins": K, "r": "seeded",
             "encrypt_path": "crt", "hist_chunk": tuned_chunk, "hist_split": tuned_split,
             "hist_lanes": hist_tune.lanes, "hist_waves_per_simd": hist_tune.waves or "own occupancy",
-            "hist_shape": ("library default, exponentiation shapes pinned" if args.fixed_shapes else
+            "hist_shape": ("library defaults" if args.fixed_shapes else
                            "autotuned before timing" if args.chunk == 0 else "given"),
             "exponentiation_shapes": {k: {"lanes": v.lanes, "waves_per_simd": v.waves or "own occupancy",
                                           "last_round_lanes": v.tail_lanes or "same launch",
@@ -506,7 +530,7 @@ def main():
         "step_latency_ms": {"p50": round(percentile(stage_ms["step"], 0.5), 3),
                             "p99": round(percentile(stage_ms["step"], 0.99), 3)},
         "roofline": {
-            "kernel": "k_enc_r + k_pow (mod p) + k_pow (lift mod p^2) + k_enc_crt_b (CRT encryption)",
+            "kernel": "k_enc_r + k_pow_joint (r^n mod p^2) + k_enc_crt_b (CRT encryption)",
             "bound": "alu",
             "achieved": round(achieved / 1e12, 3),
             "peak": round(PEAK_MUL32_PER_S / 1e12, 3),

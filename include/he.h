@@ -231,9 +231,12 @@ int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t rows, int c
                      const he_hist_job *jobs, uint32_t n_jobs, uint32_t *chunk, uint32_t *split,
                      uint32_t *lanes, uint32_t *waves, float *ms, hipStream_t stream);
 
-/* Autotuner for the private-key exponentiations: the CRT encryption's
- * exponentiation mod p and p-th-power lift mod p^2 (Sec. III-C: 2M
- * encryptions for M samples) and decryption's exponentiation mod p^2.  Times
+/* Autotuner for the private-key exponentiations: the CRT encryption's r^n mod
+ * p^2 (Sec. III-C: 2M encryptions for M samples; the "lift", one launch for
+ * both of its exponents -- for a constant-time key the power r^q mod p, "mod
+ * p", and then the p-th power mod p^2; a key without that option is timed on
+ * mod p all the same, for the constant-time keys of its size) and decryption's
+ * exponentiation mod p^2.  Times
  * every built launch shape of each -- lanes per integer (2, 4, 8 or 16) and
  * waves per SIMD (the kernel's own occupancy, or 3 or 2 by reserving LDS) --
  * and then, at the best of those, the same work in two launches: the
@@ -260,7 +263,8 @@ int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t dec_count, u
 
 /* Sets the launch shape he_crt_autotune would remember, without timing (a
  * shape measured once, pinned in a deployment): for kind 0 (the mod-p
- * exponentiation of encryption), 1 (the lift), 2 (decryption) or 3 (the
+ * exponentiation of a constant-time key's encryption), 1 (the lift, of other
+ * keys the whole of r^n mod p^2), 2 (decryption) or 3 (the
  * exponentiation by n mod n^2 of public-key encryption, also the path of a
  * key holding n only) at this key's size, on the current device, for counts
  * of count's size class (bit length; for kind 3 of (count + 1) / 2): lanes

@@ -96,6 +96,7 @@ int build_key(he_key *k) {
       P.e_enc = mk_exp(base, po[w]->e_enc);
       P.e_lift = mk_exp(base, po[w]->e_lift);
       P.e_dec = mk_exp(base, po[w]->e_dec);
+      P.joint = mk_exp(base, po[w]->joint);
       P.QR2_P = base + po[w]->QR2_P;
       P.PR_P2 = base + po[w]->PR_P2;
       P.Pinv = base + po[w]->Pinv;
@@ -258,9 +259,9 @@ uint64_t plan_table_bytes(int KP, int kind, const he::PowPlan &p) {
 // with the rest in a second launch at a wider one.
 // The constants are milliseconds measured at one and at several waves per
 // SIMD (MI355X, about 2.15 GHz under this load); only their ratios matter.
-// E.g. 200,000 lifts at 2048 bits: 81.3 ms for 196,608 at one lane and 2.9 ms
-// for the rest at 8 lanes; in one launch 83.7-95 ms at one lane (an uneven last
-// wave), 93 ms at 2 and 104 ms at 8.
+// E.g. 200,000 encryptions' powers at 2048 bits: 196,608 at one lane and the rest
+// at 8 take 98 ms; in one launch 109 ms at one lane (an uneven last wave), 119
+// at 2 and 132 at 8.
 struct PowCost {
   int G;
   double first, more;
@@ -270,9 +271,12 @@ const std::vector<PowCost> &pow_costs(int KP, int kind) {
   static const std::vector<PowCost> mod32 = {{1, 5.8, 5.3}, {2, 3.75, 2.85}, {4, 2.37, 1.65}, {8, 2.26, 1.22}, {16, 2.4, 1.12}};
   static const std::vector<PowCost> pair16 = {{1, 1.93, 1.72}, {2, 1.2, .98}, {4, .88, .55}, {8, .72, .41}, {16, .78, .38}};
   static const std::vector<PowCost> pair32 = {{1, 13.1, 12.1}, {2, 7.95, 7.1}, {4, 4.7, 3.6}, {8, 2.9, 2.1}, {16, 2.58, 1.53}};
+  static const std::vector<PowCost> joint16 = {{1, 2.5, 2.2}, {2, 1.65, 1.35}, {4, 1.12, .74}, {8, .93, .54}, {16, .98, .46}};
+  static const std::vector<PowCost> joint32 = {{1, 17.0, 15.4}, {2, 10.2, 9.2}, {4, 6.0, 4.75}, {8, 3.65, 2.75}, {16, 3.2, 1.95}};
   static const std::vector<PowCost> pair64 = {{8, 17.1, 13.7}, {16, 11.1, 8.0}};
   if (kind == 4) return KP == 1 ? mod16 : mod32;
   if (kind == 1) return KP == 1 ? pair32 : pair64;
+  if (kind == 3) return KP == 1 ? joint16 : joint32;
   return KP == 1 ? pair16 : pair32;
 }
 
@@ -316,7 +320,7 @@ he::PowPlan pow_plan(int KP, int kind, uint64_t count) {
   (void)hipGetDevice(&dev);
   {
     std::lock_guard<std::mutex> lk(g_pow_mu);
-    auto it = g_pow_tuned.find({dev, KP, kind, count_class(count)});
+    auto it = g_pow_tuned.find({dev, KP, kind == 3 ? 0 : kind, count_class(count)});
     if (it != g_pow_tuned.end()) sh = it->second;
   }
   return sh.G ? pow_plan_at(KP, kind, count, sh) : default_pow_plan(KP, kind, count);
@@ -332,8 +336,16 @@ int encrypt_impl(const he_key *key, const int64_t *m, uint64_t count, const uint
   const int KP = kp_of(key);
   const size_t L = key->n_bits / 32;
   if (key->priv && !force_pub) {
-    he::PowPlan p1 = pow_plan(KP, 4, count), p2 = pow_plan(KP, 0, count);
-    int rc = ensure(w->tab, std::max(plan_table_bytes(KP, 4, p1), plan_table_bytes(KP, 0, p2)), stream);
+    // secret digits: r^(Q mod (P-1)) mod P, then its power P; else both at once
+    const he::DKey dk = key->dk;
+    const int kind = dk.ct ? 0 : 3;
+    he::PowPlan p1{}, p2 = pow_plan(KP, kind, count);
+    uint64_t tab_bytes = plan_table_bytes(KP, kind, p2);
+    if (dk.ct) {
+      p1 = pow_plan(KP, 4, count);
+      tab_bytes = std::max(tab_bytes, plan_table_bytes(KP, 4, p1));
+    }
+    int rc = ensure(w->tab, tab_bytes, stream);
     if (rc) return rc;
     rc = ensure(w->ctr, 256, stream);
     if (rc) return rc;
@@ -344,7 +356,7 @@ int encrypt_impl(const he_key *key, const int64_t *m, uint64_t count, const uint
     rc = ensure(w->tmp, count * 3 * L * sizeof(uint32_t), stream);
     if (rc) return rc;
     uint32_t *cpq = (uint32_t *)w->tmp.p, *tq = cpq + count * 2 * L;
-    HE_TRY_HIP(he::launch_enc_crt(KP, key->dk, m, count, r, r_seed, r_offset, tq, cpq, ct, (uint32_t *)w->tab.p,
+    HE_TRY_HIP(he::launch_enc_crt(KP, dk, m, count, r, r_seed, r_offset, tq, cpq, ct, (uint32_t *)w->tab.p,
                                   p1, p2, stream));
   } else {
     // the exponentiation's units pair consecutive ciphertexts (both "primes"
@@ -1026,7 +1038,9 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   // tables, work counters
   DevBuf tq, cpq, ct, xpq, tab, ctr;
   size_t tab_bytes = 0;
-  for (int kind : {4, 0, 2})
+  // mod P, the lift (with public digits: both powers at once), decryption
+  const int kinds[3] = {4, key->dk.ct ? 0 : 3, 2};
+  for (int kind : kinds)
     for (int G : {1, 2, 4, 8, 16})
       if (he::pow_shape_valid(KP, kind, G))
         tab_bytes = std::max<size_t>(tab_bytes, (size_t)he::pow_resident_blocks(KP, kind, G, 0) *
@@ -1049,14 +1063,13 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   HE_TRY_HIP(hipEventCreate(&e1));
   PowShape best[3];
   float best_ms[3] = {1e30f, 1e30f, 1e30f};
-  const int kinds[3] = {4, 0, 2};
   for (int t = 0; t < 3 && !rc; ++t) {
     const int kind = kinds[t];
     const uint64_t count = kind == 2 ? dec_count : enc_count;
     auto trial = [&](const PowShape &sh, he::PowPlan p) -> int {
       p.ctr = (uint32_t *)ctr.p;
       auto run = [&]() -> hipError_t {
-        return he::launch_pow_kind(KP, key->dk, kind, kind == 2 ? ct_p : tq_p, kind == 4 ? tq_p : (kind == 0 ? cpq_p : xpq_p),
+        return he::launch_pow_kind(KP, key->dk, kind, kind == 2 ? ct_p : tq_p, kind == 4 ? tq_p : (kind == 2 ? xpq_p : cpq_p),
                                    count, tab_p, p, stream);
       };
       float ms = 0;
@@ -1100,7 +1113,7 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   {
     std::lock_guard<std::mutex> lk(g_pow_mu);
     for (int t = 0; t < 3; ++t)
-      g_pow_tuned[{dev, KP, kinds[t], count_class(kinds[t] == 2 ? dec_count : enc_count)}] = best[t];
+      g_pow_tuned[{dev, KP, kinds[t] == 3 ? 0 : kinds[t], count_class(kinds[t] == 2 ? dec_count : enc_count)}] = best[t];
   }
   for (int t = 0; t < 3; ++t) {
     if (choice) {

@@ -50,9 +50,12 @@ struct PairPowArgs {
   uint32_t *tabs;
   uint32_t *next;
 };
+// Exponentiation schedules: sliding windows, fixed windows with masked table
+// reads (secret digits), or two exponents that share their squarings.
+enum class PairPow { kSliding, kMasked, kJoint };
 // The kernel for a base of SN 32-bit limbs at L lanes per integer (0: one
-// residue mod N per lane), null if not built.
-const void *pow_pair_kernel(int SN, int L, bool ct);
+// residue mod N per lane, masked only), null if not built.
+const void *pow_pair_kernel(int SN, int L, PairPow which);
 
 // Per-prime constants for the CRT paths; P is this prime, Q the other one.
 // S_P = L/2 limbs for P, S_P2 = L limbs for P^2 (L = limbs of n).
@@ -62,6 +65,7 @@ struct DPrime {
   DExp e_enc;        // Q mod (P - 1): r^Q mod P = r^(Q mod (P-1)) mod P
   DExp e_lift;       // P: x -> x^P mod P^2 depends only on x mod P
   DExp e_dec;        // P - 1: decryption exponent
+  DExp joint;        // schedule of the powers P - 1 and e_enc mod P^2 of one base (ops only)
   const uint32_t *QR2_P;  // Q R^2 mod P        (S_P limbs)
   const uint32_t *PR_P2;  // P R' mod P^2       (S_P2 limbs)
   const uint32_t *Pinv;   // P^-1 mod 2^(32 S_P)

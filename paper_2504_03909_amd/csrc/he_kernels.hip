@@ -129,7 +129,7 @@ struct PowArgs {
   uint32_t *next;
 };
 
-template <int S32, int G, bool CT>
+template <int S32, int G>
 __global__ __launch_bounds__(kBlockThreads, 3) void k_pow(PowArgs a) {
   constexpr int K32 = S32 / G, NG = 64 / G, GB = kBlockThreads / G;
   constexpr int S29 = he29::limbs_for_group(S32, G), ROW = 2 * S29 > S32 ? 2 * S29 : S32;
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kBlockThreads, 3) void k_pow(PowArgs a) {
     const uint64_t u = i * 2 + which;
     uint32_t x[K32];
     ld_part<K32, G>(x, a.in + u * a.in_stride, (int)a.in_limbs);
-    pow29<K32, G>(x, a.exp[which], tab, a.mod[which], lds, zeros, CT);
+    pow29<K32, G>(x, a.exp[which], tab, a.mod[which], lds, zeros);
     if (valid) st<K32, G>(a.out + u * a.out_stride, x);
   }
 }
@@ -159,10 +159,10 @@ __global__ __launch_bounds__(kBlockThreads, 3) void k_pow(PowArgs a) {
 // For each (ciphertext i, prime P):
 //   c_P = (1 + m n) r^n mod P^2,  r^n mod P^2 = (r^(Q mod (P-1)) mod P)^P mod P^2
 // (x -> x^P mod P^2 depends only on x mod P), and 1 + m n = 1 + P (m Q mod P)
-// mod P^2.  k_enc_r reduces r mod P, k_pow computes t = r^(Q mod (P-1)) mod P
-// (mod-P arithmetic, 2-lane groups for large counts) and then omega = t^P mod
-// P^2 as two digits base P, and k_enc_crt_b forms c_P = omega (1 + P (m Q mod
-// P)) and combines c_p, c_q by the CRT.
+// mod P^2.  k_enc_r reduces r mod P, k_pow_joint computes omega = r^n mod P^2
+// as two digits base P (with secret digits, in two steps: k_pow t = r^(Q mod
+// (P-1)) mod P, k_pow_pair t^P), and k_enc_crt_b forms c_P = omega (1 + P (m Q
+// mod P)) and combines c_p, c_q by the CRT.
 
 // r mod P for each (ciphertext i, prime P) into tq[2 i + P] (S_P limbs): r's
 // S_P-limb words w_k (two for an explicit r, three for the seeded one), each
@@ -1245,37 +1245,41 @@ hipError_t launch_encode(const double *x, uint64_t count, uint32_t frac_bits, in
   return hipGetLastError();
 }
 
-const void *pow_lane16(int SN, int L, bool ct);
-const void *pow_lane32(int SN, int L, bool ct);
-const void *pow_twin32(int SN, int L, bool ct);
-const void *pow_group(int SN, int L, bool ct);
-const void *pow_pair_kernel(int SN, int L, bool ct) {
+const void *pow_lane16(int SN, int L, PairPow which);
+const void *pow_lane32(int SN, int L, PairPow which);
+const void *pow_twin32(int SN, int L, PairPow which);
+const void *pow_group(int SN, int L, PairPow which);
+const void *pow_pair_kernel(int SN, int L, PairPow which) {
   for (auto f : {pow_lane16, pow_lane32, pow_twin32, pow_group})
-    if (const void *k = f(SN, L, ct)) return k;
+    if (const void *k = f(SN, L, which)) return k;
   return nullptr;
 }
 
-// Base limbs of an exponentiation of `kind`: p, q (kinds 4, 0, 2) or n (1).
+// Base limbs of an exponentiation of `kind`: n (1) or p, q.
 static int pow_base(int KP, int kind) { return kind == 1 ? 32 * KP : 16 * KP; }
 
 // The exponentiation kernel of `kind` at G lanes per integer, null if not
-// built.  Mod P: k_pow from 2 lanes on, one residue per lane below.  The
-// public exponent n is never secret.
+// built.  Mod P (4) and the lift (0), the two steps of an encryption whose
+// digits are secret, read their tables masked; an encryption that need not hide
+// them takes kind 3; decryption (2) comes both ways; the public exponent n
+// is never secret.  Mod P: k_pow from 2 lanes on, one residue per lane below.
 template <int S32>
-static const void *pow_mod_kernel(int G, bool ct) {
+static const void *pow_mod_kernel(int G) {
   switch (G) {
-    case 2: return ct ? (const void *)k_pow<S32, 2, true> : (const void *)k_pow<S32, 2, false>;
-    case 4: return ct ? (const void *)k_pow<S32, 4, true> : (const void *)k_pow<S32, 4, false>;
-    case 8: return ct ? (const void *)k_pow<S32, 8, true> : (const void *)k_pow<S32, 8, false>;
-    case 16: return ct ? (const void *)k_pow<S32, 16, true> : (const void *)k_pow<S32, 16, false>;
+    case 2: return (const void *)k_pow<S32, 2>;
+    case 4: return (const void *)k_pow<S32, 4>;
+    case 8: return (const void *)k_pow<S32, 8>;
+    case 16: return (const void *)k_pow<S32, 16>;
     default: return nullptr;
   }
 }
 static const void *pow_kernel(int KP, int kind, int G, bool ct) {
   const int SN = pow_base(KP, kind);
-  if (kind != 4) return pow_pair_kernel(SN, G, ct && kind != 1);
-  if (G == 1) return pow_pair_kernel(SN, 0, ct);
-  return KP == 1 ? pow_mod_kernel<16>(G, ct) : pow_mod_kernel<32>(G, ct);
+  if (kind == 3) return pow_pair_kernel(SN, G, PairPow::kJoint);
+  if (kind == 1 || (kind == 2 && !ct)) return pow_pair_kernel(SN, G, PairPow::kSliding);
+  if (kind != 4) return pow_pair_kernel(SN, G, PairPow::kMasked);
+  if (G == 1) return pow_pair_kernel(SN, 0, PairPow::kMasked);
+  return KP == 1 ? pow_mod_kernel<16>(G) : pow_mod_kernel<32>(G);
 }
 bool pow_shape_valid(int KP, int kind, int G) { return pow_kernel(KP, kind, G, false) != nullptr; }
 
@@ -1306,7 +1310,13 @@ static hipError_t launch_pow(int KP, const DKey &k, int kind, const uint32_t *in
     const DPair &pc = kind == 1 ? k.pair_n : k.pr[w].pair;
     a.consts[w] = pc.c[v];
     a.ninv[w] = pc.ninv;
-    a.exp[w] = kind == 1 ? k.e_n : (kind == 4 ? k.pr[w].e_enc : (kind == 0 ? k.pr[w].e_lift : k.pr[w].e_dec));
+    switch (kind) {
+      case 0: a.exp[w] = k.pr[w].e_lift; break;
+      case 1: a.exp[w] = k.e_n; break;
+      case 2: a.exp[w] = k.pr[w].e_dec; break;
+      case 3: a.exp[w] = k.pr[w].joint; break;
+      default: a.exp[w] = k.pr[w].e_enc;
+    }
   }
   a.pieces = kind == 2 ? 4 : 1;
   a.in_w = kind == 2 ? 0 : SN;
@@ -1324,8 +1334,8 @@ static hipError_t launch_pow(int KP, const DKey &k, int kind, const uint32_t *in
 
 // The plan's launches over `count` unit pairs: the first main_count at
 // p.main, the rest at p.tail, each with its work counter in p.ctr when given
-// (cleared here, in stream order).  Kind 4 works on tq in place, 0 reads tq, 2
-// the ciphertexts, 1 the rows of r mod n; the last three write two digits.
+// (cleared here, in stream order).  Kind 4 works on tq in place, 0 and 3 read tq,
+// 2 the ciphertexts, 1 the rows of r mod n; all but 4 write two digits.
 hipError_t launch_pow_kind(int KP, const DKey &k, int kind, const uint32_t *in, uint32_t *out, uint64_t count,
                            uint32_t *tab, const PowPlan &p, hipStream_t s) {
   if (!count) return hipSuccess;
@@ -1360,9 +1370,9 @@ static hipError_t enc_crt(const DKey &k, const int64_t *m, uint64_t count, const
                           const PowPlan &p1, const PowPlan &p2, hipStream_t s) {
   hipLaunchKernelGGL(k_enc_r<KP>, dim3(blocks_for(2 * count, 16)), dim3(kBlockThreads), 0, s, k, count, r, seed,
                      roff, tq);
-  hipError_t e = launch_pow_kind(KP, k, 4, tq, tq, count, tab, p1, s);
+  hipError_t e = k.ct ? launch_pow_kind(KP, k, 4, tq, tq, count, tab, p1, s) : hipSuccess;
   if (e != hipSuccess) return e;
-  e = launch_pow_kind(KP, k, 0, tq, cpq, count, tab, p2, s);
+  e = launch_pow_kind(KP, k, k.ct ? 0 : 3, tq, cpq, count, tab, p2, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_enc_crt_b<KP>, dim3(blocks_for(count, 16)), dim3(kBlockThreads), 0, s, k, m,
                      (const uint32_t *)cpq, count, ct);

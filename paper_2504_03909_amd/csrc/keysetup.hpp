@@ -92,10 +92,57 @@ inline std::vector<uint32_t> sliding_schedule(const Limbs &e) {
   if (pend) ops.push_back((pend << 8) | kSlideNoMul);
   return ops;
 }
+
+// Two powers x^f and x^e of one base, f, e >= 1, sharing the squarings (Yao
+// 1976, right to left): x runs through x^(2^i); where a window of he29::kJointBits
+// bits with lowest bit 1 and value 2 k + 1 starts at bit i of an exponent, x^(2^i)
+// is multiplied into that exponent's bucket k, and at the end an exponent's
+// power is prod_k B_k^(2 k + 1) = (prod_k B_k^k)^2 prod_k B_k, the inner product
+// by suffix products.  f's buckets are slots 0..15, e's 16..31.  An op is its
+// slot (bits 0..7), what to do with it (bits 8..9) and the squarings of the
+// state before (bits 10..31).  At the end slot 0 holds x^f, the state x^e.
+inline std::vector<uint32_t> joint_schedule(const Limbs &f, const Limbs &e) {
+  std::vector<uint32_t> ops;
+  auto op = [&](size_t nsq, he29::JointOp what, uint32_t slot) { ops.push_back((uint32_t)(nsq << 10) | (what << 8) | slot); };
+  bool used[2 * he29::kJointBuckets] = {};
+  size_t next[2] = {0, 0}, at = 0;  // bit of the next window, bit the state is at
+  const Limbs *x[2] = {&f, &e};
+  const size_t bits = std::max(hebn::bit_length(f), hebn::bit_length(e));
+  for (size_t i = 0; i < bits; ++i)
+    for (uint32_t w = 0; w < 2; ++w) {
+      if (i < next[w] || !hebn::bit(*x[w], i)) continue;
+      uint32_t val = 0;
+      for (int b = he29::kJointBits - 1; b >= 0; --b) val = (val << 1) | (uint32_t)hebn::bit(*x[w], i + (size_t)b);
+      const uint32_t slot = w * he29::kJointBuckets + (val >> 1);
+      op(i - at, used[slot] ? he29::kJointAcc : he29::kJointPut, slot);
+      used[slot] = true;
+      at = i;
+      next[w] = i + he29::kJointBits;
+    }
+  for (uint32_t w = 0; w < 2; ++w) {
+    const uint32_t base = w * he29::kJointBuckets;
+    uint32_t top = he29::kJointBuckets - 1;
+    while (top > 0 && !used[base + top]) --top;
+    op(0, he29::kJointLoad, base + top);
+    if (top > 0) {
+      // the state: prod of the buckets from j up; slot top: the product of those
+      for (uint32_t j = top - 1; j >= 1; --j) {
+        if (used[base + j]) op(0, he29::kJointTake, base + j);
+        op(0, he29::kJointAcc, base + top);
+      }
+      if (used[base]) op(0, he29::kJointTake, base);
+      op(0, he29::kJointPut, base);
+      op(0, he29::kJointLoad, base + top);
+      op(1, he29::kJointTake, base);
+    }
+    if (w == 0) op(0, he29::kJointPut, 0);
+  }
+  return ops;
+}
 struct PrimeOff {
   ModOff P, P2;
   PairOff pair;
-  ExpOff e_enc, e_lift, e_dec;
+  ExpOff e_enc, e_lift, e_dec, joint;
   size_t QR_P, QR2_P, PR_P2, Pinv, hR_P;
 };
 struct KeyConsts {
@@ -135,7 +182,8 @@ inline ModOff put_mod(Blob &b, const Limbs &N, size_t S) {
 // The two-digit constants of N (S 32-bit limbs), see radix29.hpp.  X mod N^2
 // is the pair (c, d 2^29 mod N) with X = c - d N.  Piece h of an input
 // sum_h x_h 2^(32 S h) enters by the product with 2^(32 S h) R^2 mod N^2.
-inline PairOff put_pair(Blob &b, const Limbs &N, size_t S) {
+// e: see kPairE.
+inline PairOff put_pair(Blob &b, const Limbs &N, size_t S, const Limbs &e) {
   PairOff o;
   o.ninv = hebn::neg_inv32(N[0]);
   const Limbs N2 = hebn::mul(N, N), shift = hebn::mod(pow2(he29::kBits), N);
@@ -161,6 +209,9 @@ inline PairOff put_pair(Blob &b, const Limbs &N, size_t S) {
     put(hebn::from_u64(1));
     put(hebn::mod(pow2(he29::kBits * (S29 - 1)), N));
     put(R);
+    const Limbs eR = hebn::mulmod(hebn::mod(e, N2), R, N2);
+    put(eR);
+    put(hebn::mod(hebn::sub(hebn::add(R, N2), eR), N2));
     b.put29(N, S29);
   }
   return o;
@@ -179,6 +230,16 @@ inline ExpOff put_exp(Blob &b, const Limbs &e, size_t limbs) {
   return x;
 }
 
+inline ExpOff put_joint(Blob &b, const Limbs &f, const Limbs &e) {
+  ExpOff x{};
+  const std::vector<uint32_t> ops = joint_schedule(f, e);
+  x.nops = (int)ops.size();
+  x.ops = b.words.size();
+  b.words.insert(b.words.end(), ops.begin(), ops.end());
+  b.words.resize((b.words.size() + 3) & ~size_t(3), 0u);
+  return x;
+}
+
 // Constants of prime P (other prime Q) for the CRT paths; S_P limbs per prime.
 inline PrimeOff put_prime(Blob &b, const Limbs &P, const Limbs &Q, const Limbs &n, size_t SP) {
   PrimeOff o;
@@ -186,9 +247,11 @@ inline PrimeOff put_prime(Blob &b, const Limbs &P, const Limbs &Q, const Limbs &
   const Limbs P2 = hebn::mul(P, P);
   o.P = put_mod(b, P, SP);
   o.P2 = put_mod(b, P2, 2 * SP);
-  o.pair = put_pair(b, P, SP);
-  const Limbs Pm1 = hebn::sub(P, one);
-  o.e_enc = put_exp(b, hebn::mod(Q, Pm1), SP);
+  const Limbs Pm1 = hebn::sub(P, one), e = hebn::mod(Q, Pm1);
+  const Limbs ej = hebn::is_zero(e) ? Pm1 : e;  // x^(P-1) = x^0 mod P
+  o.pair = put_pair(b, P, SP, ej);
+  o.joint = put_joint(b, Pm1, ej);
+  o.e_enc = put_exp(b, e, SP);
   o.e_lift = put_exp(b, P, SP);
   o.e_dec = put_exp(b, Pm1, SP);
   const Limbs RP = hebn::mod(pow2(32 * SP), P);
@@ -214,7 +277,7 @@ inline KeyConsts derive(uint32_t n_bits, const Limbs &n, const Limbs &p, const L
   Blob &b = k.blob;
   k.n = put_mod(b, n, L);
   k.n2 = put_mod(b, n2, 2 * L);
-  k.pair_n = put_pair(b, n, L);
+  k.pair_n = put_pair(b, n, L, Limbs());
   k.e_n = put_exp(b, n, L);
   const Limbs Rn2 = hebn::mod(pow2(64 * L), n2);
   const Limbs Rn = hebn::mod(pow2(32 * L), n);

@@ -3,10 +3,10 @@
 
 namespace he {
 
-const void *pow_lane16(int SN, int L, bool ct) {
-  if (SN == 16 && L == 0) return pow_pair_fn<16, 0>(ct);
-  if (SN == 16 && L == 1) return pow_pair_fn<16, 1>(ct);
-  if (SN == 16 && L == 2) return pow_pair_fn<16, 2>(ct);
+const void *pow_lane16(int SN, int L, PairPow which) {
+  if (SN == 16 && L == 0) return pow_pair_fn<16, 0>(which);
+  if (SN == 16 && L == 1) return pow_pair_fn<16, 1>(which);
+  if (SN == 16 && L == 2) return pow_pair_fn<16, 2>(which);
   return nullptr;
 }
 

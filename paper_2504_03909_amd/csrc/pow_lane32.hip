@@ -3,9 +3,9 @@
 
 namespace he {
 
-const void *pow_lane32(int SN, int L, bool ct) {
-  if (SN == 32 && L == 0) return pow_pair_fn<32, 0>(ct);
-  if (SN == 32 && L == 1) return pow_pair_fn<32, 1>(ct);
+const void *pow_lane32(int SN, int L, PairPow which) {
+  if (SN == 32 && L == 0) return pow_pair_fn<32, 0>(which);
+  if (SN == 32 && L == 1) return pow_pair_fn<32, 1>(which);
   return nullptr;
 }
 

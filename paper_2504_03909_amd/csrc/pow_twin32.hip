@@ -3,8 +3,8 @@
 
 namespace he {
 
-const void *pow_twin32(int SN, int L, bool ct) {
-  if (SN == 32 && L == 2) return pow_pair_fn<32, 2>(ct);
+const void *pow_twin32(int SN, int L, PairPow which) {
+  if (SN == 32 && L == 2) return pow_pair_fn<32, 2>(which);
   return nullptr;
 }
 

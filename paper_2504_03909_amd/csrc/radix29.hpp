@@ -40,7 +40,19 @@ constexpr int kPairPieces = 4;                // input pieces of 32 S bits
 constexpr int kPairOne = kPairPieces;         // (1, 0): leaves the Montgomery domain
 constexpr int kPairUnscale = kPairOne + 1;    // (2^(29 (S29 - 1)) mod N, 0): drops the second digit's 2^29
 constexpr int kPairR = kPairUnscale + 1;      // R mod N^2: Montgomery form of 1
-constexpr int kPairN = kPairR + 1;            // N
+constexpr int kPairE = kPairR + 1;            // e R mod N^2, and (1 - e) R mod N^2: with e the other prime mod
+constexpr int kPairE1 = kPairE + 1;           // (N - 1), they raise 1 + f N to the power e (0 where there is no e)
+constexpr int kPairN = kPairE1 + 1;           // N
 constexpr int pair_words(int S, int v) { return (2 * kPairN + 1) * pair_limbs(S, v); }
+
+// Schedule of two powers that share their squarings (keysetup.hpp,
+// joint_schedule): what an op does with its slot.
+constexpr int kJointBits = 5, kJointBuckets = 16;
+enum JointOp : unsigned {
+  kJointPut,   // slot = state
+  kJointLoad,  // state = slot
+  kJointTake,  // state *= slot
+  kJointAcc,   // slot *= state
+};
 
 }  // namespace he29
