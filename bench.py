@@ -747,7 +747,7 @@ def bench_batched(args, compact=False):
     same = all(torch.equal(a.hist, b.hist) and torch.equal(a.hist, c.hist) for a, b, c in zip(ja, jb, jc))
     # work counters at the tuned shape: products joining real partials vs executed
     L = key.limbs
-    prod = contrib * (2 * (2 * L) ** 2 + 2 * L)
+    prod = contrib * mm2_products(L)
     if compact:
         return {
             "workload": "64 node jobs, |S| log-uniform [1e3, 2e5], F uniform [8, 128], B in {16, 64, 256}, "
