@@ -185,12 +185,14 @@ def crt_encrypt_products(p: int, q: int, L: int) -> int:
     sp = L // 2
     tot = 0
     for P, Q in ((p, q), (q, p)):
-        # mod P: r reduction (3), m Q (2)
-        tot += (3 + 2) * mm_products(sp)
+        # mod P: r reduction (3), m Q and its product with the first digit (2);
+        # mod P^2: the second digit times P
+        tot += (3 + 2) * mm_products(sp) + mm_products(2 * sp)
         # mod P^2: in, the powers P - 1 and Q mod (P - 1), their joining (2), out (2)
         mults, sqs = joint_ops(P - 1, Q % (P - 1))
         tot += (mults + 5) * mm2_products(sp) + sqs * sq2_products(sp)
-    return tot
+    # the CRT: two products mod p^2, one mod n^2
+    return tot + 2 * mm_products(L) + mm_products(2 * L)
 
 
 def crt_decrypt_products(p: int, q: int, L: int) -> int:
@@ -198,9 +200,10 @@ def crt_decrypt_products(p: int, q: int, L: int) -> int:
     sp = L // 2
     tot = 0
     for P in (p, q):
-        # c mod P^2 (4 pieces), exponentiation, out (2), m_P = k h_P
-        tot += (4 + 2) * mm2_products(sp) + modexp2_products(P - 1, sp) + mm_products(sp)
-    return tot + mm_products(sp)
+        # c mod P^2 (4 pieces), exponentiation, out (2), exact division (a
+        # low-half product), m_P = k h_P
+        tot += (4 + 2) * mm2_products(sp) + modexp2_products(P - 1, sp) + sp * sp + mm_products(sp)
+    return tot + 3 * mm_products(sp) + mm_products(L)
 
 
 def hist_products(n_contrib: int, n_slots: int, rows: int, L: int) -> int:
@@ -438,8 +441,9 @@ def main():
     torch.cuda.synchronize()
     pub_same = bool(torch.equal(ct_pub, ct.view(-1, 2 * L)[:n_pub]))
     t_pub = pub_marks[0].elapsed_time(pub_marks[1])
-    # in, the exponentiation by n mod n^2 in two digits base n, out (2)
-    pub_products = modexp2_products(n, L) + 3 * mm2_products(L)
+    # in, the exponentiation by n mod n^2 in two digits base n, out (2), then m and
+    # its product with the first digit, and the second digit times n
+    pub_products = modexp2_products(n, L) + 3 * mm2_products(L) + 2 * mm_products(L) + mm_products(2 * L)
     del ct_pub, pub
     # Beside the step: packed decryption of the same 16,384 histogram
     # ciphertexts (the passive party folds 4 per ciphertext).
