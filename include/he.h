@@ -84,18 +84,19 @@ int he_key_import(uint32_t n_bits, const uint32_t *p, const uint32_t *q, he_key 
 int he_key_export(const he_key *key, uint32_t *n, uint32_t *p, uint32_t *q);
 
 /* Side-channel hardening of the private-key exponentiations (the CRT
- * encryption's r^(q mod (p-1)) mod p and x^p mod p^2, and decryption's
- * c^(p-1) mod p^2, whose exponents are secret; Sec. III-B: only the active
- * party holds p and q).  Off (the default), each exponentiation follows the
- * key's sliding-window schedule: the same sequence of operations for every
- * ciphertext and call, a function of p and q (not of the data), and each
- * window reads the one table entry it names.  With on != 0 they use fixed
+ * encryption's r^n mod p^2 and decryption's c^(p-1) mod p^2, whose exponents
+ * are secret; Sec. III-B: only the active party holds p and q).  Off (the
+ * default), each exponentiation follows the key's schedule of windows: the
+ * same sequence of operations for every ciphertext and call, a function of p
+ * and q (not of the data), and each window reads (in encryption, updates) the
+ * one table entry it names.  With on != 0 encryption runs r^(q mod (p-1)) mod p
+ * and then x^p mod p^2, and all use fixed
  * 5-bit windows, one multiplication per window whatever its digit, and
  * every window reads all 32 table entries and keeps the one its digit names
  * by a mask, so neither the operations nor the device addresses touched
- * depend on the exponent (about 1.6x the default's encryption time on the
- * 2048-bit pass).  Results are identical bit for bit.  Applies to calls enqueued after it returns; must not run
- * concurrently with other calls on the same key.  HE_ERR_ARG for a null key. */
+ * depend on the exponent (about 2.1x the default's encryption time on the
+ * 2048-bit pass).  Results are identical bit for bit.  Applies to calls enqueued
+ * after it returns; must not run concurrently with other calls on the same key.  HE_ERR_ARG for a null key. */
 int he_key_set_constant_time(he_key *key, int on);
 
 /* Number of bits of n, and whether the key holds p and q (1) or not (0). */
@@ -244,7 +245,7 @@ int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t rows, int c
  * and the remainder (less than one round) at a wider group per integer, so
  * that the last partial round spreads over more waves.  Trials run on
  * enc_count encryptions and dec_count decryptions of trial operands (the
- * sliding-window schedule is fixed per key, so the running time does not
+ * schedules are fixed per key, so the running time does not
  * depend on the data), and the fastest per kind is remembered for the
  * count's size class (bit length) on this device and key size; later
  * he_encrypt, he_obfuscators and he_decrypt calls of that class use it.
