@@ -113,7 +113,7 @@ __global__ void k_encode(const double *__restrict__ x, uint64_t count, uint32_t 
 // in_limbs limbs at in + (2 i + w) in_stride (zero-extended to S32) and writes
 // S32 canonical limbs at out + (2 i + w) out_stride.  Work unit = (prime, 64/G
 // consecutive ciphertexts), so the modulus and exponent are the same for the
-// whole wave.  CT: constant-time window-table reads.  At most 3 waves per SIMD:
+// whole wave.  For secret exponents: every table entry is read.  At most 3 waves per SIMD:
 // the 18-limb-per-lane shape needs about 168 VGPRs to run its step loops
 // without spills.  With `next` (a counter zeroed before the launch) the waves
 // claim units as they finish them, so they end together; without, wave w takes

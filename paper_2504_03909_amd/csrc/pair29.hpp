@@ -902,8 +902,8 @@ struct GroupPair {
 // X <- X^e mod N^2 (mod N for LaneMod) for one unit of 64 / kLanes integers:
 // in, `pieces` pieces of SN 32-bit limbs (X = sum_h x_h 2^(32 SN h)); out, the
 // digits (a, e) of X^e = a + e N, canonical, SN limbs each (LaneMod: X^e).
-// The schedules are pow29's: sliding windows over odd powers, or (CT) fixed
-// windows and masked reads of every table entry.  One loop holds the only copy
+// Schedules: sliding windows over odd powers (keysetup.hpp), or (CT) fixed
+// windows and masked reads of every table entry, as in pow29.  One loop holds the only copy
 // of the squaring and of the product, since each fills a good part of the
 // instruction cache; what surrounds them is chosen by wave-uniform state.
 template <class E, int SN, bool CT>
