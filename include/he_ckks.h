@@ -43,8 +43,10 @@ int he_ckks_params(const he_ckks *ctx, uint32_t *n, uint32_t *primes, uint32_t *
 int he_ckks_encode(const he_ckks *ctx, const double *z, uint64_t count, uint32_t n_values, uint32_t *pt,
                    hipStream_t stream);
 /* Encrypts count plaintexts; ciphertext t uses the randomness of index
- * offset + t under `seed`.  ct: [count][2][3][N].  Not reentrant per context
- * (a context-owned scratch buffer holds the randomness). */
+ * offset + t under `seed`.  ct: [count][2][3][N]; it must not overlap pt, and
+ * it holds the randomness in clear until the call's work is done (a call that
+ * cannot launch all of it clears ct and fails).  Reentrant: the context is only
+ * read, so calls on one context may overlap if their buffers do not. */
 int he_ckks_encrypt(he_ckks *ctx, const uint32_t *pt, uint64_t count, uint64_t seed, uint64_t offset, uint32_t *ct,
                     hipStream_t stream);
 /* out = x + y for count ciphertexts (out may alias x or y). */

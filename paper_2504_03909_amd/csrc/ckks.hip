@@ -20,6 +20,7 @@
 
 #include "../../include/he.h"
 #include "../../include/he_ckks.h"
+#include "he_internal.hpp"
 #include "mont.hpp"
 
 namespace {
@@ -809,12 +810,18 @@ int he_ckks_encrypt(he_ckks *c, const uint32_t *pt, uint64_t count, uint64_t see
   if (count * 2 * kL > 0x7FFFFFFFull || count * c->n > 0xFFFFFFFFull) return fail(HE_ERR_ARG, "count too large");
   const uint64_t quads = count * (c->n / 4);
   hipLaunchKernelGGL(k_sample_enc, dim3(blocks(quads, 256)), dim3(256), 0, s, seed, offset, c->log_n, quads, ct);
+  CK_TRY(hipGetLastError());
   for_ring(c->log_n, [&](auto ln) {
     constexpr int LN = decltype(ln)::value;
     hipLaunchKernelGGL(k_encrypt<LN>, dim3((uint32_t)(count * kL * 2)), dim3(Ntt<LN>::T), Ntt<LN>::kLds * 4, s, pt,
                        c->T, c->d_keys, ct);
   });
-  CK_TRY(hipGetLastError());
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) {
+    // ct holds u, e0 and e1 in clear: they must not reach the caller
+    (void)he::launch_fill(ct, 2 * count * kL * (uint64_t)c->n, 0u, s);
+    return fail(HE_ERR_DEVICE, hipGetErrorString(e));
+  }
   return HE_OK;
 }
 
