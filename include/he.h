@@ -247,7 +247,8 @@ int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t rows, int c
  * enc_count encryptions and dec_count decryptions of trial operands (the
  * schedules are fixed per key, so the running time does not
  * depend on the data), and the fastest per kind is remembered for the
- * count's size class (bit length) on this device and key size; later
+ * count's size class (bit length) on this device, for keys of this size with
+ * the same constant-time option (the two run other kernels); their later
  * he_encrypt, he_obfuscators and he_decrypt calls of that class use it.
  * Results never depend on the shape.  Without a tuned (or pinned) shape, and
  * where no timed shape beats it, a kind's launches are planned from the count
@@ -272,7 +273,8 @@ int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t dec_count, u
  * per integer (2, 4, 8 or 16 where built for the kind; 8 or 16 for kind 3 at
  * 2048-bit keys),
  * waves per SIMD (0 = own occupancy, 2 or 3) and lanes of the last partial
- * round's launch (0 = one launch, else a built width above lanes).  Results
+ * round's launch (0 = one launch, else a built width above lanes).  A pin holds
+ * for every key of the size, constant-time or not.  Results
  * never depend on the shape.  HE_ERR_ARG for anything else. */
 int he_crt_set_shape(const he_key *key, uint32_t kind, uint64_t count, uint32_t lanes, uint32_t waves,
                      uint32_t tail_lanes);

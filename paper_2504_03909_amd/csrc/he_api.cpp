@@ -186,9 +186,10 @@ int ensure(Buf &b, size_t bytes, hipStream_t s) {
 }
 
 // ------------------------------------------------- exponentiation launch shapes
-// Tuned shapes (lanes per integer, waves per SIMD) of the private-key
-// exponentiations per (device, key size, kind, count class), filled by
-// he_crt_autotune; count class = bit length of the count.
+// Tuned shapes (lanes per integer, waves per SIMD) of the exponentiations per
+// (device, key size, kind, count class), filled by he_crt_autotune and
+// he_crt_set_shape; count class = bit length of the count.  A kind is one set of
+// kernels (he_internal.hpp), so a shape timed on one is never used for another.
 struct PowShape {
   int G = 0, waves = 0;  // G 0: the default plan; waves 0: the kernel's own occupancy
   int tailG = 0;         // lanes per integer of the last partial round's launch (0: no separate launch)
@@ -320,7 +321,7 @@ he::PowPlan pow_plan(int KP, int kind, uint64_t count) {
   (void)hipGetDevice(&dev);
   {
     std::lock_guard<std::mutex> lk(g_pow_mu);
-    auto it = g_pow_tuned.find({dev, KP, kind == 3 ? 0 : kind, count_class(count)});
+    auto it = g_pow_tuned.find({dev, KP, kind, count_class(count)});
     if (it != g_pow_tuned.end()) sh = it->second;
   }
   return sh.G ? pow_plan_at(KP, kind, count, sh) : default_pow_plan(KP, kind, count);
@@ -338,7 +339,7 @@ int encrypt_impl(const he_key *key, const int64_t *m, uint64_t count, const uint
   if (key->priv && !force_pub) {
     // secret digits: r^(Q mod (P-1)) mod P, then its power P; else both at once
     const he::DKey dk = key->dk;
-    const int kind = dk.ct ? 0 : 3;
+    const int kind = he::pow_lift_kind(dk);
     he::PowPlan p1{}, p2 = pow_plan(KP, kind, count);
     uint64_t tab_bytes = plan_table_bytes(KP, kind, p2);
     if (dk.ct) {
@@ -559,8 +560,10 @@ int he_decrypt(const he_key *key, const uint32_t *ct, uint64_t count, int64_t *m
   Workspace *w = workspace(stream);
   const int KP = kp_of(key);
   const size_t L = key->n_bits / 32;
-  he::PowPlan p = pow_plan(KP, 2, count);
-  int rc = ensure(w->tab, plan_table_bytes(KP, 2, p), stream);
+  const he::DKey dk = key->dk;
+  const int kind = he::pow_dec_kind(dk);
+  he::PowPlan p = pow_plan(KP, kind, count);
+  int rc = ensure(w->tab, plan_table_bytes(KP, kind, p), stream);
   if (rc) return rc;
   rc = ensure(w->ctr, 256, stream);
   if (rc) return rc;
@@ -568,7 +571,7 @@ int he_decrypt(const he_key *key, const uint32_t *ct, uint64_t count, int64_t *m
   // c^(P-1) mod P^2 per (ciphertext, prime): 2L limbs per ciphertext
   rc = ensure(w->tmp, count * 2 * L * sizeof(uint32_t), stream);
   if (rc) return rc;
-  HE_TRY_HIP(he::launch_dec(KP, key->dk, ct, count, (uint32_t *)w->tmp.p, m, raw, n_overflow,
+  HE_TRY_HIP(he::launch_dec(KP, dk, ct, count, (uint32_t *)w->tmp.p, m, raw, n_overflow,
                             (uint32_t *)w->tab.p, p, stream));
   return HE_OK;
 }
@@ -632,10 +635,12 @@ int he_decrypt_noalloc(const he_key *key, const uint32_t *ct, uint64_t count, in
   // narrowest width that still puts a wave on every SIMD (a table holds as
   // many integers at every width, so wider groups mean more waves).
   const uint64_t cus = (uint64_t)he::device_cus();
+  const he::DKey dk = key->dk;
+  const int kind = he::pow_dec_kind(dk);
   he::PowLaunch l{};
   for (int G : {2, 4, 8, 16}) {
-    l = pow_launch_at(KP, 2, count, PowShape{G, 0, 0});
-    const uint64_t fit = (kNoAllocBytes - xpq_bytes) / he::table_bytes_per_block(KP, 2, G);
+    l = pow_launch_at(KP, kind, count, PowShape{G, 0, 0});
+    const uint64_t fit = (kNoAllocBytes - xpq_bytes) / he::table_bytes_per_block(KP, kind, G);
     if (fit == 0) return fail(HE_ERR_ARG, "he_decrypt_noalloc: no room for one block's window tables");
     l.grid = (uint32_t)std::min<uint64_t>(fit, l.grid);
     if (l.grid >= cus) break;
@@ -643,7 +648,7 @@ int he_decrypt_noalloc(const he_key *key, const uint32_t *ct, uint64_t count, in
   uint32_t *xpq = (uint32_t *)base;
   uint32_t *tab = (uint32_t *)((char *)base + xpq_bytes);
   // static units: no work counter in the scratch
-  HE_TRY_HIP(he::launch_dec(KP, key->dk, ct, count, xpq, m, raw, n_overflow, tab,
+  HE_TRY_HIP(he::launch_dec(KP, dk, ct, count, xpq, m, raw, n_overflow, tab,
                             he::PowPlan{l, count, he::PowLaunch{0, 0, 0}, nullptr}, stream));
   return HE_OK;
 }
@@ -1039,7 +1044,7 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   DevBuf tq, cpq, ct, xpq, tab, ctr;
   size_t tab_bytes = 0;
   // mod P, the lift (with public digits: both powers at once), decryption
-  const int kinds[3] = {4, key->dk.ct ? 0 : 3, 2};
+  const int kinds[3] = {4, he::pow_lift_kind(key->dk), he::pow_dec_kind(key->dk)};
   for (int kind : kinds)
     for (int G : {1, 2, 4, 8, 16})
       if (he::pow_shape_valid(KP, kind, G))
@@ -1065,12 +1070,12 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   float best_ms[3] = {1e30f, 1e30f, 1e30f};
   for (int t = 0; t < 3 && !rc; ++t) {
     const int kind = kinds[t];
-    const uint64_t count = kind == 2 ? dec_count : enc_count;
+    const uint64_t count = t == 2 ? dec_count : enc_count;
     auto trial = [&](const PowShape &sh, he::PowPlan p) -> int {
       p.ctr = (uint32_t *)ctr.p;
       auto run = [&]() -> hipError_t {
-        return he::launch_pow_kind(KP, key->dk, kind, kind == 2 ? ct_p : tq_p, kind == 4 ? tq_p : (kind == 2 ? xpq_p : cpq_p),
-                                   count, tab_p, p, stream);
+        return he::launch_pow_kind(KP, key->dk, kind, t == 2 ? ct_p : tq_p, t == 0 ? tq_p : (t == 2 ? xpq_p : cpq_p), count,
+                                   tab_p, p, stream);
       };
       float ms = 0;
       const int r = time_ms(run, stream, e0, e1, &ms);
@@ -1113,11 +1118,11 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   {
     std::lock_guard<std::mutex> lk(g_pow_mu);
     for (int t = 0; t < 3; ++t)
-      g_pow_tuned[{dev, KP, kinds[t] == 3 ? 0 : kinds[t], count_class(kinds[t] == 2 ? dec_count : enc_count)}] = best[t];
+      g_pow_tuned[{dev, KP, kinds[t], count_class(t == 2 ? dec_count : enc_count)}] = best[t];
   }
   for (int t = 0; t < 3; ++t) {
     if (choice) {
-      const he::PowPlan dp = default_pow_plan(KP, kinds[t], kinds[t] == 2 ? dec_count : enc_count);
+      const he::PowPlan dp = default_pow_plan(KP, kinds[t], t == 2 ? dec_count : enc_count);
       choice[3 * t] = (uint32_t)(best[t].G ? best[t].G : dp.main.G);
       choice[3 * t + 1] = (uint32_t)best[t].waves;
       choice[3 * t + 2] = (uint32_t)(best[t].G ? best[t].tailG : dp.tail.G);
@@ -1144,7 +1149,11 @@ extern "C" int he_crt_set_shape(const he_key *key, uint32_t kind, uint64_t count
   int dev = 0;
   HE_TRY_HIP(hipGetDevice(&dev));
   std::lock_guard<std::mutex> lk(g_pow_mu);
-  g_pow_tuned[{dev, KP, k, count_class(units)}] = PowShape{(int)lanes, (int)waves, (int)tail_lanes};
+  // a pin holds for every key of this size: the lift and decryption with secret
+  // digits and without
+  const int both[2] = {k, k == 0 ? 3 : (k == 2 ? 5 : k)};
+  for (int kk : both)
+    g_pow_tuned[{dev, KP, kk, count_class(units)}] = PowShape{(int)lanes, (int)waves, (int)tail_lanes};
   return HE_OK;
 }
 

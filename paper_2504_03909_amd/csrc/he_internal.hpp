@@ -194,7 +194,7 @@ hipError_t launch_mont_convert(int KP, const DKey &k, const uint32_t *in, uint64
                                uint32_t *out, bool to_mont, hipStream_t s);
 // The pieces, for the autotuner: r mod P into tq; one private-key
 // exponentiation of `kind` (4 mod P: tq in place, 0 lift, 3 both powers: tq into out, 2
-// decryption: ciphertexts into out).
+// and 5 decryption: ciphertexts into out).
 hipError_t launch_enc_r(int KP, const DKey &k, uint64_t count, const uint32_t *r, uint64_t seed, uint64_t roff,
                         uint32_t *tq, hipStream_t s);
 hipError_t launch_pow_kind(int KP, const DKey &k, int kind, const uint32_t *in, uint32_t *out, uint64_t count,
@@ -219,10 +219,13 @@ hipError_t launch_fill(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_probe_mul(uint64_t iters, uint32_t grid, uint32_t *sink, hipStream_t s);
 
 // The exponentiations by kind -- 4 mod P and 0 (lift) of an encryption with secret
-// digits, 3 (both powers at once) of the others, 2 (decryption) mod P^2,
-// 1 (public key) mod n^2 -- at G lanes per integer: whether that shape is
-// built, its resident blocks with `dyn` bytes of dynamic LDS, and the dynamic
-// LDS that caps it at `waves` blocks per compute unit (0: no cap).
+// digits, 3 (both powers at once) of the others, 2 (decryption) mod P^2 and 5
+// the same with secret digits, 1 (public key) mod n^2 -- at G lanes per integer:
+// whether that shape is built, its resident blocks with `dyn` bytes of dynamic
+// LDS, and the dynamic LDS that caps it at `waves` blocks per compute unit (0:
+// no cap).
+inline int pow_lift_kind(const DKey &k) { return k.ct ? 0 : 3; }
+inline int pow_dec_kind(const DKey &k) { return k.ct ? 5 : 2; }
 bool pow_shape_valid(int KP, int kind, int G);
 int device_cus();
 uint32_t pow_resident_blocks(int KP, int kind, int G, uint32_t dyn);

@@ -1261,7 +1261,7 @@ static int pow_base(int KP, int kind) { return kind == 1 ? 32 * KP : 16 * KP; }
 // The exponentiation kernel of `kind` at G lanes per integer, null if not
 // built.  Mod P (4) and the lift (0), the two steps of an encryption whose
 // digits are secret, read their tables masked; an encryption that need not hide
-// them takes kind 3; decryption (2) comes both ways; the public exponent n
+// them takes kind 3; decryption is kind 2, or masked 5; the public exponent n
 // is never secret.  Mod P: k_pow from 2 lanes on, one residue per lane below.
 template <int S32>
 static const void *pow_mod_kernel(int G) {
@@ -1273,21 +1273,21 @@ static const void *pow_mod_kernel(int G) {
     default: return nullptr;
   }
 }
-static const void *pow_kernel(int KP, int kind, int G, bool ct) {
+static const void *pow_kernel(int KP, int kind, int G) {
   const int SN = pow_base(KP, kind);
   if (kind == 3) return pow_pair_kernel(SN, G, PairPow::kJoint);
-  if (kind == 1 || (kind == 2 && !ct)) return pow_pair_kernel(SN, G, PairPow::kSliding);
+  if (kind == 1 || kind == 2) return pow_pair_kernel(SN, G, PairPow::kSliding);
   if (kind != 4) return pow_pair_kernel(SN, G, PairPow::kMasked);
   if (G == 1) return pow_pair_kernel(SN, 0, PairPow::kMasked);
   return KP == 1 ? pow_mod_kernel<16>(G) : pow_mod_kernel<32>(G);
 }
-bool pow_shape_valid(int KP, int kind, int G) { return pow_kernel(KP, kind, G, false) != nullptr; }
+bool pow_shape_valid(int KP, int kind, int G) { return pow_kernel(KP, kind, G) != nullptr; }
 
 // One launch of an exponentiation over the unit pairs [first, first + count).
 static hipError_t launch_pow(int KP, const DKey &k, int kind, const uint32_t *in, uint32_t *out, uint64_t first,
                              uint64_t count, uint32_t *tabs, uint32_t *next, const PowLaunch &l, hipStream_t s) {
   const uint32_t SN = (uint32_t)pow_base(KP, kind);
-  const void *fn = pow_kernel(KP, kind, l.G, k.ct != 0);
+  const void *fn = pow_kernel(KP, kind, l.G);
   if (!fn) return hipErrorInvalidValue;
   if (kind == 4 && l.G > 1) {
     PowArgs a{};
@@ -1313,14 +1313,16 @@ static hipError_t launch_pow(int KP, const DKey &k, int kind, const uint32_t *in
     switch (kind) {
       case 0: a.exp[w] = k.pr[w].e_lift; break;
       case 1: a.exp[w] = k.e_n; break;
-      case 2: a.exp[w] = k.pr[w].e_dec; break;
+      case 2:
+      case 5: a.exp[w] = k.pr[w].e_dec; break;
       case 3: a.exp[w] = k.pr[w].joint; break;
       default: a.exp[w] = k.pr[w].e_enc;
     }
   }
-  a.pieces = kind == 2 ? 4 : 1;
-  a.in_w = kind == 2 ? 0 : SN;
-  a.in_i = kind == 2 ? 4 * SN : 2 * SN;
+  const bool dec = kind == 2 || kind == 5;
+  a.pieces = dec ? 4 : 1;
+  a.in_w = dec ? 0 : SN;
+  a.in_i = dec ? 4 * SN : 2 * SN;
   a.out_w = kind == 4 ? SN : 2 * SN;
   a.out_i = 2 * a.out_w;
   a.in = in + first * a.in_i;
@@ -1335,7 +1337,7 @@ static hipError_t launch_pow(int KP, const DKey &k, int kind, const uint32_t *in
 // The plan's launches over `count` unit pairs: the first main_count at
 // p.main, the rest at p.tail, each with its work counter in p.ctr when given
 // (cleared here, in stream order).  Kind 4 works on tq in place, 0 and 3 read tq,
-// 2 the ciphertexts, 1 the rows of r mod n; all but 4 write two digits.
+// 2 and 5 the ciphertexts, 1 the rows of r mod n; all but 4 write two digits.
 hipError_t launch_pow_kind(int KP, const DKey &k, int kind, const uint32_t *in, uint32_t *out, uint64_t count,
                            uint32_t *tab, const PowPlan &p, hipStream_t s) {
   if (!count) return hipSuccess;
@@ -1372,7 +1374,7 @@ static hipError_t enc_crt(const DKey &k, const int64_t *m, uint64_t count, const
                      roff, tq);
   hipError_t e = k.ct ? launch_pow_kind(KP, k, 4, tq, tq, count, tab, p1, s) : hipSuccess;
   if (e != hipSuccess) return e;
-  e = launch_pow_kind(KP, k, k.ct ? 0 : 3, tq, cpq, count, tab, p2, s);
+  e = launch_pow_kind(KP, k, pow_lift_kind(k), tq, cpq, count, tab, p2, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_enc_crt_b<KP>, dim3(blocks_for(count, 16)), dim3(kBlockThreads), 0, s, k, m,
                      (const uint32_t *)cpq, count, ct);
@@ -1498,7 +1500,7 @@ hipError_t launch_mont_convert(int KP, const DKey &k, const uint32_t *in, uint64
 template <int KP>
 static hipError_t dec(const DKey &k, const uint32_t *ct, uint64_t count, uint32_t *xpq, int64_t *m,
                       uint32_t *raw, uint32_t *n_overflow, uint32_t *tab, const PowPlan &p, hipStream_t s) {
-  const hipError_t e = launch_pow_kind(KP, k, 2, ct, xpq, count, tab, p, s);
+  const hipError_t e = launch_pow_kind(KP, k, pow_dec_kind(k), ct, xpq, count, tab, p, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_dec_b<KP>, dim3(blocks_for(count, 16)), dim3(kBlockThreads), 0, s, k,
                      (const uint32_t *)xpq, count, m, raw, n_overflow);
@@ -1576,7 +1578,7 @@ uint32_t ct_div_batch(uint64_t count) {
 uint32_t pow_resident_blocks(int KP, int kind, int G, uint32_t dyn) {
   static std::mutex mu;
   static std::map<std::tuple<const void *, uint32_t>, uint32_t> cache;
-  const void *fn = pow_kernel(KP, kind, G, false);
+  const void *fn = pow_kernel(KP, kind, G);
   std::lock_guard<std::mutex> lk(mu);
   auto it = cache.find({fn, dyn});
   if (it != cache.end()) return it->second;
@@ -1608,7 +1610,7 @@ static uint32_t cap_dyn_lds(const void *fn, int natural, int waves) {
 // is 0 or the kernel's own occupancy is at most `waves`.
 uint32_t pow_dyn_lds(int KP, int kind, int G, int waves) {
   if (waves <= 0 || !pow_shape_valid(KP, kind, G)) return 0;
-  return cap_dyn_lds(pow_kernel(KP, kind, G, false),
+  return cap_dyn_lds(pow_kernel(KP, kind, G),
                      (int)(pow_resident_blocks(KP, kind, G, 0) / (uint32_t)device_cus()), waves);
 }
 

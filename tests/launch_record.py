@@ -95,7 +95,13 @@ int hipEventElapsedTime(float *ms, void *, void *) { *ms = timed++ == fastest ? 
 int hipFuncGetAttributes(void *a, const void *) { memset(a, 0, 56); return 0; }
 int hipFuncSetAttribute(const void *, int, int) { return 0; }
 int hipGetSymbolAddress(void **p, const void *) { *p = scratch; return 0; }
-int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = 2; return 0; }
+// blocks per compute unit: one for a kernel whose name holds rec_single's text, else two
+static std::string single;
+void rec_single(const char *name) { single = name; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *fn, int, size_t) {
+  *n = !single.empty() && names.count(fn) && names[fn].find(single) != std::string::npos ? 1 : 2;
+  return 0;
+}
 int hipStreamSynchronize(void *) { return 0; }
 int hipStreamCreateWithFlags(void **s, unsigned) { *s = &handle; return 0; }
 int hipStreamDestroy(void *) { return 0; }

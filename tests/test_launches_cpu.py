@@ -33,3 +33,64 @@ def test_ckks_encrypt_leaves_no_samples_behind_a_failed_launch(tmp_path):
     assert at == [got["ct"]] and words == [got["words"]], names
     rc, names, _, _ = got["k_sample_enc"]
     assert rc == -6 and len(names) == 1, names
+
+
+# ---------------------------------------------------- exponentiation shapes
+KEYS = r"""
+bits, p, q = env["bits"], int(env["p"]), int(env["q"])
+plain, secret = key(bits, p, q), key(bits, p, q)
+assert lib.he_key_set_constant_time(secret, 1) == 0
+A, B = vp(0x100000), vp(0x900000)  # device addresses, never read on the host
+
+def encrypt(k, count):
+    rec.rec_reset()
+    assert lib.he_encrypt(k, A, u64(count), None, u64(1), u64(0), B, None) == 0
+    return launches()
+
+def decrypt(k, count):
+    rec.rec_reset()
+    assert lib.he_decrypt(k, A, u64(count), B, None, None, None) == 0
+    return launches()
+
+def tune(k, enc, dec):
+    choice, ms = (u32 * 9)(), (ctypes.c_float * 3)()
+    assert lib.he_crt_autotune(k, u64(enc), u64(dec), choice, ms, None) == 0, lib.he_last_error()
+    return list(choice), list(ms)
+"""
+
+
+@pytest.fixture(scope="module")
+def primes():
+    import oracle.paillier as P
+    return {bits: [str(x) for x in P.keygen(bits, seed)] for bits, seed in ((1024, 1), (2048, 2))}
+
+
+@pytest.mark.parametrize("bits", [1024, 2048])
+def test_tuning_one_kind_of_key_leaves_the_other_alone(tmp_path, primes, bits):
+    """Constant-time keys run other kernels: what was timed for an ordinary key's
+    is not used for theirs, and the reverse."""
+    got = record(tmp_path, KEYS + r"""
+n = 5000
+def squared(k):  # the launches of the exponentiations mod p^2 (those mod p are constant-time keys' alone)
+    return [l for l in encrypt(k, n) + decrypt(k, n) if "k_pow" in l[0] and "k_powI" not in l[0] and "ELi0E" not in l[0]]
+
+for name, tuned, other in (("plain", plain, secret), ("secret", secret, plain)):
+    before, own = squared(other), squared(tuned)
+    tune(tuned, n, n)  # every trial takes as long: the first, one lane per integer, stays
+    out[name] = [before, squared(other), own, squared(tuned)]
+    n *= 4  # another class
+""", bits=bits, p=primes[bits][0], q=primes[bits][1])
+    for before, after, own, own_after in got.values():
+        assert before == after
+        assert own != own_after  # the tuner's choice did take effect
+
+
+def test_masked_decryption_is_planned_on_its_own_kernel(tmp_path, primes):
+    """The resident blocks of a constant-time key's decryption are the masked
+    kernel's, not those of the kernel with sliding windows."""
+    got = record(tmp_path, KEYS + r"""
+rec.rec_single(b"Lb1E")  # k_pow_pair<.., .., true>
+out["secret"], out["plain"] = decrypt(secret, 60000), decrypt(plain, 60000)
+""", bits=2048, p=primes[2048][0], q=primes[2048][1])
+    grids = {k: [g for name, g, _ in v if "k_pow" in name] for k, v in got.items()}
+    assert max(grids["secret"]) <= 256 and max(grids["plain"]) <= 512, grids
