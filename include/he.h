@@ -235,9 +235,9 @@ int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t rows, int c
 /* Autotuner for the private-key exponentiations: the CRT encryption's r^n mod
  * p^2 (Sec. III-C: 2M encryptions for M samples; the "lift", one launch for
  * both of its exponents -- for a constant-time key the power r^q mod p, "mod
- * p", and then the p-th power mod p^2; a key without that option is timed on
- * mod p all the same, for the constant-time keys of its size) and decryption's
- * exponentiation mod p^2.  Times
+ * p", and then the p-th power mod p^2) and decryption's exponentiation mod p^2.
+ * A key without that option has no step mod p: the launch that step would have
+ * is timed for the report, and nothing is remembered for it.  Times
  * every built launch shape of each -- lanes per integer (2, 4, 8 or 16) and
  * waves per SIMD (the kernel's own occupancy, or 3 or 2 by reserving LDS) --
  * and then, at the best of those, the same work in two launches: the

@@ -1086,6 +1086,14 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
       }
       return HE_OK;
     };
+    // Ordinary keys have no step mod P: its present plan is timed for the report
+    // and nothing remembered (a sweep took 15 times three launches of up to 140 ms
+    // each at 200,000 encryptions).
+    if (t == 0 && !key->dk.ct) {
+      const he::PowPlan p = pow_plan(KP, kind, count);
+      rc = trial(PowShape{p.main.G, 0, p.tail.G}, p);
+      continue;
+    }
     // lanes per integer and waves per SIMD in one launch, then, at the best
     // of those, a separate launch for the last partial round at each wider
     // group
@@ -1117,7 +1125,7 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   if (rc) return rc;
   {
     std::lock_guard<std::mutex> lk(g_pow_mu);
-    for (int t = 0; t < 3; ++t)
+    for (int t = key->dk.ct ? 0 : 1; t < 3; ++t)
       g_pow_tuned[{dev, KP, kinds[t], count_class(t == 2 ? dec_count : enc_count)}] = best[t];
   }
   for (int t = 0; t < 3; ++t) {

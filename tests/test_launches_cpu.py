@@ -94,3 +94,18 @@ out["secret"], out["plain"] = decrypt(secret, 60000), decrypt(plain, 60000)
 """, bits=2048, p=primes[2048][0], q=primes[2048][1])
     grids = {k: [g for name, g, _ in v if "k_pow" in name] for k, v in got.items()}
     assert max(grids["secret"]) <= 256 and max(grids["plain"]) <= 512, grids
+
+
+def test_ordinary_keys_do_not_sweep_a_step_they_do_not_have(tmp_path, primes):
+    """The exponentiation mod p is constant-time keys' alone: tuning an ordinary key
+    launches it for one timing only and changes nothing for those keys."""
+    got = record(tmp_path, KEYS + r"""
+before = encrypt(secret, 5000)
+rec.rec_reset()
+choice, ms = tune(plain, 5000, 3000)
+out["launches"] = [l[0] for l in launches() if "k_powI" in l[0] or "ELi0E" in l[0]]
+out["choice"], out["ms"] = choice, ms
+out["same"] = encrypt(secret, 5000) == before
+""", bits=2048, p=primes[2048][0], q=primes[2048][1])
+    assert 1 <= len(got["launches"]) <= 3, got["launches"]  # a warm-up and two timed runs
+    assert got["same"] and got["choice"][0] > 0 and min(got["ms"]) > 0
