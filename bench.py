@@ -511,8 +511,9 @@ def main():
             "hist_lanes": hist_tune.lanes, "hist_waves_per_simd": hist_tune.waves or "own occupancy",
             "hist_shape": ("library defaults" if args.fixed_shapes else
                            "autotuned before timing" if args.chunk == 0 else "given"),
-            "exponentiation_shapes": {k: {"lanes": v.lanes, "waves_per_simd": v.waves or "own occupancy",
-                                          "last_round_lanes": v.tail_lanes or "same launch",
+            "exponentiation_shapes": {k: {"lanes": v.lanes or "default plan",
+                                          "waves_per_simd": v.waves or "own occupancy",
+                                          "last_round_lanes": (v.tail_lanes or "same launch") if v.lanes else "planned",
                                           "tuning_ms": round(v.ms, 3)} for k, v in exp_shapes.items()},
         },
         "stages": {

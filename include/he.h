@@ -238,12 +238,12 @@ int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t rows, int c
  * p", and then the p-th power mod p^2) and decryption's exponentiation mod p^2.
  * A key without that option has no step mod p: the launch that step would have
  * is timed for the report, and nothing is remembered for it.  Times
- * every built launch shape of each -- lanes per integer (2, 4, 8 or 16) and
+ * every launch shape of each that he_crt_set_shape takes -- lanes per integer and
  * waves per SIMD (the kernel's own occupancy, or 3 or 2 by reserving LDS) --
- * and then, at the best of those, the same work in two launches: the
- * ciphertexts that fill whole rounds of the resident waves at that shape,
- * and the remainder (less than one round) at a wider group per integer, so
- * that the last partial round spreads over more waves.  Trials run on
+ * then the default plan (below), and, at the best of the shapes, the same work in
+ * two launches: the ciphertexts that fill whole rounds of the resident waves at
+ * that shape, and the remainder (less than one round) at a wider group per integer,
+ * so that the last partial round spreads over more waves.  Trials run on
  * enc_count encryptions and dec_count decryptions of trial operands (the
  * schedules are fixed per key, so the running time does not
  * depend on the data), and the fastest per kind is remembered for the
@@ -251,13 +251,14 @@ int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t rows, int c
  * the same constant-time option (the two run other kernels); their later
  * he_encrypt, he_obfuscators and he_decrypt calls of that class use it.
  * Results never depend on the shape.  Without a tuned (or pinned) shape, and
- * where no timed shape beats it, a kind's launches are planned from the count
- * and each width's measured cost (1, 2, 4, 8 or 16 lanes per integer where
- * built, the rest of a last partly filled round at a wider one).  Allocates
+ * where no timed shape beats it, a kind's launches follow the default plan: from
+ * each count and each width's measured cost (1, 2, 4, 8 or 16 lanes per integer
+ * where built, the rest of a last partly filled round at a wider one).  Allocates
  * trial buffers and synchronises `stream`.
  * choice: optional host uint32[9]: per kind (the mod-p exponentiation, the
- *         lift, decryption) lanes, waves (0 = own occupancy) and lanes of
- *         the remainder's launch (0 = one launch).
+ *         lift, decryption) lanes (0 = the default plan), waves (0 = own
+ *         occupancy) and lanes of the remainder's launch (0 = one launch):
+ *         what he_crt_set_shape takes to set the same.
  * ms: optional host float[3]: their launch times.
  * HE_ERR_NOPRIV for a public key, HE_ERR_ARG for a zero count. */
 int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t dec_count, uint32_t *choice, float *ms,
@@ -270,10 +271,12 @@ int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t dec_count, u
  * exponentiation by n mod n^2 of public-key encryption, also the path of a
  * key holding n only) at this key's size, on the current device, for counts
  * of count's size class (bit length; for kind 3 of (count + 1) / 2): lanes
- * per integer (2, 4, 8 or 16 where built for the kind; 8 or 16 for kind 3 at
- * 2048-bit keys),
+ * per integer (1, 2, 4, 8 or 16; not 2 for kinds 1 and 2 at 2048-bit and kind 3
+ * at 1024-bit keys; 8 or 16 for kind 3 at 2048-bit keys),
  * waves per SIMD (0 = own occupancy, 2 or 3) and lanes of the last partial
- * round's launch (0 = one launch, else a built width above lanes).  A pin holds
+ * round's launch (0 = one launch, else a width as above and above lanes).  lanes
+ * 0, with waves and tail_lanes 0, takes a pin or a tuned shape back: the class
+ * follows the default plan again.  A pin holds
  * for every key of the size, constant-time or not.  Results
  * never depend on the shape.  HE_ERR_ARG for anything else. */
 int he_crt_set_shape(const he_key *key, uint32_t kind, uint64_t count, uint32_t lanes, uint32_t waves,

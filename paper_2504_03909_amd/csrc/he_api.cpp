@@ -197,11 +197,15 @@ struct PowShape {
 std::mutex g_pow_mu;
 std::map<std::tuple<int, int, int, int>, PowShape> g_pow_tuned;
 
-// The widths he_crt_set_shape and the remainder's launch are named by.
+// The widths that he_crt_set_shape takes and the autotuner tries and returns:
+// every built one but two lanes where the power's modulus has 64 32-bit limbs
+// (the lift and decryption at 2048 bits, public-key encryption at 1024).  A pin
+// holds for a whole class of counts, and there two lanes are the best only where
+// the count just fills a wave per SIMD with them (at 16,384 of 2048 bits 7.95
+// against two rounds at four lanes of 8.3 ms); the default plan takes them there.
 bool pow_shape_named(int KP, int kind, int G) {
   const int S32 = kind == 4 ? 16 * KP : (kind == 1 ? 64 * KP : 32 * KP);
-  return (G == 2 || G == 4 || G == 8 || G == 16) &&
-         (S32 == 16 || S32 == 32 || (S32 == 64 && G != 2) || (S32 == 128 && G >= 8));
+  return he::pow_shape_valid(KP, kind, G) && !(S32 == 64 && G == 2);
 }
 
 int count_class(uint64_t count) {
@@ -312,18 +316,29 @@ he::PowPlan default_pow_plan(int KP, int kind, uint64_t count) {
   return p;
 }
 
-// The launches of an exponentiation over `count` ciphertexts (units): the
-// tuned or pinned shape for its class if there is one (G 0: the autotuner found
-// none faster than the default plan), else default_pow_plan's.
-he::PowPlan pow_plan(int KP, int kind, uint64_t count) {
-  PowShape sh;
+// The tuned or pinned shape of an exponentiation over `count` ciphertexts
+// (units), G 0 (the default plan) if there is none.
+PowShape pow_shape_set(int KP, int kind, uint64_t count) {
   int dev = 0;
   (void)hipGetDevice(&dev);
-  {
-    std::lock_guard<std::mutex> lk(g_pow_mu);
-    auto it = g_pow_tuned.find({dev, KP, kind, count_class(count)});
-    if (it != g_pow_tuned.end()) sh = it->second;
-  }
+  std::lock_guard<std::mutex> lk(g_pow_mu);
+  auto it = g_pow_tuned.find({dev, KP, kind, count_class(count)});
+  return it != g_pow_tuned.end() ? it->second : PowShape{};
+}
+
+// The shape whose pin gives the plan that `count` has now: G 0 for a default plan
+// of two launches, or of a width no pin names.
+PowShape pow_pin(int KP, int kind, uint64_t count) {
+  const PowShape sh = pow_shape_set(KP, kind, count);
+  if (sh.G) return sh;
+  const he::PowPlan p = default_pow_plan(KP, kind, count);
+  return p.tail.G || !pow_shape_named(KP, kind, p.main.G) ? PowShape{} : PowShape{p.main.G, 0, 0};
+}
+
+// The launches of an exponentiation over `count` ciphertexts (units): those of
+// the shape set for its class, else default_pow_plan's.
+he::PowPlan pow_plan(int KP, int kind, uint64_t count) {
+  const PowShape sh = pow_shape_set(KP, kind, count);
   return sh.G ? pow_plan_at(KP, kind, count, sh) : default_pow_plan(KP, kind, count);
 }
 
@@ -1090,15 +1105,14 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
     // and nothing remembered (a sweep took 15 times three launches of up to 140 ms
     // each at 200,000 encryptions).
     if (t == 0 && !key->dk.ct) {
-      const he::PowPlan p = pow_plan(KP, kind, count);
-      rc = trial(PowShape{p.main.G, 0, p.tail.G}, p);
+      rc = trial(pow_pin(KP, kind, count), pow_plan(KP, kind, count));
       continue;
     }
     // lanes per integer and waves per SIMD in one launch, then, at the best
     // of those, a separate launch for the last partial round at each wider
     // group
     for (int G : {1, 2, 4, 8, 16}) {
-      if (!he::pow_shape_valid(KP, kind, G)) continue;
+      if (!pow_shape_named(KP, kind, G)) continue;
       for (int waves : {0, 3, 2}) {
         const PowShape sh{G, waves, 0};
         const he::PowPlan p = pow_plan_at(KP, kind, count, sh);
@@ -1107,10 +1121,11 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
       }
       if (rc) break;
     }
-    // the default plan, kept as such (its split follows the count)
+    // the default plan, kept as such (its split follows the count), unless it is
+    // one of the launches above
     const PowShape one = best[t];
     const he::PowPlan dp = default_pow_plan(KP, kind, count);
-    if (!rc) rc = trial(PowShape{}, dp);
+    if (!rc && (dp.tail.G || !pow_shape_named(KP, kind, dp.main.G))) rc = trial(PowShape{}, dp);
     for (int tg : {4, 8, 16}) {
       if (rc || tg <= one.G || !he::pow_shape_valid(KP, kind, tg)) continue;
       const PowShape sh{one.G, one.waves, tg};
@@ -1130,10 +1145,9 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
   }
   for (int t = 0; t < 3; ++t) {
     if (choice) {
-      const he::PowPlan dp = default_pow_plan(KP, kinds[t], t == 2 ? dec_count : enc_count);
-      choice[3 * t] = (uint32_t)(best[t].G ? best[t].G : dp.main.G);
+      choice[3 * t] = (uint32_t)best[t].G;
       choice[3 * t + 1] = (uint32_t)best[t].waves;
-      choice[3 * t + 2] = (uint32_t)(best[t].G ? best[t].tailG : dp.tail.G);
+      choice[3 * t + 2] = (uint32_t)best[t].tailG;
     }
     if (ms_out) ms_out[t] = best_ms[t];
   }
@@ -1149,8 +1163,10 @@ extern "C" int he_crt_set_shape(const he_key *key, uint32_t kind, uint64_t count
   const int KP = kp_of(key), k = kind == 0 ? 4 : (kind == 1 ? 0 : (kind == 2 ? 2 : 1));
   // public-key encryption plans its exponentiation over unit pairs of two ciphertexts
   const uint64_t units = kind == 3 ? (count + 1) / 2 : count;
-  if (!pow_shape_named(KP, k, (int)lanes))
-    return fail(HE_ERR_ARG, "lanes " + std::to_string(lanes) + " not built for this kind and key size");
+  if (lanes != 0 && !pow_shape_named(KP, k, (int)lanes))
+    return fail(HE_ERR_ARG, "lanes " + std::to_string(lanes) + " not a shape of this kind and key size");
+  if (lanes == 0 && (waves != 0 || tail_lanes != 0))
+    return fail(HE_ERR_ARG, "the default plan (lanes 0) has no waves or tail_lanes");
   if (waves != 0 && waves != 2 && waves != 3) return fail(HE_ERR_ARG, "waves must be 0 (own occupancy), 2 or 3");
   if (tail_lanes != 0 && (tail_lanes <= lanes || !pow_shape_named(KP, k, (int)tail_lanes)))
     return fail(HE_ERR_ARG, "tail_lanes must be 0 or a built width above lanes");

@@ -400,8 +400,8 @@ PowTune = collections.namedtuple("PowTune", "lanes waves tail_lanes ms")
 def crt_autotune(key: Key, enc_count: int, dec_count: int, stream=None):
     """Tunes the launch shapes of the private-key exponentiations for these
     counts (see he_crt_autotune); returns {kind: PowTune(lanes, waves,
-    tail_lanes, ms)} for "mod_p", "lift" and "decrypt" (tail_lanes 0: one
-    launch)."""
+    tail_lanes, ms)} for "mod_p", "lift" and "decrypt" (lanes 0: the default
+    plan; tail_lanes 0: one launch), which crt_set_shape takes as they are."""
     choice = (_u32 * 9)()
     ms = (ctypes.c_float * 3)()
     _check(_crt_autotune(key.handle, enc_count, dec_count, choice, ms, _stream(stream)))
@@ -414,8 +414,8 @@ POW_KINDS = {"mod_p": 0, "lift": 1, "decrypt": 2, "public": 3}
 
 def crt_set_shape(key: Key, kind: str, count: int, lanes: int, waves: int = 0, tail_lanes: int = 0) -> None:
     """Pins the launch shape of one exponentiation kind ("mod_p", "lift",
-    "decrypt" or "public") for counts of count's size class (see
-    he_crt_set_shape)."""
+    "decrypt" or "public") for counts of count's size class; lanes 0 takes a
+    pin or tuned shape back (see he_crt_set_shape)."""
     _check(_crt_set_shape(key.handle, POW_KINDS[kind], count, lanes, waves, tail_lanes))
 
 

@@ -109,3 +109,68 @@ out["same"] = encrypt(secret, 5000) == before
 """, bits=2048, p=primes[2048][0], q=primes[2048][1])
     assert 1 <= len(got["launches"]) <= 3, got["launches"]  # a warm-up and two timed runs
     assert got["same"] and got["choice"][0] > 0 and min(got["ms"]) > 0
+
+
+PINS = KEYS + r"""
+def pin(k, kind, count, lanes, waves, tail):
+    return lib.he_crt_set_shape(k, u32(kind), u64(count), u32(lanes), u32(waves), u32(tail))
+
+def clear(k, enc, dec):
+    for kind, count in ((0, enc), (1, enc), (2, dec)):
+        assert pin(k, kind, count, 0, 0, 0) == 0
+"""
+
+
+@pytest.mark.parametrize("bits", [1024, 2048])
+@pytest.mark.parametrize("enc,dec", [(5003, 3001), (200000, 16384), (33, 16390)])
+def test_what_the_tuner_returns_can_be_pinned(tmp_path, primes, bits, enc, dec):
+    """Whichever trial is the fastest: he_crt_set_shape takes what he_crt_autotune
+    returned, and the launches are then those the tuner remembered.  lanes 0 takes
+    both back."""
+    got = record(tmp_path, PINS + r"""
+enc, dec = env["enc"], env["dec"]
+out["bad"] = []
+for name, k in (("plain", plain), ("secret", secret)):
+    clear(k, enc, dec)
+    default = [encrypt(k, enc), decrypt(k, dec)]
+    rec.rec_fastest(-1)
+    tune(k, enc, dec)
+    trials = rec.rec_timed()
+    for fastest in range(trials):
+        rec.rec_fastest(fastest)
+        choice, _ = tune(k, enc, dec)
+        tuned = [encrypt(k, enc), decrypt(k, dec)]
+        clear(k, enc, dec)
+        if [encrypt(k, enc), decrypt(k, dec)] != default:
+            out["bad"].append([name, fastest, "lanes 0 is not the default plan"])
+        for i, count in enumerate((enc, enc, dec)):
+            if pin(k, i, count, *choice[3 * i:3 * i + 3]) != 0:
+                out["bad"].append([name, fastest, choice, lib.he_last_error().decode()])
+        if [encrypt(k, enc), decrypt(k, dec)] != tuned:
+            out["bad"].append([name, fastest, choice, "other launches"])
+    clear(k, enc, dec)
+    out[name] = trials
+""", bits=bits, p=primes[bits][0], q=primes[bits][1], enc=enc, dec=dec)
+    assert got["plain"] >= 9 and got["secret"] >= 13
+    assert not got["bad"], got["bad"][:5]
+
+
+@pytest.mark.parametrize("bits", [1024, 2048])
+def test_pins_taken_and_refused(tmp_path, primes, bits):
+    """One lane is a pin of every private-key kind; two lanes are none where the
+    modulus has 64 limbs; unbuilt widths, waves and tails are refused as ever."""
+    got = record(tmp_path, PINS + r"""
+out["ok"] = [[kind, lanes, tail] for kind in range(4) for lanes in range(0, 33) for tail in range(0, 33)
+             if pin(plain, kind, 777, lanes, 0, tail) == 0]
+out["waves"] = [w for w in range(9) if pin(plain, 0, 777, 4, w, 0) == 0]
+out["zero"] = [w for w in range(9) if pin(plain, 0, 777, 0, w, 0) == 0]
+out["count"] = pin(plain, 0, 0, 4, 0, 0)
+for kind in range(4):
+    assert pin(plain, kind, 777, 0, 0, 0) == 0
+""", bits=bits, p=primes[bits][0], q=primes[bits][1])
+    two = bits == 1024
+    widths = {0: [1, 2, 4, 8, 16], 1: [1, 2, 4, 8, 16] if two else [1, 4, 8, 16],
+              2: [1, 2, 4, 8, 16] if two else [1, 4, 8, 16], 3: [1, 4, 8, 16] if two else [8, 16]}
+    want = [[k, 0, 0] for k in widths] + [[k, g, t] for k, ws in widths.items() for g in ws for t in [0] + [x for x in ws if x > g]]
+    assert sorted(got["ok"]) == sorted(want)
+    assert got["waves"] == [0, 2, 3] and got["zero"] == [0] and got["count"] == -1
