@@ -272,14 +272,20 @@ struct PowCost {
   double first, more;
 };
 const std::vector<PowCost> &pow_costs(int KP, int kind) {
-  static const std::vector<PowCost> mod16 = {{1, .89, .73}, {2, .88, .55}, {4, .63, .34}, {8, .72, .32}, {16, 1.13, .35}};
-  static const std::vector<PowCost> mod32 = {{1, 5.8, 5.3}, {2, 3.75, 2.85}, {4, 2.37, 1.65}, {8, 2.26, 1.22}, {16, 2.4, 1.12}};
+  // Masked tables: every window reads 32 entries, which narrow groups, with more
+  // integers per wave, wait for longest (`first` between a few waves and one on
+  // every SIMD, e.g. 1.05 and 1.7 at four lanes mod a 512-bit prime).
+  static const std::vector<PowCost> mod16 = {{1, 2.5, 2.55}, {2, 2.0, 1.65}, {4, 1.15, .6}, {8, 1.2, .45}, {16, 1.53, .42}};
+  static const std::vector<PowCost> mod32 = {{1, 11, 10.4}, {2, 6.5, 7.7}, {4, 3.5, 2.7}, {8, 3.3, 1.8}, {16, 3.4, 1.5}};
+  static const std::vector<PowCost> mask16 = {{1, 5.2, 5.25}, {2, 2.7, 2.55}, {4, 1.9, 1.05}, {8, 1.6, .7}, {16, 1.34, .55}};
+  static const std::vector<PowCost> mask32 = {{1, 32, 23.5}, {2, 14, 12.7}, {4, 8.4, 6.1}, {8, 5, 3.35}, {16, 4.2, 2.3}};
   static const std::vector<PowCost> pair16 = {{1, 1.93, 1.72}, {2, 1.2, .98}, {4, .88, .55}, {8, .72, .41}, {16, .78, .38}};
   static const std::vector<PowCost> pair32 = {{1, 13.1, 12.1}, {2, 7.95, 7.1}, {4, 4.7, 3.6}, {8, 2.9, 2.1}, {16, 2.58, 1.53}};
   static const std::vector<PowCost> joint16 = {{1, 2.5, 2.2}, {2, 1.65, 1.35}, {4, 1.12, .74}, {8, .93, .54}, {16, .98, .46}};
   static const std::vector<PowCost> joint32 = {{1, 17.0, 15.4}, {2, 10.2, 9.2}, {4, 6.0, 4.75}, {8, 3.65, 2.75}, {16, 3.2, 1.95}};
   static const std::vector<PowCost> pair64 = {{8, 17.1, 13.7}, {16, 11.1, 8.0}};
   if (kind == 4) return KP == 1 ? mod16 : mod32;
+  if (kind == 0 || kind == 5) return KP == 1 ? mask16 : mask32;
   if (kind == 1) return KP == 1 ? pair32 : pair64;
   if (kind == 3) return KP == 1 ? joint16 : joint32;
   return KP == 1 ? pair16 : pair32;

@@ -82,8 +82,9 @@ def test_edge_r_at_a_pinned_width(he, pins, bits, lanes, secret, count):
 
 @pytest.mark.parametrize("secret", [False, True])
 def test_default_plans_of_two_launches(he, pins, secret):
-    """Counts just above a round of waves at two lanes and at one (2048 bits), with
-    no pin in their class: whole waves at a narrow width, the rest at a wide one."""
+    """A round of waves at two lanes (masked tables too), and counts just above one
+    at two lanes and at one (2048 bits), with no pin in their class: whole waves at a
+    narrow width, the rest at a wide one."""
     import torch
     bits = 2048
     p, q = P.keygen(bits, 2)
@@ -92,7 +93,7 @@ def test_default_plans_of_two_launches(he, pins, secret):
     k = he.Key.from_primes(bits, p, q)
     k.set_constant_time(secret)
     rng = np.random.default_rng(7)
-    for count in (16384 + 5, 32768 + 3):
+    for count in (16384, 16384 + 5, 32768 + 3):
         say(f"default plan, {count}, secret={secret}")
         for kind in KINDS:
             pins(k, kind, count, 0)

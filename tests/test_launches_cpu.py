@@ -174,3 +174,17 @@ for kind in range(4):
     want = [[k, 0, 0] for k in widths] + [[k, g, t] for k, ws in widths.items() for g in ws for t in [0] + [x for x in ws if x > g]]
     assert sorted(got["ok"]) == sorted(want)
     assert got["waves"] == [0, 2, 3] and got["zero"] == [0] and got["count"] == -1
+
+
+@pytest.mark.parametrize("bits", [1024, 2048])
+def test_masked_plans_follow_the_masked_kernels_times(tmp_path, primes, bits):
+    """At 40,000 values the masked lift and decryption take four lanes or more per
+    integer, where the sliding ones take one or two: at 1024 bits a decryption is
+    6.3 ms so and was 8.0 planned with the sliding kernels' times."""
+    got = record(tmp_path, KEYS + """
+out["secret"], out["plain"] = encrypt(secret, 40000) + decrypt(secret, 40000), decrypt(plain, 40000)
+""", bits=bits, p=primes[bits][0], q=primes[bits][1])
+    width = {k: [int(name.split("ELi")[1].split("E")[0]) for name, _, _ in v if "k_pow_pairI" in name and "ELi0E" not in name]
+             for k, v in got.items()}
+    assert len(width["secret"]) >= 2 and min(width["secret"]) >= 4, width
+    assert width["plain"][0] <= 2, width
