@@ -881,22 +881,6 @@ __global__ __launch_bounds__(256) void k_job_setup(JobPack pack, uint32_t n, DJo
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (uint64_t)gridDim.x * 256) zero[i] = 0;
 }
 
-__device__ __forceinline__ uint32_t find_job_by_blk(const DJob *jobs, uint32_t n_jobs, uint64_t blk) {
-  uint32_t j = 0;
-  while (j + 1 < n_jobs && jobs[j + 1].blk_off <= blk) ++j;
-  return j;
-}
-__device__ __forceinline__ uint32_t find_job_by_f(const DJob *jobs, uint32_t n_jobs, uint64_t f) {
-  uint32_t j = 0;
-  while (j + 1 < n_jobs && jobs[j + 1].f_off <= f) ++j;
-  return j;
-}
-__device__ __forceinline__ uint32_t find_job_by_fb(const DJob *jobs, uint32_t n_jobs, uint64_t e) {
-  uint32_t j = 0;
-  while (j + 1 < n_jobs && jobs[j + 1].fb_off <= e) ++j;
-  return j;
-}
-
 // Bin counts of one (job, feature, sample block) into counts[fb].  Samples
 // whose row is not resident or whose bin is out of range are skipped and
 // counted into the job's n_bad (bucket_sample).
@@ -904,7 +888,7 @@ __global__ __launch_bounds__(256) void k_hist_count(HistWs ws) {
   __shared__ uint32_t h[256];
   __shared__ uint32_t nbad;
   const uint64_t blk = blockIdx.x;
-  const uint32_t jn = find_job_by_blk(ws.jobs, ws.n_jobs, blk);
+  const uint32_t jn = find_job(ws.jobs, ws.n_jobs, &DJob::blk_off, blk);
   const DJob J = ws.jobs[jn];
   uint32_t f;
   uint64_t s0, s1;
@@ -941,7 +925,7 @@ __device__ __forceinline__ uint32_t item_class(uint32_t cnt, uint32_t nch) {
 __global__ __launch_bounds__(256) void k_hist_scan(HistWs ws) {
   __shared__ uint32_t sc[256], cn[256], last;
   const uint64_t jf = blockIdx.x;
-  const uint32_t jn = find_job_by_f(ws.jobs, ws.n_jobs, jf);
+  const uint32_t jn = find_job(ws.jobs, ws.n_jobs, &DJob::f_off, jf);
   const DJob J = ws.jobs[jn];
   const uint32_t f = (uint32_t)(jf - J.f_off);
   const uint64_t e = J.fb_off + (uint64_t)f * J.B + threadIdx.x;
@@ -1008,7 +992,7 @@ __global__ __launch_bounds__(256) void k_hist_scan(HistWs ws) {
 // next free items of its length's class.
 __device__ __forceinline__ void hist_items(const HistWs &ws, uint64_t jf) {
   __shared__ uint32_t at[256];
-  const DJob J = ws.jobs[find_job_by_f(ws.jobs, ws.n_jobs, jf)];
+  const DJob J = ws.jobs[find_job(ws.jobs, ws.n_jobs, &DJob::f_off, jf)];
   const uint32_t f = (uint32_t)(jf - J.f_off);
   const uint64_t e0 = J.fb_off + (uint64_t)f * J.B;
   if (threadIdx.x < J.B) {
@@ -1039,7 +1023,7 @@ __global__ __launch_bounds__(256) void k_hist_scatter(HistWs ws) {
   }
   __shared__ uint32_t h[256], base[256];
   const uint64_t blk = blockIdx.x - ws.total_f;
-  const uint32_t jn = find_job_by_blk(ws.jobs, ws.n_jobs, blk);
+  const uint32_t jn = find_job(ws.jobs, ws.n_jobs, &DJob::blk_off, blk);
   const DJob J = ws.jobs[jn];
   uint32_t f;
   uint64_t s0, s1;
@@ -1125,7 +1109,7 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_hist_final(DPair pc, HistW
     const uint64_t v = whole ? u : u - solo;
     const uint64_t jf = v % ws.total_f;
     const uint32_t r = whole ? (uint32_t)(v / ws.total_f) : kFinalSolo + kWaves * (uint32_t)(v / ws.total_f) + wv;
-    const DJob J = ws.jobs[find_job_by_f(ws.jobs, ws.n_jobs, jf)];
+    const DJob J = ws.jobs[find_job(ws.jobs, ws.n_jobs, &DJob::f_off, jf)];
     if (whole && r >= J.B) continue;  // block-uniform
     const uint64_t fb_f = (jf - J.f_off) * J.B;  // the feature's first entry within the job
     if (whole) {

@@ -2,6 +2,7 @@
 // ciphertexts, the products of the work items and the join of their partials.
 #pragma once
 #include "he_internal.hpp"
+#include "hist_bucket.hpp"
 #include "pair29.hpp"
 
 namespace he {
@@ -152,9 +153,7 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_hist_pairs(DPair pc, const
   if (!valid) r = count - 1;
   uint64_t row = r;
   if (ws.gather) {
-    uint32_t j = 0;
-    while (j + 1 < ws.n_jobs && ws.jobs[j + 1].s_off <= r) ++j;
-    const DJob J = ws.jobs[j];
+    const DJob J = ws.jobs[find_job(ws.jobs, ws.n_jobs, &DJob::s_off, r)];
     const uint32_t at = J.idx[r - J.s_off];
     valid = valid && at < ws.rows;
     row = at < ws.rows ? at : 0;
