@@ -205,7 +205,8 @@ typedef struct he_hist_job {
  * batching, chunking and order (exact modular products).  Work shape: the
  * one he_hist_autotune found for the batch's shape class, else items of 8 to
  * 256 samples in two runs, longer where the batch fills the device several
- * times over. */
+ * times over, and for a bin so full that joining its items would take longer
+ * than the items. */
 int he_hist_aggregate(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form,
                       const he_hist_job *jobs, uint32_t n_jobs, hipStream_t stream);
 

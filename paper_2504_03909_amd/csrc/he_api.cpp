@@ -731,7 +731,7 @@ struct HistLayout {
   uint32_t chunk = 64, runs = 1;
   int waves = 0;          // product kernel: waves per SIMD cap (0: none)
   uint64_t pairs = 0;     // ciphertext pairs converted: every row, or (gather) the jobs' samples
-  bool gather = false, mont = false;
+  bool gather = false, mont = false, stretch = false;
 };
 
 // Work shapes callers may name: 16 lanes per sample, or 8 at 2048-bit keys.
@@ -840,6 +840,7 @@ he::HistWs bind_layout(const HistLayout &lay, char *base) {
   ws.rows = lay.rows;
   ws.chunk = lay.chunk;
   ws.runs = lay.runs;
+  ws.stretch = lay.stretch ? 1u : 0u;
   ws.gather = lay.gather ? 1u : 0u;
   return ws;
 }
@@ -861,12 +862,13 @@ int enqueue_hist(const he_key *key, const uint32_t *ct, const HistLayout &lay, c
 
 int hist_run(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form, const he_hist_job *jobs,
              uint32_t n_jobs, uint32_t chunk, uint32_t split, hipStream_t stream, uint64_t *mm_count = nullptr,
-             int G = he::kHistGroup, int waves = 0) {
+             int G = he::kHistGroup, int waves = 0, bool stretch = false) {
   if (n_jobs == 0) return key ? HE_OK : fail(HE_ERR_ARG, "null key");
   HistLayout lay;
   int rc = plan_layout(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, G, lay);
   if (rc) return rc;
   lay.waves = waves;
+  lay.stretch = stretch;
   Workspace *w = workspace(stream);
   rc = ensure(w->hist, lay.bytes, stream);
   if (rc) return rc;
@@ -884,6 +886,7 @@ struct TuneVal {
   uint32_t chunk, split;
   float ms;
   int G = he::kHistGroup, waves = 0;
+  bool stretch = false;  // longer items for full bins: the default shape only
 };
 std::mutex g_tune_mu;
 std::map<TuneKey, TuneVal> g_tune;
@@ -917,13 +920,16 @@ TuneKey tune_key(const he_key *key, const he_hist_job *jobs, uint32_t n_jobs) {
 // 2048 bits (ms at half, this and twice the length): W = 8,000 0.20 / 0.20 /
 // 0.24; 36,000 0.33 / 0.29 / 0.39; 168,000 0.73 / 0.62 / 0.74; 480,000 1.32 /
 // 1.13 / 1.14; 3,200,000 6.35 / 6.18 / 6.31; 14.7 M 46.2 / 45.4 / -.
+// The bins' counts are known on the device only: there a full bin's items are
+// longer (item_chunk).  100,000 samples of one feature at 2048 bits, all in one
+// bin 5.33 -> 1.88 ms, in two 2.92 -> 1.36; 32 features x 256 Zipf bins as before.
 TuneVal default_hist_shape(const he_hist_job *jobs, uint32_t n_jobs) {
   uint64_t w = 0;
   for (uint32_t j = 0; j < n_jobs; ++j) w += (uint64_t)jobs[j].n_features * jobs[j].n_samples;
   const uint32_t lo = w < 16000 ? 4 : 8, hi = w < 6000000 ? 64 : 128;
   uint32_t len = lo;
   while (len < hi && (uint64_t)len * 2 * 20000 <= w) len *= 2;
-  return TuneVal{2 * len, 2, 0.f, 8, 0};
+  return TuneVal{2 * len, 2, 0.f, 8, 0, true};
 }
 
 }  // namespace
@@ -933,6 +939,7 @@ extern "C" int he_hist_aggregate_ex(const he_key *key, const uint32_t *ct, uint6
                                     hipStream_t stream) {
   uint32_t split = 2;
   int G = he::kHistGroup, waves = 0;
+  bool stretch = false;
   if (chunk == 0 && key && jobs && n_jobs) {
     TuneVal v = default_hist_shape(jobs, n_jobs);
     {
@@ -944,8 +951,9 @@ extern "C" int he_hist_aggregate_ex(const he_key *key, const uint32_t *ct, uint6
     split = v.split;
     G = v.G;
     waves = v.waves;
+    stretch = v.stretch;
   }
-  return hist_run(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, stream, nullptr, G, waves);
+  return hist_run(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, stream, nullptr, G, waves, stretch);
 }
 
 extern "C" int he_hist_aggregate_counted(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form,
@@ -1210,6 +1218,7 @@ extern "C" int he_hist_plan_create(const he_key *key, const uint32_t *ct, uint64
   if (!out) return fail(HE_ERR_ARG, "null out");
   if (!key || !jobs || n_jobs == 0) return fail(HE_ERR_ARG, "need a key and at least one job");
   int G = he::kHistGroup, waves = 0;
+  bool stretch = false;
   if (chunk == 0) {
     TuneVal v = default_hist_shape(jobs, n_jobs);
     {
@@ -1221,6 +1230,7 @@ extern "C" int he_hist_plan_create(const he_key *key, const uint32_t *ct, uint64
     if (split == 0) split = v.split;
     G = v.G;
     waves = v.waves;
+    stretch = v.stretch;
   }
   if (split == 0) split = 2;
   he_hist_plan *p = new (std::nothrow) he_hist_plan();
@@ -1232,6 +1242,7 @@ extern "C" int he_hist_plan_create(const he_key *key, const uint32_t *ct, uint64
     return rc;
   }
   p->lay.waves = waves;
+  p->lay.stretch = stretch;
   if (hipMalloc(&p->ws, std::max<size_t>(p->lay.bytes, 256)) != hipSuccess) {
     hipGetLastError();
     delete p;

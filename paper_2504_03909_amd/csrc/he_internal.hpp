@@ -130,6 +130,7 @@ struct HistWs {
   uint64_t total_fb, total_f, total_blocks, items_cap;
   uint64_t rows;                                   // resident ciphertext rows
   uint32_t chunk;                                  // most samples per item
+  uint32_t stretch;                                // longer items for full bins (item_chunk)
   uint32_t runs;                                   // groups per (item, slot): 1, 2 or 4
   uint32_t gather;                                 // pairs holds the jobs' samples, not every row
   unsigned long long *mm_count;                    // optional debug counters [3], else null

@@ -931,7 +931,6 @@ __global__ __launch_bounds__(256) void k_hist_scan(HistWs ws) {
   const uint64_t e = J.fb_off + (uint64_t)f * J.B + threadIdx.x;
   const uint32_t t = threadIdx.x;
   const uint32_t cnt = t < J.B ? ws.counts[e] : 0u;
-  const uint32_t nch = (cnt + ws.chunk - 1) / ws.chunk;
   cn[t] = cnt;
   sc[t] = cnt;
   __syncthreads();
@@ -941,6 +940,8 @@ __global__ __launch_bounds__(256) void k_hist_scan(HistWs ws) {
       const uint32_t c = cn[b];
       rank += (c > cnt || (c == cnt && b < t)) ? 1u : 0u;
     }
+  const uint32_t chunk = ws.stretch ? item_chunk(cnt, rank, ws.chunk) : ws.chunk;
+  const uint32_t nch = (cnt + chunk - 1) / chunk;
   for (uint32_t d = 1; d < 256; d <<= 1) {  // inclusive Hillis-Steele scan
     const uint32_t a = t >= d ? sc[t - d] : 0u;
     __syncthreads();
@@ -1050,10 +1051,6 @@ __global__ __launch_bounds__(256) void k_hist_scatter(HistWs ws) {
   for (int k = 0; k < kPer; ++k)
     if (ok[k]) pf[bucket_slot(base[bn[k]], rk[k])] = rows[k];
 }
-
-// Ranks (within a feature, by decreasing bin count) that k_hist_final takes
-// one per block; higher ranks go one per wave, four to a block.
-constexpr uint32_t kFinalSolo = 8;
 
 // Final product over the chunks of one (job, feature, bin), conversion out of
 // Montgomery form, and the store into the job's histogram.  A block takes

@@ -57,6 +57,24 @@ HE_HD inline void bucket_block(uint64_t local, uint32_t nblk, uint64_t n, uint32
   s1 = s0 + block < n ? s0 + block : n;
 }
 
+// Ranks (within a feature, by decreasing bin count) that k_hist_final takes one
+// per block, their partials in up to eight runs; higher ranks go one per wave, in
+// two runs.
+constexpr uint32_t kFinalSolo = 8;
+
+// Most samples per item of a feature's bin of `cnt` samples, the rank-th fullest,
+// in an untuned batch of items of up to `chunk`: longer items where the bin's
+// partials would otherwise chain for longer than its items do.  With c samples per
+// item these are c / 2 products in k_hist_chunk (two runs) and cnt / (8 c) or
+// cnt / (2 c) in k_hist_final, which take half the time each, so 2 c beats c from cnt =
+// 16 c^2 or 4 c^2 on.
+HE_HD inline uint32_t item_chunk(uint32_t cnt, uint32_t rank, uint32_t chunk) {
+  const uint64_t k = rank < kFinalSolo ? 16 : 4;
+  uint64_t c = chunk;
+  while (k * c * c < cnt) c *= 2;
+  return (uint32_t)c;
+}
+
 // Slot of a sample in the feature's permutation row: the start of its bin's
 // run reserved by its block (`block_base`, taken from the bin's cursor, which
 // starts at the bin's offset) plus its rank among the block's samples of
