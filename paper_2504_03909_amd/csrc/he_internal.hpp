@@ -176,6 +176,7 @@ hipError_t launch_enc_crt(int KP, const DKey &k, const int64_t *m, uint64_t coun
 // unit pairs (kind 1).
 hipError_t launch_enc_pub(int KP, const DKey &k, const int64_t *m, uint64_t count, const uint32_t *r, uint64_t seed,
                           uint64_t roff, uint32_t *x, uint32_t *ct, uint32_t *tab, const PowPlan &p, hipStream_t s);
+// m null: 2^63 for every ciphertext.
 hipError_t launch_enc_obf(int KP, const DKey &k, const int64_t *m, uint64_t count, const uint32_t *rho,
                           uint32_t *ct, hipStream_t s);
 uint32_t ct_div_batch(uint64_t count);

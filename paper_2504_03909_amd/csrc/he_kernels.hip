@@ -333,7 +333,8 @@ __global__ __launch_bounds__(kBlockThreads) void k_pub_post(DKey key, const int6
 // rho = r^n mod n^2 (canonical).  Since (1 + m n) rho = rho + n (m rho) and
 // n x mod n^2 = n (x mod n), ct = rho + n t mod n^2 with t = m rho mod n:
 // three products mod n (rho R mod n from rho's halves, then times m) and
-// one mod n^2 (n t), instead of three mod n^2.
+// one mod n^2 (n t), instead of three mod n^2.  Without m: m = 2^63, the offset of
+// a packed slot, for packing one ciphertext to one.
 template <int KP>
 __global__ __launch_bounds__(kBlockThreads) void k_enc_obf(DKey key, const int64_t *__restrict__ m,
                                                           uint64_t count, const uint32_t *rho,
@@ -358,7 +359,12 @@ __global__ __launch_bounds__(kBlockThreads) void k_enc_obf(DKey key, const int64
     ld<KN>(c, key.n.R3);
     mont_mul<KN>(b, b, c, Mn, lds);
     add_mod<KN>(a, a, b, Mn);
-    signed_mod<KN>(b, m[i], Mn.n);
+    if (m) {
+      signed_mod<KN>(b, m[i], Mn.n);
+    } else {
+#pragma unroll
+      for (int j = 0; j < KN; ++j) b[j] = (int)glane() * KN + j == 1 ? 0x80000000u : 0u;
+    }
     mont_mul<KN>(a, a, b, Mn, lds);
     relayout<KN, KN2>(t2, a, lds);
   }
@@ -634,7 +640,9 @@ __global__ __launch_bounds__(kBlockThreads) void k_ct_mul(DKey key, const uint32
 // run over `slots` and its missing slots multiply by one.  The slot count
 // leaves one wave per SIMD (pack_slots), so a squaring's latency, 72 steps of
 // 27 multiply-adds, bounds it: 32,768 ciphertexts at 8 slots 3.5 -> 2.5 ms
-// against squarings of one 144-limb integer.
+// against squarings of one 144-limb integer.  One slot needs no squaring, and the
+// way into and out of the two digits would be most of its time (30,000 ciphertexts
+// 0.35 ms): k_enc_obf multiplies by 1 + K n mod n instead (0.16 ms).
 template <int KP>
 __global__ __launch_bounds__(kBlockThreads, 2) void k_pack(DKey key, const uint32_t *__restrict__ ct, uint64_t count,
                                                           uint32_t slots, uint32_t *__restrict__ packed) {
@@ -1435,6 +1443,7 @@ hipError_t launch_ct_mul(int KP, const DKey &k, const uint32_t *a, const uint32_
 hipError_t launch_pack(int KP, const DKey &k, const uint32_t *ct, uint64_t count, uint32_t slots,
                        uint32_t *packed, hipStream_t s) {
   if (!count) return hipSuccess;
+  if (slots == 1) return launch_enc_obf(KP, k, nullptr, count, ct, packed, s);
   const dim3 grid(blocks_for((count + slots - 1) / slots, 16));
   if (KP == 1)
     hipLaunchKernelGGL(k_pack<1>, grid, dim3(kBlockThreads), 0, s, k, ct, count, slots, packed);

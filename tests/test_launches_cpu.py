@@ -188,3 +188,16 @@ out["secret"], out["plain"] = encrypt(secret, 40000) + decrypt(secret, 40000), d
              for k, v in got.items()}
     assert len(width["secret"]) >= 2 and min(width["secret"]) >= 4, width
     assert width["plain"][0] <= 2, width
+
+
+def test_packing_one_slot_does_not_enter_the_squarings(tmp_path, primes):
+    """One slot is one product by a constant: the kernel built for 64 squarings a
+    slot took 1.7 times the former's time at it."""
+    got = record(tmp_path, KEYS + r"""
+for slots in (1, 2, 31):
+    rec.rec_reset()
+    assert lib.he_pack(plain, A, u64(1000), u32(slots), B, None) == 0
+    out[slots] = [l[0] for l in launches()]
+""", bits=2048, p=primes[2048][0], q=primes[2048][1])
+    assert len(got["1"]) == 1 and "k_enc_obf" in got["1"][0]
+    assert all(len(got[s]) == 1 and "k_pack" in got[s][0] for s in ("2", "31"))
