@@ -307,7 +307,13 @@ int he_hist_aggregate_counted(const he_key *key, const uint32_t *ct, uint64_t ro
  * job descriptors and `ct` point to at replay time, so the caller refreshes
  * their contents in place; the sizes are fixed at creation.  chunk/split 0
  * take the autotuned or default values.  Replays of one plan must not
- * overlap (one plan per concurrent stream). */
+ * overlap (one plan per concurrent stream).
+ * The plan's workspace holds, beside the partial products, the ciphertexts in the
+ * kernels' own form, for either ct_form: 1,152 bytes (2048-bit keys; 640 at 1024)
+ * per resident row, or per sample where the jobs together have fewer samples than
+ * rows.  Where that cannot be allocated, plans (and he_hist_aggregate) do without
+ * it: the products then read `ct` and convert each sample anew, at 1.4 (Montgomery
+ * form) to 2.2 times the work. */
 typedef struct he_hist_plan he_hist_plan;
 int he_hist_plan_create(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form,
                         const he_hist_job *jobs, uint32_t n_jobs, uint32_t chunk, uint32_t split,

@@ -732,6 +732,7 @@ struct HistLayout {
   int waves = 0;          // product kernel: waves per SIMD cap (0: none)
   uint64_t pairs = 0;     // ciphertext pairs converted: every row, or (gather) the jobs' samples
   bool gather = false, mont = false, stretch = false;
+  bool direct = false;    // no pairs: the products read the resident ciphertexts
 };
 
 // Work shapes callers may name: 16 lanes per sample, or 8 at 2048-bit keys.
@@ -741,7 +742,7 @@ bool hist_shape_valid(int KP, int lanes) { return lanes == 16 || (lanes == 8 && 
 uint32_t hist_runs(uint32_t split, int lanes) { return split * (lanes == 8 ? 1u : 2u); }
 
 int plan_layout(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form, const he_hist_job *jobs,
-                uint32_t n_jobs, uint32_t chunk, uint32_t split, int lanes, HistLayout &lay) {
+                uint32_t n_jobs, uint32_t chunk, uint32_t split, int lanes, HistLayout &lay, bool direct = false) {
   if (!key) return fail(HE_ERR_ARG, "null key");
   if (!jobs) return fail(HE_ERR_ARG, "null jobs");
   if (ct_form != HE_FORM_CANONICAL && ct_form != HE_FORM_MONT) return fail(HE_ERR_ARG, "bad ct_form");
@@ -749,6 +750,7 @@ int plan_layout(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_for
   if (chunk > (1u << 20)) return fail(HE_ERR_ARG, "chunk too large");
   if (split != 1 && split != 2) return fail(HE_ERR_ARG, "split must be 1 or 2");
   const size_t S = 2 * (key->n_bits / 32);
+  lay = HistLayout{};
   lay.dj.assign(n_jobs, he::DJob{});
   lay.rows = rows;
   lay.chunk = chunk;
@@ -808,14 +810,17 @@ int plan_layout(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_for
   // resident row, or where the jobs hold fewer samples those one by one
   const uint64_t row = 2 * (uint64_t)he29::limbs_for_group((int)S, he::kHistGroup) * 4;
   lay.o_part = take(std::max<uint64_t>(lay.items_cap, 1) * row);
-  lay.gather = samples < rows;
-  lay.pairs = lay.gather ? samples : rows;
-  lay.o_pairs = take(std::max<uint64_t>(lay.pairs, 1) * row);
+  lay.direct = direct;
+  if (!direct) {
+    lay.gather = samples < rows;
+    lay.pairs = lay.gather ? samples : rows;
+    lay.o_pairs = take(std::max<uint64_t>(lay.pairs, 1) * row);
+  }
   lay.bytes = off;
   return HE_OK;
 }
 
-he::HistWs bind_layout(const HistLayout &lay, char *base) {
+he::HistWs bind_layout(const HistLayout &lay, const uint32_t *ct, char *base) {
   he::HistWs ws{};
   ws.jobs = (he::DJob *)(base + lay.o_jobs);
   ws.n_jobs = (uint32_t)lay.dj.size();
@@ -832,7 +837,9 @@ he::HistWs bind_layout(const HistLayout &lay, char *base) {
   ws.items = (he::HistItem *)(base + lay.o_items);
   ws.perm = (uint32_t *)(base + lay.o_perm);
   ws.partials = (uint32_t *)(base + lay.o_part);
-  ws.pairs = (uint32_t *)(base + lay.o_pairs);
+  ws.pairs = lay.direct ? nullptr : (uint32_t *)(base + lay.o_pairs);
+  ws.ct = ct;
+  ws.mont = lay.mont ? 1u : 0u;
   ws.total_fb = lay.total_fb;
   ws.total_f = lay.total_f;
   ws.total_blocks = lay.total_blocks;
@@ -849,14 +856,15 @@ he::HistWs bind_layout(const HistLayout &lay, char *base) {
 // memset: safe to capture into a graph).
 int enqueue_hist(const he_key *key, const uint32_t *ct, const HistLayout &lay, char *base, hipStream_t stream,
                  uint64_t *mm_count = nullptr) {
-  he::HistWs ws = bind_layout(lay, base);
+  he::HistWs ws = bind_layout(lay, ct, base);
   ws.mm_count = (unsigned long long *)mm_count;
   const int KP = kp_of(key);
-  he::HistLaunch hl{0, he::hist_dyn_lds(KP, lay.waves)};
+  he::HistLaunch hl{0, he::hist_dyn_lds(KP, lay.direct, lay.waves)};
   // a wave takes 8 / runs items at a time
   const uint64_t waves = (lay.items_cap * lay.runs + 7) / 8;
-  hl.grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(he::hist_resident_blocks(KP, hl.dyn), (waves + 3) / 4));
-  HE_TRY_HIP(he::launch_hist(KP, key->dk, ct, lay.mont, lay.pairs, lay.dj.data(), ws, hl, stream));
+  hl.grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(he::hist_resident_blocks(KP, lay.direct, hl.dyn),
+                                                                     (waves + 3) / 4));
+  HE_TRY_HIP(he::launch_hist(KP, key->dk, lay.pairs, lay.dj.data(), ws, hl, stream));
   return HE_OK;
 }
 
@@ -867,11 +875,16 @@ int hist_run(const he_key *key, const uint32_t *ct, uint64_t rows, int ct_form, 
   HistLayout lay;
   int rc = plan_layout(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, G, lay);
   if (rc) return rc;
-  lay.waves = waves;
-  lay.stretch = stretch;
   Workspace *w = workspace(stream);
   rc = ensure(w->hist, lay.bytes, stream);
+  if (rc == HE_ERR_OOM && lay.pairs) {
+    // no memory for the ciphertexts in two digits beside the caller's
+    rc = plan_layout(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, G, lay, true);
+    if (!rc) rc = ensure(w->hist, lay.bytes, stream);
+  }
   if (rc) return rc;
+  lay.waves = waves;
+  lay.stretch = stretch;
   return enqueue_hist(key, ct, lay, (char *)w->hist.p, stream, mm_count);
 }
 
@@ -1016,7 +1029,7 @@ extern "C" int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t 
     if (rc || !hist_shape_valid(KP, G)) continue;
     const TuneVal bg = best_g[G == he::kHistGroup ? 0 : 1];
     for (int waves : {4, 3, 2}) {
-      if (he::hist_dyn_lds(KP, waves) == 0) continue;  // no cap needed: same as its own occupancy
+      if (he::hist_dyn_lds(KP, false, waves) == 0) continue;  // no cap needed: same as its own occupancy
       if ((rc = trial(bg.chunk, bg.split, G, waves))) break;
     }
   }
@@ -1241,17 +1254,24 @@ extern "C" int he_hist_plan_create(const he_key *key, const uint32_t *ct, uint64
     delete p;
     return rc;
   }
-  p->lay.waves = waves;
-  p->lay.stretch = stretch;
   if (hipMalloc(&p->ws, std::max<size_t>(p->lay.bytes, 256)) != hipSuccess) {
     hipGetLastError();
-    delete p;
-    return fail(HE_ERR_OOM, "plan workspace allocation of " + std::to_string(p->lay.bytes) + " bytes failed");
+    p->ws = nullptr;
+    // no memory for the ciphertexts in two digits beside the caller's
+    if (p->lay.pairs) rc = plan_layout(key, ct, rows, ct_form, jobs, n_jobs, chunk, split, G, p->lay, true);
+    if (rc || !p->lay.direct || hipMalloc(&p->ws, std::max<size_t>(p->lay.bytes, 256)) != hipSuccess) {
+      hipGetLastError();
+      const size_t bytes = p->lay.bytes;
+      delete p;
+      return rc ? rc : fail(HE_ERR_OOM, "plan workspace allocation of " + std::to_string(bytes) + " bytes failed");
+    }
   }
+  p->lay.waves = waves;
+  p->lay.stretch = stretch;
   // resident block counts and LDS caps are queried before capture
   // (occupancy calls are not stream work, but keep capture free of anything
   // but launches)
-  (void)he::hist_resident_blocks(kp_of(key), he::hist_dyn_lds(kp_of(key), waves));
+  (void)he::hist_resident_blocks(kp_of(key), p->lay.direct, he::hist_dyn_lds(kp_of(key), p->lay.direct, waves));
   hipStream_t cs;
   if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) {
     he_hist_plan_free(p);

@@ -125,7 +125,10 @@ struct HistWs {
   uint32_t *next;                                  // device scalar: the product kernel's next wave unit
   HistItem *items;                                 // [items_cap]
   uint32_t *perm;                                  // [total_perm]: index into pairs
-  uint32_t *pairs;                                 // [rows or samples][2][2 S29]: the ciphertexts in two digits
+  uint32_t *pairs;                                 // [rows or samples][2][2 S29]: the ciphertexts in two digits,
+                                                   // null: read from ct (mont: HE_FORM_MONT)
+  const uint32_t *ct;
+  uint32_t mont;
   uint32_t *partials;                              // [items_cap][2][2 S29]
   uint64_t total_fb, total_f, total_blocks, items_cap;
   uint64_t rows;                                   // resident ciphertext rows
@@ -211,12 +214,12 @@ struct HistLaunch {
   uint32_t grid;
   uint32_t dyn;
 };
-uint32_t hist_resident_blocks(int KP, uint32_t dyn);
-uint32_t hist_dyn_lds(int KP, int waves);
-// ct: the resident ciphertexts (mont: HE_FORM_MONT); pairs: how many of them
-// (or of the jobs' samples) ws.pairs holds.
-hipError_t launch_hist(int KP, const DKey &k, const uint32_t *ct, bool mont, uint64_t pairs, const DJob *host_jobs,
-                       const HistWs &ws, const HistLaunch &l, hipStream_t s);
+uint32_t hist_resident_blocks(int KP, bool direct, uint32_t dyn);
+uint32_t hist_dyn_lds(int KP, bool direct, int waves);
+// pairs: how many of the resident ciphertext pairs (or of the jobs' samples)
+// ws.pairs holds.
+hipError_t launch_hist(int KP, const DKey &k, uint64_t pairs, const DJob *host_jobs, const HistWs &ws,
+                       const HistLaunch &l, hipStream_t s);
 hipError_t launch_fill(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_probe_mul(uint64_t iters, uint32_t grid, uint32_t *sink, hipStream_t s);
 

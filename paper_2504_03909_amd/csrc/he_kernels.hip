@@ -1512,8 +1512,8 @@ hipError_t launch_fill(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s) {
 }
 
 template <int KP>
-static hipError_t hist(const DKey &k, const uint32_t *ct, bool mont, uint64_t pairs, const DJob *host_jobs,
-                       const HistWs &ws, const HistLaunch &l, hipStream_t s) {
+static hipError_t hist(const DKey &k, uint64_t pairs, const DJob *host_jobs, const HistWs &ws, const HistLaunch &l,
+                       hipStream_t s) {
   constexpr int G = kHistLanes;
   for (uint32_t j0 = 0; j0 < ws.n_jobs; j0 += kJobsPerSetup) {
     JobPack pack;
@@ -1528,18 +1528,22 @@ static hipError_t hist(const DKey &k, const uint32_t *ct, bool mont, uint64_t pa
   hipLaunchKernelGGL(k_hist_scan, dim3((uint32_t)ws.total_f), dim3(256), 0, s, ws);
   hipLaunchKernelGGL(k_hist_scatter, dim3((uint32_t)(ws.total_f + ws.total_blocks)), dim3(256), 0, s, ws);
   if (ws.total_blocks) {
-    hipLaunchKernelGGL((k_hist_pairs<KP, G>), dim3(blocks_for(pairs, kBlockThreads / (2 * G))), dim3(kBlockThreads), 0,
-                       s, k.pair_n, ct, (int)mont, ws, pairs);
-    hipLaunchKernelGGL((k_hist_chunk<KP, G>), dim3(l.grid), dim3(kBlockThreads), l.dyn, s, k.pair_n, ws);
+    if (ws.pairs) {
+      hipLaunchKernelGGL((k_hist_pairs<KP, G>), dim3(blocks_for(pairs, kBlockThreads / (2 * G))), dim3(kBlockThreads),
+                         0, s, k.pair_n, ws.ct, (int)ws.mont, ws, pairs);
+      hipLaunchKernelGGL((k_hist_chunk<KP, G, false>), dim3(l.grid), dim3(kBlockThreads), l.dyn, s, k.pair_n, ws);
+    } else {
+      hipLaunchKernelGGL((k_hist_chunk<KP, G, true>), dim3(l.grid), dim3(kBlockThreads), l.dyn, s, k.pair_n, ws);
+    }
   }
   const uint64_t final_units = ws.total_f * (kFinalSolo + (256 - kFinalSolo) / 4);
   const uint32_t fgrid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(final_units, 1u << 20));
   hipLaunchKernelGGL(k_hist_final<KP>, dim3(fgrid), dim3(kBlockThreads), 0, s, k.pair_n, ws);
   return hipGetLastError();
 }
-hipError_t launch_hist(int KP, const DKey &k, const uint32_t *ct, bool mont, uint64_t pairs, const DJob *host_jobs,
-                       const HistWs &ws, const HistLaunch &l, hipStream_t s) {
-  return KP == 1 ? hist<1>(k, ct, mont, pairs, host_jobs, ws, l, s) : hist<2>(k, ct, mont, pairs, host_jobs, ws, l, s);
+hipError_t launch_hist(int KP, const DKey &k, uint64_t pairs, const DJob *host_jobs, const HistWs &ws,
+                       const HistLaunch &l, hipStream_t s) {
+  return KP == 1 ? hist<1>(k, pairs, host_jobs, ws, l, s) : hist<2>(k, pairs, host_jobs, ws, l, s);
 }
 
 hipError_t launch_probe_mul(uint64_t iters, uint32_t grid, uint32_t *sink, hipStream_t s) {
@@ -1604,25 +1608,29 @@ uint32_t pow_dyn_lds(int KP, int kind, int G, int waves) {
                      (int)(pow_resident_blocks(KP, kind, G, 0) / (uint32_t)device_cus()), waves);
 }
 
-static const void *hist_kernel(int KP) {
-  return KP == 1 ? (const void *)k_hist_chunk<1, kHistLanes> : (const void *)k_hist_chunk<2, kHistLanes>;
+template <int KP>
+static const void *hist_kernel(bool direct) {
+  return direct ? (const void *)k_hist_chunk<KP, kHistLanes, true> : (const void *)k_hist_chunk<KP, kHistLanes, false>;
 }
-uint32_t hist_resident_blocks(int KP, uint32_t dyn) {
+static const void *hist_kernel(int KP, bool direct) { return KP == 1 ? hist_kernel<1>(direct) : hist_kernel<2>(direct); }
+uint32_t hist_resident_blocks(int KP, bool direct, uint32_t dyn) {
   static std::mutex mu;
-  static std::map<std::pair<int, uint32_t>, uint32_t> cache;
+  static std::map<std::tuple<int, bool, uint32_t>, uint32_t> cache;
   std::lock_guard<std::mutex> lk(mu);
-  auto it = cache.find({KP, dyn});
+  auto it = cache.find({KP, direct, dyn});
   if (it != cache.end()) return it->second;
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, hist_kernel(KP), kBlockThreads, dyn) != hipSuccess || nb < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, hist_kernel(KP, direct), kBlockThreads, dyn) != hipSuccess ||
+      nb < 1)
     nb = 1;
   const uint32_t r = (uint32_t)(nb * device_cus());
-  cache[{KP, dyn}] = r;
+  cache[{KP, direct, dyn}] = r;
   return r;
 }
-uint32_t hist_dyn_lds(int KP, int waves) {
+uint32_t hist_dyn_lds(int KP, bool direct, int waves) {
   return waves <= 0 ? 0
-                    : cap_dyn_lds(hist_kernel(KP), (int)(hist_resident_blocks(KP, 0) / (uint32_t)device_cus()), waves);
+                    : cap_dyn_lds(hist_kernel(KP, direct),
+                                  (int)(hist_resident_blocks(KP, direct, 0) / (uint32_t)device_cus()), waves);
 }
 
 uint64_t table_bytes_per_block(int KP, int kind, int G) {

@@ -129,21 +129,79 @@ struct SeqPair {
 #pragma unroll
     for (int j = 0; j < K; ++j) a[j] = a1[j];
   }
+  // The pair (a, b) of x R from the ciphertext x (2 SN words): from the Montgomery
+  // form X = x R^2 by two reductions alone: X + m n = R a', so X R^-1 = a' - (m
+  // R^-1) n.  From x itself by the products of its two halves with the constants'
+  // (c0) first two pieces.
+  __device__ __forceinline__ void enter(uint32_t (&a)[K], uint32_t (&b)[K], const uint32_t *x, bool mont,
+                                        const uint32_t *c0) {
+    constexpr int K32 = SN / G;
+    uint32_t lo[K], hi[K];
+    uint64_t C[K];
+    if (mont) {
+      // X's 2 S limbs: the low half is the reduction's input, the high half its addend
+      uint32_t w[2 * K32];
+      ld<2 * K32, G>(w, x);
+      st<2 * K32, G>(lds, w);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+          const uint32_t bit = he29::kBits * (h * S + glane<G>() * K + j), i = bit >> 5;
+          const uint32_t l = i < 2 * SN ? lds[i] : 0u, u = i + 1 < 2 * SN ? lds[i + 1] : 0u;
+          const uint32_t t = __builtin_amdgcn_alignbit(u, l, bit & 31u) & kMask29;
+          if (h) hi[j] = t;
+          else lo[j] = t;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int j = 0; j < K; ++j) C[j] = lo[j];
+      pass<0, true>(C, nullptr, lo, nullptr, lo);
+#pragma unroll
+      for (int j = 0; j < K; ++j) C[j] += hi[j];
+      settle(a, C);
+      start_second(C);
+      pass<0, false>(C, nullptr, lo, nullptr, lo);
+      end_second(C);
+      settle(b, C);
+    } else {
+      const uint32_t *c1 = c0 + 2 * S;
+      uint32_t w[K32];
+      ld<K32, G>(w, x);
+      to29<K32, K, G>(lo, w, lds);
+      ld<K32, G>(w, x + SN);
+      to29<K32, K, G>(hi, w, lds);
+      st29<K, G>(lds, lo);
+      st29<K, G>(lds + S, hi);
+      __builtin_amdgcn_wave_barrier();
+      ld29<K, G>(lo, c0);
+      ld29<K, G>(hi, c1);
+#pragma unroll
+      for (int j = 0; j < K; ++j) C[j] = 0;
+      pass<2, true>(C, lds, lo, lds + S, hi);
+      settle(a, C);
+      ld29<K, G>(lo, c0 + S);
+      ld29<K, G>(hi, c1 + S);
+      start_second(C);
+      pass<2, false>(C, lds, lo, lds + S, hi);
+      end_second(C);
+      settle(b, C);
+    }
+  }
 };
 
 // ---- ciphertexts -> pairs ------------------------------------------------------
 // Pair of x R per ciphertext x: 2 S words (first digit, then the second times
-// 2^29).  From the Montgomery form X = x R^2 by two reductions alone: X + m n =
-// R a', so X R^-1 = a' - (m R^-1) n.  From x itself by the products of its two
-// halves with the constants' first two pieces.  `rows` ciphertext pairs: all
-// resident rows in order, or (gather) the samples of every job one after the
-// other; a job's sample whose row is not resident is left out.  4 lanes per
-// ciphertext; two reductions are 0.4 of one histogram product, six limb
-// products 1.2 of one.
+// 2^29).  `rows` ciphertext pairs: all resident rows in order, or (gather) the
+// samples of every job one after the other; a job's sample whose row is not
+// resident is left out.  4 lanes per ciphertext; two reductions are 0.4 of one
+// histogram product, six limb products 1.2 of one.
 template <int KP, int G>
 __global__ __launch_bounds__(kBlockThreads, 2) void k_hist_pairs(DPair pc, const uint32_t *__restrict__ in, int mont,
                                                                  HistWs ws, uint64_t count) {
-  constexpr int SN = 32 * KP, K32 = SN / G, GB = kBlockThreads / G;
+  constexpr int SN = 32 * KP, GB = kBlockThreads / G;
   using E = SeqPair<SN, G>;
   constexpr int S = E::S, K = E::K;
   __shared__ __align__(16) uint32_t lds_all[GB * E::kLds];
@@ -159,60 +217,8 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_hist_pairs(DPair pc, const
     row = at < ws.rows ? at : 0;
   }
   E eng(pc, lds_all + (threadIdx.x / G) * E::kLds);
-  uint32_t lo[K], hi[K], a[K], b[K];
-  uint64_t C[K];
-  const uint32_t *x = in + (row * 2 + slot) * (uint64_t)(2 * SN);
-  if (mont) {
-    // X's 2 S limbs: the low half is the reduction's input, the high half its addend
-    uint32_t w[2 * K32];
-    ld<2 * K32, G>(w, x);
-    st<2 * K32, G>(eng.lds, w);
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        const uint32_t bit = he29::kBits * (h * S + glane<G>() * K + j), i = bit >> 5;
-        const uint32_t l = i < 2 * SN ? eng.lds[i] : 0u, u = i + 1 < 2 * SN ? eng.lds[i + 1] : 0u;
-        const uint32_t t = __builtin_amdgcn_alignbit(u, l, bit & 31u) & kMask29;
-        if (h) hi[j] = t;
-        else lo[j] = t;
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int j = 0; j < K; ++j) C[j] = lo[j];
-    eng.template pass<0, true>(C, nullptr, lo, nullptr, lo);
-#pragma unroll
-    for (int j = 0; j < K; ++j) C[j] += hi[j];
-    eng.settle(a, C);
-    eng.start_second(C);
-    eng.template pass<0, false>(C, nullptr, lo, nullptr, lo);
-    eng.end_second(C);
-    eng.settle(b, C);
-  } else {
-    const uint32_t *c0 = pc.c[kHistVariant], *c1 = c0 + 2 * S;
-    uint32_t w[K32];
-    ld<K32, G>(w, x);
-    to29<K32, K, G>(lo, w, eng.lds);
-    ld<K32, G>(w, x + SN);
-    to29<K32, K, G>(hi, w, eng.lds);
-    st29<K, G>(eng.lds, lo);
-    st29<K, G>(eng.lds + S, hi);
-    __builtin_amdgcn_wave_barrier();
-    ld29<K, G>(lo, c0);
-    ld29<K, G>(hi, c1);
-#pragma unroll
-    for (int j = 0; j < K; ++j) C[j] = 0;
-    eng.template pass<2, true>(C, eng.lds, lo, eng.lds + S, hi);
-    eng.settle(a, C);
-    ld29<K, G>(lo, c0 + S);
-    ld29<K, G>(hi, c1 + S);
-    eng.start_second(C);
-    eng.template pass<2, false>(C, eng.lds, lo, eng.lds + S, hi);
-    eng.end_second(C);
-    eng.settle(b, C);
-  }
+  uint32_t a[K], b[K];
+  eng.enter(a, b, in + (row * 2 + slot) * (uint64_t)(2 * SN), mont != 0, pc.c[kHistVariant]);
   if (valid) {
     uint32_t *o = ws.pairs + (r * 2 + slot) * (uint64_t)(2 * S);
     st29<K, G>(o, a);
@@ -234,7 +240,9 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_hist_pairs(DPair pc, const
 // lanes; two waves per SIMD (LDS and VGPRs allow no third) issue every cycle.
 // Root node of 100,000 samples x 32 features x 256 bins: 9.6 -> 6.0 ms for 6.4 M
 // products, 27.6 T multiply-adds/s.
-template <int KP, int G>
+// DIRECT: the ciphertexts are read as they are resident and converted one by one,
+// 1.4 to 2.2 times the work, for callers whose memory holds no second copy.
+template <int KP, int G, bool DIRECT>
 __global__ __launch_bounds__(kBlockThreads, 2) void k_hist_chunk(DPair pc, HistWs ws) {
   constexpr int SN = 32 * KP, GW = 64 / G;
   using E = SeqPair<SN, G>;
@@ -274,17 +282,40 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_hist_chunk(DPair pc, HistW
       return k < len ? ws.pairs + ((uint64_t)pp[k] * 2 + slot) * ROW : one;
     };
     uint32_t a[K], b[K];
-    const uint32_t *first = row_at(0);
-    ld29<K, G>(a, first);
-    ld29<K, G>(b, first + S);
-    uint32_t next[4 * V];
-    load(next, row_at(1));
+    if constexpr (DIRECT) {
+      // sample k's pair; past the run a resident row is read and the one kept
+      auto take = [&](uint32_t (&u)[K], uint32_t (&v)[K], uint32_t k) __attribute__((always_inline)) {
+        uint32_t o[K];
+        eng.enter(u, v, ws.ct + ((uint64_t)(k < len ? pp[k] : 0u) * 2 + slot) * (2 * SN), ws.mont != 0, pc.c[kHistVariant]);
+        ld29<K, G>(o, one);
+        select(u, k < len, u, o);
+        ld29<K, G>(o, one + S);
+        select(v, k < len, v, o);
+      };
+      take(a, b, 0);
 #pragma unroll 1
-    for (uint32_t k = 1; k < trip; ++k) {
-      stage(next);
-      load(next, row_at(k + 1));  // (past the run: the one)
-      eng.mul(a, b, lds, lds + S);
-      __builtin_amdgcn_wave_barrier();
+      for (uint32_t k = 1; k < trip; ++k) {
+        uint32_t u[K], v[K];
+        take(u, v, k);
+        st29<K, G>(lds, u);
+        st29<K, G>(lds + S, v);
+        __builtin_amdgcn_wave_barrier();
+        eng.mul(a, b, lds, lds + S);
+        __builtin_amdgcn_wave_barrier();
+      }
+    } else {
+      const uint32_t *first = row_at(0);
+      ld29<K, G>(a, first);
+      ld29<K, G>(b, first + S);
+      uint32_t next[4 * V];
+      load(next, row_at(1));
+#pragma unroll 1
+      for (uint32_t k = 1; k < trip; ++k) {
+        stage(next);
+        load(next, row_at(k + 1));  // (past the run: the one)
+        eng.mul(a, b, lds, lds + S);
+        __builtin_amdgcn_wave_barrier();
+      }
     }
     uint64_t done = trip ? trip - 1 : 0, real = len ? len - 1 : 0;
     for (uint32_t d = 1; d < P; d <<= 1) {

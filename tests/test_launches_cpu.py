@@ -201,3 +201,48 @@ for slots in (1, 2, 31):
 """, bits=2048, p=primes[2048][0], q=primes[2048][1])
     assert len(got["1"]) == 1 and "k_enc_obf" in got["1"][0]
     assert all(len(got[s]) == 1 and "k_pack" in got[s][0] for s in ("2", "31"))
+
+
+# ---------------------------------------------------------------- histograms
+JOBS = KEYS + r"""
+class Job(ctypes.Structure):
+    _fields_ = [("idx", vp), ("n", u64), ("bins", vp), ("ld", u64), ("F", u32), ("B", u32), ("hist", vp), ("bad", vp)]
+
+rows = env["rows"]
+def aggregate(n):
+    rec.rec_reset()
+    j = Job(A, n, A, rows, 2, 16, B, None)
+    rc = lib.he_hist_aggregate(plain, A, u64(rows), env["form"], ctypes.byref(j), u32(1), None)
+    return rc, [l[0] for l in launches()]
+
+def plan(n):
+    rec.rec_reset()
+    j, h = Job(A, n, A, rows, 2, 16, B, None), vp()
+    rc = lib.he_hist_plan_create(plain, A, u64(rows), env["form"], ctypes.byref(j), u32(1), u32(0), u32(0), ctypes.byref(h))
+    names = [l[0] for l in launches()]
+    if rc == 0:
+        lib.he_hist_plan_free(h)
+    return rc, names
+"""
+
+
+@pytest.mark.parametrize("form", [0, 1])
+@pytest.mark.parametrize("n", [200_000, 150_000])  # every row converted, or the samples gathered
+def test_histograms_without_memory_for_a_second_copy(tmp_path, primes, form, n):
+    """Where the ciphertexts in the kernels' form cannot be allocated (230 MB here),
+    a plan and a call run without them, as they did before there was such a copy;
+    where not even the partial products can, they are refused."""
+    got = record(tmp_path, JOBS + r"""
+out["roomy"] = [plan(env["n"]), aggregate(0)]
+base = rec.rec_total()
+rec.rec_limit(base + (64 << 20))
+out["tight"] = [plan(env["n"]), aggregate(env["n"])]
+rec.rec_limit(base + (1 << 20))
+out["none"] = [plan(env["n"])]
+""", bits=2048, p=primes[2048][0], q=primes[2048][1], rows=200_000, n=n, form=form)
+    rc, names = got["roomy"][0]
+    assert rc == 0 and any("k_hist_pairs" in x for x in names) and any("k_hist_chunkILi2ELi4ELb0E" in x for x in names)
+    for rc, names in got["tight"]:
+        assert rc == 0 and not any("k_hist_pairs" in x for x in names)
+        assert any("k_hist_chunkILi2ELi4ELb1E" in x for x in names)
+    assert got["none"][0][0] == -5
