@@ -257,6 +257,11 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_hist_chunk(DPair pc, HistW
   E eng(pc, lds);
   const uint32_t *one = pc.c[kHistVariant] + 2 * he29::kPairR * S;
   const uint64_t n_items = *ws.n_items;
+  // The grid is sized for the most items there could be.  Where there are fewer
+  // units than its waves, whichever waves claim first would take them, two on one
+  // SIMD and none on another: the blocks past the units leave (784 units on 512
+  // blocks 0.66 ms, on the 196 they need 0.52).
+  if ((uint64_t)blockIdx.x * (kBlockThreads / 64) * per_wave >= n_items) return;
   auto stage = [&](const uint32_t (&p)[4 * V]) __attribute__((always_inline)) {  // a row to LDS words [0, 2 S)
     stv<4 * V>(lds + glane<G>() * 4, p, 4 * G);
     __builtin_amdgcn_wave_barrier();
