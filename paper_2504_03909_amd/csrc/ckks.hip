@@ -51,12 +51,6 @@ __device__ __forceinline__ uint32_t add_q(uint32_t a, uint32_t b, uint32_t q) {
 __device__ __forceinline__ uint32_t sub_q(uint32_t a, uint32_t b, uint32_t q) {
   return a >= b ? a - b : a + q - b;
 }
-// x w mod q with the precomputed ws = floor(w 2^32 / q) (Shoup).
-__device__ __forceinline__ uint32_t mul_shoup(uint32_t x, uint32_t w, uint32_t ws, uint32_t q) {
-  const uint32_t hi = __umulhi(x, ws);
-  const uint32_t r = x * w - hi * q;  // in [0, 2q)
-  return r >= q ? r - q : r;
-}
 // a b 2^-32 mod q (Montgomery), a, b < q.
 __device__ __forceinline__ uint32_t mont_q(uint32_t a, uint32_t b, uint32_t q, uint32_t qinv) {
   const uint64_t t = (uint64_t)a * b;

@@ -45,8 +45,9 @@ int fail(int code, const std::string &msg) {
   } while (0)
 
 he::DMod mk_mod(const uint32_t *base, const hekey::ModOff &o) {
-  he::DMod m{base + o.N, base + o.R1, base + o.R2, base + o.R3, base + o.R4, o.ninv, {}, {}, {}};
+  he::DMod m{base + o.N, base + o.R1, base + o.R2, base + o.R3, o.ninv, {}, {}, {}};
   for (int v = 0; v < he29::kVariants; ++v) {
+    if (!o.N29[v]) continue;
     m.N29[v] = base + o.N29[v];
     m.R1_29[v] = base + o.R1_29[v];
     m.R2_29[v] = base + o.R2_29[v];
@@ -932,7 +933,11 @@ TuneKey tune_key(const he_key *key, const he_hist_job *jobs, uint32_t n_jobs) {
 // for the smallest batches, where nothing else fills the device.  Measured at
 // 2048 bits (ms at half, this and twice the length): W = 8,000 0.20 / 0.20 /
 // 0.24; 36,000 0.33 / 0.29 / 0.39; 168,000 0.73 / 0.62 / 0.74; 480,000 1.32 /
-// 1.13 / 1.14; 3,200,000 6.35 / 6.18 / 6.31; 14.7 M 46.2 / 45.4 / -.
+// 1.13 / 1.14; 3,200,000 6.35 / 6.18 / 6.31; 14.7 M 46.2 / 45.4 / -.  At 1024 bits
+// the best lengths are the same to one doubling, the rule's within 8% of them: W =
+// 8,000 0.124 / 0.112 / 0.124; 36,000 0.21 / 0.18 / 0.20; 165,000 0.44 / 0.38 / 0.36;
+// 480,000 0.93 / 0.83 / 0.92; 1,280,000 1.33 / 1.43 / 1.74; 3,200,000 2.55 / 2.50 /
+// 2.69; 12.8 M 9.42 / 9.33 / 9.47.
 // The bins' counts are known on the device only: there a full bin's items are
 // longer (item_chunk).  100,000 samples of one feature at 2048 bits, all in one
 // bin 5.33 -> 1.88 ms, in two 2.92 -> 1.36; 32 features x 256 Zipf bins as before.

@@ -12,8 +12,9 @@ namespace he {
 // the key's constant blob, each S limbs.  The radix-2^29 form (R' =
 // 2^(29 S29), one set per limb-count variant) serves the exponentiations.
 struct DMod {
-  const uint32_t *N, *R1, *R2, *R3, *R4;  // N, R^k mod N
+  const uint32_t *N, *R1, *R2, *R3;       // N, R^k mod N
   uint32_t ninv;                          // -N^-1 mod 2^32
+  // radix 2^29, null for a variant that no kernel reads
   const uint32_t *N29[he29::kVariants];   // N in S29 limbs of 29 bits
   const uint32_t *R1_29[he29::kVariants]; // R' mod N
   const uint32_t *R2_29[he29::kVariants]; // R'^2 mod N

@@ -75,18 +75,6 @@ __device__ __forceinline__ void seeded_limbs(uint32_t (&x)[K], uint64_t seed, ui
   }
 }
 
-// The wave's index in its block, as a wave-uniform (scalar) value: what the
-// persistent loops derive from it (unit index, prime, modulus and exponent
-// pointers) then lives in SGPRs.
-__device__ __forceinline__ uint32_t wave_in_block() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
-
-// The next work unit for this wave: one atomic add by the wave's first lane,
-// its result made wave-uniform.
-__device__ __forceinline__ uint64_t claim_unit(uint32_t *next) {
-  uint32_t v = 0;
-  if (lane_id() == 0) v = atomicAdd(next, 1u);
-  return __builtin_amdgcn_readfirstlane(v);
-}
 __device__ __forceinline__ uint32_t group_in_wave() { return (threadIdx.x >> 4) & 3u; }
 
 // ------------------------------------------------------------------- encode
@@ -677,7 +665,7 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_pack(DKey key, const uint3
     eng.mul();
 #pragma unroll
     for (int j = 0; j < K; ++j) C[j] = (uint64_t)eng.r[j] + t[j];
-    eng.settle(eng.r, C);
+    settle29<K, 8>(eng.r, C);
     st29<K, 16>(lds, eng.r);
     __builtin_amdgcn_wave_barrier();
     ld29<K, 16>(eng.y, lds);

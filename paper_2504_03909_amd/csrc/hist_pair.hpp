@@ -34,19 +34,6 @@ struct SeqPair {
     M.mask = mask_vgpr();
     if (glane<G>() == 0) lds[kM] = 0;
   }
-  __device__ __forceinline__ void settle(uint32_t (&t)[K], const uint64_t (&C)[K]) const {
-    uint64_t c = 0;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const uint64_t s = C[j] + c;
-      t[j] = (uint32_t)s & kMask29;
-      c = s >> he29::kBits;
-    }
-    const uint32_t cl = from_prev<G>((uint32_t)c), ch = from_prev<G>((uint32_t)(c >> 32));
-    const uint64_t s0 = (uint64_t)t[0] + (((uint64_t)ch << 32) | cl);
-    t[0] = (uint32_t)s0 & kMask29;
-    t[1] += (uint32_t)(s0 >> he29::kBits);
-  }
   // C <- (C + sum_i (u_i Y + v_i Z) 2^(29 i) + q N) 2^(-29 S): u, v (PRODS of
   // them) limbs in LDS; KEEP: the quotient digits to LDS.
   template <int PRODS, bool KEEP>
@@ -121,11 +108,11 @@ struct SeqPair {
 #pragma unroll
     for (int j = 0; j < K; ++j) C[j] = 0;
     pass<1, true>(C, c, a, c, a);
-    settle(a1, C);
+    settle29<K, G>(a1, C);
     start_second(C);
     pass<2, false>(C, c, b, d, a);
     end_second(C);
-    settle(b, C);
+    settle29<K, G>(b, C);
 #pragma unroll
     for (int j = 0; j < K; ++j) a[j] = a1[j];
   }
@@ -161,11 +148,11 @@ struct SeqPair {
       pass<0, true>(C, nullptr, lo, nullptr, lo);
 #pragma unroll
       for (int j = 0; j < K; ++j) C[j] += hi[j];
-      settle(a, C);
+      settle29<K, G>(a, C);
       start_second(C);
       pass<0, false>(C, nullptr, lo, nullptr, lo);
       end_second(C);
-      settle(b, C);
+      settle29<K, G>(b, C);
     } else {
       const uint32_t *c1 = c0 + 2 * S;
       uint32_t w[K32];
@@ -181,13 +168,13 @@ struct SeqPair {
 #pragma unroll
       for (int j = 0; j < K; ++j) C[j] = 0;
       pass<2, true>(C, lds, lo, lds + S, hi);
-      settle(a, C);
+      settle29<K, G>(a, C);
       ld29<K, G>(lo, c0 + S);
       ld29<K, G>(hi, c1 + S);
       start_second(C);
       pass<2, false>(C, lds, lo, lds + S, hi);
       end_second(C);
-      settle(b, C);
+      settle29<K, G>(b, C);
     }
   }
 };

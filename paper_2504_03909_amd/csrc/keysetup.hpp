@@ -44,8 +44,9 @@ struct Blob {
 struct ModOff {  // Montgomery modulus N of S limbs, R = 2^(32 S)
   size_t N, R1, R2, R3, R4;
   uint32_t ninv;
-  // radix-2^29 form per variant: N, R mod N and R^2 mod N with R = 2^(29 S29)
-  size_t N29[he29::kVariants], R1_29[he29::kVariants], R2_29[he29::kVariants];
+  // radix-2^29 form per variant asked for: N, R mod N and R^2 mod N with R = 2^(29
+  // S29); 0 where it was not
+  size_t N29[he29::kVariants] = {}, R1_29[he29::kVariants] = {}, R2_29[he29::kVariants] = {};
 };
 // Constants of the two-digit form of residues mod N^2, per limb-count variant.
 struct PairOff {
@@ -157,7 +158,8 @@ struct KeyConsts {
 
 inline Limbs pow2(size_t e) { return hebn::shl(hebn::from_u64(1), e); }
 
-inline ModOff put_mod(Blob &b, const Limbs &N, size_t S) {
+// v29: the radix-2^29 variants a kernel reads of N (bit v), none of n and P^2.
+inline ModOff put_mod(Blob &b, const Limbs &N, size_t S, uint32_t v29) {
   ModOff m;
   const Limbs R1 = hebn::mod(pow2(32 * S), N);
   const Limbs R2 = hebn::mulmod(R1, R1, N);
@@ -170,6 +172,7 @@ inline ModOff put_mod(Blob &b, const Limbs &N, size_t S) {
   m.R4 = b.put(R4, S);
   m.ninv = hebn::neg_inv32(N[0]);
   for (int v = 0; v < he29::kVariants; ++v) {
+    if (!(v29 >> v & 1u)) continue;
     const size_t S29 = (size_t)he29::limbs((int)S, v);
     const Limbs Q1 = hebn::mod(pow2(he29::kBits * S29), N);
     m.N29[v] = b.put29(N, S29);
@@ -245,8 +248,8 @@ inline PrimeOff put_prime(Blob &b, const Limbs &P, const Limbs &Q, const Limbs &
   PrimeOff o;
   const Limbs one = hebn::from_u64(1);
   const Limbs P2 = hebn::mul(P, P);
-  o.P = put_mod(b, P, SP);
-  o.P2 = put_mod(b, P2, 2 * SP);
+  o.P = put_mod(b, P, SP, 7);
+  o.P2 = put_mod(b, P2, 2 * SP, 0);
   const Limbs Pm1 = hebn::sub(P, one), e = hebn::mod(Q, Pm1);
   const Limbs ej = hebn::is_zero(e) ? Pm1 : e;  // x^(P-1) = x^0 mod P
   o.pair = put_pair(b, P, SP, ej);
@@ -275,8 +278,8 @@ inline KeyConsts derive(uint32_t n_bits, const Limbs &n, const Limbs &p, const L
   const Limbs one = hebn::from_u64(1);
   const Limbs n2 = hebn::mul(n, n);
   Blob &b = k.blob;
-  k.n = put_mod(b, n, L);
-  k.n2 = put_mod(b, n2, 2 * L);
+  k.n = put_mod(b, n, L, 0);
+  k.n2 = put_mod(b, n2, 2 * L, 1u << he29::variant(16));  // the form the histograms take
   k.pair_n = put_pair(b, n, L, Limbs());
   k.e_n = put_exp(b, n, L);
   const Limbs Rn2 = hebn::mod(pow2(64 * L), n2);

@@ -503,6 +503,19 @@ __device__ __forceinline__ void sub_mod(uint32_t (&t)[K], const uint32_t (&x)[K]
 }
 
 // ---- shifts and tests ----------------------------------------------------------
+// The wave's index in its block, as a wave-uniform (scalar) value: what the
+// persistent loops derive from it (unit index, prime, modulus and exponent
+// pointers) then lives in SGPRs.
+__device__ __forceinline__ uint32_t wave_in_block() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// The next work unit for this wave: one atomic add by the wave's first lane,
+// its result made wave-uniform.
+__device__ __forceinline__ uint64_t claim_unit(uint32_t *next) {
+  uint32_t v = 0;
+  if (lane_id() == 0) v = atomicAdd(next, 1u);
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
 __device__ __forceinline__ bool wave_any(bool v) { return __builtin_amdgcn_ballot_w64(v) != 0ull; }
 
 // Group-uniform: x == 0.

@@ -148,6 +148,23 @@ __device__ __forceinline__ void step29(uint64_t (&C)[K], uint32_t &top, uint32_t
   asm("" : "+v"(top));
 }
 
+// t = C settled: one carry pass in the lane, the lane's carry (below 2^36) into
+// the next lane's lowest limb; the group's top carry is zero (result below R').
+template <int K, int G>
+__device__ __forceinline__ void settle29(uint32_t (&t)[K], const uint64_t (&C)[K]) {
+  uint64_t c = 0;
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const uint64_t s = C[j] + c;
+    t[j] = (uint32_t)s & kMask29;
+    c = s >> he29::kBits;
+  }
+  const uint32_t cl = from_prev<G>((uint32_t)c), ch = from_prev<G>((uint32_t)(c >> 32));
+  const uint64_t s0 = (uint64_t)t[0] + (((uint64_t)ch << 32) | cl);
+  t[0] = (uint32_t)s0 & kMask29;
+  t[1] += (uint32_t)(s0 >> he29::kBits);
+}
+
 // t = a b R'^-1 mod N (settled, below 2N) with a (settled, below 2N) in this
 // group's LDS row and b (settled, below 2N) in registers.  t may alias b.
 template <int K, int G>
@@ -171,19 +188,7 @@ __device__ __forceinline__ void mm29_lds(uint32_t (&t)[K], const uint32_t *a_lds
     });
   }
   C[K - 1] = top;
-  // settle: one carry pass in the lane, the lane's carry (below 2^36) into
-  // the next lane's lowest limb; the group's top carry is zero (result < 2N)
-  uint64_t c = 0;
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    const uint64_t s = C[j] + c;
-    t[j] = (uint32_t)s & kMask29;
-    c = s >> he29::kBits;
-  }
-  const uint32_t cl = from_prev<G>((uint32_t)c), ch = from_prev<G>((uint32_t)(c >> 32));
-  const uint64_t s0 = (uint64_t)t[0] + (((uint64_t)ch << 32) | cl);
-  t[0] = (uint32_t)s0 & kMask29;
-  t[1] += (uint32_t)(s0 >> he29::kBits);
+  settle29<K, G>(t, C);
 }
 
 // Squaring.  The products a_i a_j of a square pair up (a_i a_j = a_j a_i),
@@ -279,17 +284,7 @@ __device__ __forceinline__ void sq29_lds(uint32_t (&t)[K], const uint32_t *lds, 
     });
   }
   C[K - 1] = top;
-  uint64_t c = 0;
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    const uint64_t s = C[j] + c;
-    t[j] = (uint32_t)s & kMask29;
-    c = s >> he29::kBits;
-  }
-  const uint32_t cl = from_prev<G>((uint32_t)c), ch = from_prev<G>((uint32_t)(c >> 32));
-  const uint64_t s0 = (uint64_t)t[0] + (((uint64_t)ch << 32) | cl);
-  t[0] = (uint32_t)s0 & kMask29;
-  t[1] += (uint32_t)(s0 >> he29::kBits);
+  settle29<K, G>(t, C);
 }
 
 // Fills the block-shared zero words the squaring reads (n words); every

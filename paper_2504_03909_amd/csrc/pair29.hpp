@@ -685,27 +685,13 @@ struct GroupPair {
       for (int j = 0; j < K; ++j) z[j] |= t[j] & m;
     }
   }
-  // one carry pass in the lane, the lane's carry into the next lane's limbs
-  __device__ __forceinline__ void settle(uint32_t (&t)[K], const uint64_t (&C)[K]) const {
-    uint64_t c = 0;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const uint64_t s = C[j] + c;
-      t[j] = (uint32_t)s & kMask29;
-      c = s >> he29::kBits;
-    }
-    const uint32_t cl = from_prev<G>((uint32_t)c), ch = from_prev<G>((uint32_t)(c >> 32));
-    const uint64_t s0 = (uint64_t)t[0] + (((uint64_t)ch << 32) | cl);
-    t[0] = (uint32_t)s0 & kMask29;
-    t[1] += (uint32_t)(s0 >> he29::kBits);
-  }
   __device__ __forceinline__ void add(uint32_t e) {
     uint32_t t[K];
     uint64_t C[K];
     ld29<K, 2 * G>(t, slot(e));
 #pragma unroll
     for (int j = 0; j < K; ++j) C[j] = (uint64_t)r[j] + t[j];
-    settle(r, C);
+    settle29<K, G>(r, C);
   }
   // The reduction's part of a step: the quotient digit of the lowest column,
   // the shift by one limb and (HAND) the first digit's q into the second's
@@ -773,7 +759,7 @@ struct GroupPair {
       });
     }
     C[K - 1] = top;
-    settle(r, C);
+    settle29<K, G>(r, C);
     __builtin_amdgcn_wave_barrier();
   }
   __device__ __forceinline__ void sq() {
@@ -829,13 +815,13 @@ struct GroupPair {
       reduce_step<true>(C, top);
     }
     C[K - 1] = top;
-    settle(r, C);
+    settle29<K, G>(r, C);
 #pragma unroll
     for (int j = 0; j < K; ++j) C[j] = r[j];
     top = r[K - 1];
     reduce_step<false>(C, top);
     C[K - 1] = top;
-    settle(t, C);
+    settle29<K, G>(t, C);
 #pragma unroll
     for (int j = 0; j < K; ++j) r[j] = second_digit ? t[j] : r[j];
     const bool sub = canon29<K, G>(r, M);
@@ -864,7 +850,7 @@ struct GroupPair {
       for (int j = 0; j + 1 < K; ++j) C[j] = C[j + 1];
     }
     C[K - 1] = top;
-    settle(t, C);
+    settle29<K, G>(t, C);
     carry29<K, G>(t);
     __builtin_amdgcn_wave_barrier();
     if (!second_digit) {

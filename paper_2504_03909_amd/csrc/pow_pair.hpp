@@ -6,13 +6,6 @@
 
 namespace he {
 
-__device__ __forceinline__ uint32_t pair_wave() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
-__device__ __forceinline__ uint64_t pair_claim(uint32_t *next) {
-  uint32_t v = 0;
-  if (lane_id() == 0) v = atomicAdd(next, 1u);
-  return __builtin_amdgcn_readfirstlane(v);
-}
-
 template <int SN, int L>
 struct PairEngine;
 template <int SN>
@@ -39,11 +32,11 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_pow_pair(PairPowArgs p) {
   uint32_t *const zeros = lds_all + ROWS * E::kLds;
   if constexpr (ZERO > 0) zero_lds(zeros, ZERO);
   uint32_t *const row = lds_all + (threadIdx.x / E::kLanes) * E::kLds;
-  const uint64_t gw = (uint64_t)blockIdx.x * 4 + pair_wave();
+  const uint64_t gw = (uint64_t)blockIdx.x * 4 + wave_in_block();
   const uint64_t nw = (uint64_t)gridDim.x * 4;
   uint32_t *const tab = p.tabs + gw * (uint64_t)(kTable + 1) * E::kSlot;
   const uint64_t nunits = 2 * ((p.count + NG - 1) / NG);
-  for (uint64_t qd = p.next ? pair_claim(p.next) : gw; qd < nunits; qd = p.next ? pair_claim(p.next) : qd + nw) {
+  for (uint64_t qd = p.next ? claim_unit(p.next) : gw; qd < nunits; qd = p.next ? claim_unit(p.next) : qd + nw) {
     const int which = (int)(qd & 1);
     uint64_t i = (qd >> 1) * NG + E::member();
     const bool valid = i < p.count;
@@ -64,11 +57,11 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_pow_joint(PairPowArgs p) {
   uint32_t *const zeros = lds_all + ROWS * E::kLds;
   if constexpr (ZERO > 0) zero_lds(zeros, ZERO);
   uint32_t *const row = lds_all + (threadIdx.x / E::kLanes) * E::kLds;
-  const uint64_t gw = (uint64_t)blockIdx.x * 4 + pair_wave();
+  const uint64_t gw = (uint64_t)blockIdx.x * 4 + wave_in_block();
   const uint64_t nw = (uint64_t)gridDim.x * 4;
   uint32_t *const tab = p.tabs + gw * (uint64_t)(kTable + 1) * E::kSlot;
   const uint64_t nunits = 2 * ((p.count + NG - 1) / NG);
-  for (uint64_t qd = p.next ? pair_claim(p.next) : gw; qd < nunits; qd = p.next ? pair_claim(p.next) : qd + nw) {
+  for (uint64_t qd = p.next ? claim_unit(p.next) : gw; qd < nunits; qd = p.next ? claim_unit(p.next) : qd + nw) {
     const int which = (int)(qd & 1);
     uint64_t i = (qd >> 1) * NG + E::member();
     const bool valid = i < p.count;
@@ -91,7 +84,9 @@ const void *pow_pair_fn(PairPow which) {
     if (which == PairPow::kJoint) return (const void *)k_pow_joint<SN, L>;
   if constexpr (L > 0)
     if (which == PairPow::kSliding) return (const void *)k_pow_pair<SN, L, false>;
-  return which == PairPow::kMasked ? (const void *)k_pow_pair<SN, L, true> : nullptr;
+  if constexpr (SN <= 32)  // the public exponent n is never masked
+    if (which == PairPow::kMasked) return (const void *)k_pow_pair<SN, L, true>;
+  return nullptr;
 }
 
 }  // namespace he
