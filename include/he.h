@@ -260,7 +260,7 @@ int he_hist_autotune(const he_key *key, const uint32_t *ct, uint64_t rows, int c
  *         lift, decryption) lanes (0 = the default plan), waves (0 = own
  *         occupancy) and lanes of the remainder's launch (0 = one launch):
  *         what he_crt_set_shape takes to set the same.
- * ms: optional host float[3]: their launch times.
+ * ms: optional host float[3]: their launch times (0: no shape fit in memory).
  * HE_ERR_NOPRIV for a public key, HE_ERR_ARG for a zero count. */
 int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t dec_count, uint32_t *choice, float *ms,
                     hipStream_t stream);

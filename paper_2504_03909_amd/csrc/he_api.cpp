@@ -349,6 +349,32 @@ he::PowPlan pow_plan(int KP, int kind, uint64_t count) {
   return sh.G ? pow_plan_at(KP, kind, count, sh) : default_pow_plan(KP, kind, count);
 }
 
+// Workspace for the window tables of a call's exponentiations (one after the
+// other), 0.6 to 1.25 GB where one lane per integer fills the device.  Without
+// room for them the largest launches are halved until they fit: waves claim their
+// units, so any number of blocks does the same work.
+struct KindPlan {
+  int kind;
+  he::PowPlan *plan;  // main.G 0: a step the call does not have
+};
+int ensure_tables(Buf &b, int KP, std::initializer_list<KindPlan> plans, hipStream_t s) {
+  for (;;) {
+    uint64_t bytes = 0;
+    for (const KindPlan &k : plans)
+      if (k.plan->main.G) bytes = std::max(bytes, plan_table_bytes(KP, k.kind, *k.plan));
+    const int rc = ensure(b, bytes, s);
+    if (rc != HE_ERR_OOM) return rc;
+    bool halved = false;
+    for (const KindPlan &k : plans)
+      for (he::PowLaunch *l : {&k.plan->main, &k.plan->tail}) {
+        if (!l->G || l->grid < 2 || l->grid * he::table_bytes_per_block(KP, k.kind, l->G) <= bytes / 2) continue;
+        l->grid = (l->grid + 1) / 2;
+        halved = true;
+      }
+    if (!halved) return rc;
+  }
+}
+
 // m == nullptr encrypts zeros (the obfuscators r^n mod n^2).
 int encrypt_impl(const he_key *key, const int64_t *m, uint64_t count, const uint32_t *r,
                  uint64_t r_seed, uint64_t r_offset, uint32_t *ct, hipStream_t stream, bool force_pub) {
@@ -363,20 +389,16 @@ int encrypt_impl(const he_key *key, const int64_t *m, uint64_t count, const uint
     const he::DKey dk = key->dk;
     const int kind = he::pow_lift_kind(dk);
     he::PowPlan p1{}, p2 = pow_plan(KP, kind, count);
-    uint64_t tab_bytes = plan_table_bytes(KP, kind, p2);
-    if (dk.ct) {
-      p1 = pow_plan(KP, 4, count);
-      tab_bytes = std::max(tab_bytes, plan_table_bytes(KP, 4, p1));
-    }
-    int rc = ensure(w->tab, tab_bytes, stream);
-    if (rc) return rc;
-    rc = ensure(w->ctr, 256, stream);
+    if (dk.ct) p1 = pow_plan(KP, 4, count);
+    int rc = ensure(w->ctr, 256, stream);
     if (rc) return rc;
     p1.ctr = (uint32_t *)w->ctr.p;
     p2.ctr = p1.ctr + 2;
     // omega / c_P per (ciphertext, prime) (2L limbs per ciphertext), then
     // r mod P / t per (ciphertext, prime) (L limbs)
     rc = ensure(w->tmp, count * 3 * L * sizeof(uint32_t), stream);
+    if (rc) return rc;
+    rc = ensure_tables(w->tab, KP, {{4, &p1}, {kind, &p2}}, stream);
     if (rc) return rc;
     uint32_t *cpq = (uint32_t *)w->tmp.p, *tq = cpq + count * 2 * L;
     HE_TRY_HIP(he::launch_enc_crt(KP, dk, m, count, r, r_seed, r_offset, tq, cpq, ct, (uint32_t *)w->tab.p,
@@ -385,13 +407,13 @@ int encrypt_impl(const he_key *key, const int64_t *m, uint64_t count, const uint
     // the exponentiation's units pair consecutive ciphertexts (both "primes"
     // of a public-key unit pair are n^2)
     he::PowPlan p = pow_plan(KP, 1, (count + 1) / 2);
-    int rc = ensure(w->tab, plan_table_bytes(KP, 1, p), stream);
-    if (rc) return rc;
-    rc = ensure(w->ctr, 256, stream);
+    int rc = ensure(w->ctr, 256, stream);
     if (rc) return rc;
     p.ctr = (uint32_t *)w->ctr.p;
     // r mod n, then r^n mod n^2: count + (count & 1) rows of L and of 2L limbs
     rc = ensure(w->tmp, (count + 1) * 3 * L * sizeof(uint32_t), stream);
+    if (rc) return rc;
+    rc = ensure_tables(w->tab, KP, {{1, &p}}, stream);
     if (rc) return rc;
     HE_TRY_HIP(he::launch_enc_pub(KP, key->dk, m, count, r, r_seed, r_offset, (uint32_t *)w->tmp.p, ct,
                                   (uint32_t *)w->tab.p, p, stream));
@@ -585,13 +607,13 @@ int he_decrypt(const he_key *key, const uint32_t *ct, uint64_t count, int64_t *m
   const he::DKey dk = key->dk;
   const int kind = he::pow_dec_kind(dk);
   he::PowPlan p = pow_plan(KP, kind, count);
-  int rc = ensure(w->tab, plan_table_bytes(KP, kind, p), stream);
-  if (rc) return rc;
-  rc = ensure(w->ctr, 256, stream);
+  int rc = ensure(w->ctr, 256, stream);
   if (rc) return rc;
   p.ctr = (uint32_t *)w->ctr.p;
   // c^(P-1) mod P^2 per (ciphertext, prime): 2L limbs per ciphertext
   rc = ensure(w->tmp, count * 2 * L * sizeof(uint32_t), stream);
+  if (rc) return rc;
+  rc = ensure_tables(w->tab, KP, {{kind, &p}}, stream);
   if (rc) return rc;
   HE_TRY_HIP(he::launch_dec(KP, dk, ct, count, (uint32_t *)w->tmp.p, m, raw, n_overflow,
                             (uint32_t *)w->tab.p, p, stream));
@@ -1097,19 +1119,27 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
       if (he::pow_shape_valid(KP, kind, G))
         tab_bytes = std::max<size_t>(tab_bytes, (size_t)he::pow_resident_blocks(KP, kind, G, 0) *
                                                    he::table_bytes_per_block(KP, kind, G));
-  const size_t sizes[6] = {n_ct * L * 4, n_ct * 2 * L * 4, n_ct * 2 * L * 4, n_ct * 2 * L * 4, tab_bytes, 256};
-  DevBuf *bufs[6] = {&tq, &cpq, &ct, &xpq, &tab, &ctr};
-  for (int b = 0; b < 6; ++b)
+  const size_t sizes[5] = {n_ct * L * 4, n_ct * 2 * L * 4, n_ct * 2 * L * 4, n_ct * 2 * L * 4, 256};
+  DevBuf *bufs[5] = {&tq, &cpq, &ct, &xpq, &ctr};
+  for (int b = 0; b < 5; ++b)
     if (hipMalloc(&bufs[b]->p, sizes[b]) != hipSuccess) {
       hipGetLastError();
       return fail(HE_ERR_OOM, "autotuner trial buffers");
     }
   uint32_t *tq_p = (uint32_t *)tq.p, *cpq_p = (uint32_t *)cpq.p, *ct_p = (uint32_t *)ct.p,
-           *xpq_p = (uint32_t *)xpq.p, *tab_p = (uint32_t *)tab.p;
+           *xpq_p = (uint32_t *)xpq.p;
   // real operands: r mod P, one encryption (default shapes)
   HE_TRY_HIP(he::launch_enc_r(KP, key->dk, enc_count, nullptr, 1, 0, tq_p, stream));
   int rc = encrypt_impl(key, nullptr, n_ct, nullptr, 1, 0, ct_p, stream, false);
   if (rc) return rc;
+  // the window tables, or what there is room for: shapes that need more are not tried
+  while (hipMalloc(&tab.p, tab_bytes) != hipSuccess) {
+    hipGetLastError();
+    tab.p = nullptr;
+    tab_bytes /= 2;
+    if (tab_bytes < (1u << 20)) return fail(HE_ERR_OOM, "autotuner window tables");
+  }
+  uint32_t *tab_p = (uint32_t *)tab.p;
   hipEvent_t e0, e1;
   HE_TRY_HIP(hipEventCreate(&e0));
   HE_TRY_HIP(hipEventCreate(&e1));
@@ -1119,6 +1149,7 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
     const int kind = kinds[t];
     const uint64_t count = t == 2 ? dec_count : enc_count;
     auto trial = [&](const PowShape &sh, he::PowPlan p) -> int {
+      if (plan_table_bytes(KP, kind, p) > tab_bytes) return HE_OK;
       p.ctr = (uint32_t *)ctr.p;
       auto run = [&]() -> hipError_t {
         return he::launch_pow_kind(KP, key->dk, kind, t == 2 ? ct_p : tq_p, t == 0 ? tq_p : (t == 2 ? xpq_p : cpq_p), count,
@@ -1159,7 +1190,7 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
     const he::PowPlan dp = default_pow_plan(KP, kind, count);
     if (!rc && (dp.tail.G || !pow_shape_named(KP, kind, dp.main.G))) rc = trial(PowShape{}, dp);
     for (int tg : {4, 8, 16}) {
-      if (rc || tg <= one.G || !he::pow_shape_valid(KP, kind, tg)) continue;
+      if (rc || one.G == 0 || tg <= one.G || !he::pow_shape_valid(KP, kind, tg)) continue;
       const PowShape sh{one.G, one.waves, tg};
       const he::PowPlan p = pow_plan_at(KP, kind, count, sh);
       if (p.tail.G == 0) break;  // whole rounds only, or less than one: nothing to split
@@ -1181,7 +1212,7 @@ extern "C" int he_crt_autotune(const he_key *key, uint64_t enc_count, uint64_t d
       choice[3 * t + 1] = (uint32_t)best[t].waves;
       choice[3 * t + 2] = (uint32_t)best[t].tailG;
     }
-    if (ms_out) ms_out[t] = best_ms[t];
+    if (ms_out) ms_out[t] = best_ms[t] < 1e30f ? best_ms[t] : 0.f;
   }
   return HE_OK;
 }

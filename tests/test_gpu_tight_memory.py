@@ -78,3 +78,39 @@ def test_without_a_second_copy(bits, seed, rows):
         del hold
         torch.cuda.empty_cache()
     k.close()
+
+
+@pytest.mark.parametrize("secret", [False, True])
+def test_exponentiations_on_fewer_blocks(secret):
+    """200,000 encryptions and their decryption with 320 MB free, a quarter of the
+    window tables that fill the device: the ciphertexts and plaintexts of the full
+    launches."""
+    import torch
+    from paper_2504_03909_amd import he
+    bits, n = 2048, 200_000
+    p, q = P.keygen(bits, 2)
+    k = he.Key.from_primes(bits, p, q)
+    k.set_constant_time(secret)
+    for kind in ("mod_p", "lift", "decrypt"):
+        he.crt_set_shape(k, kind, n, 0)
+    say(f"{n} encryptions with room, secret={secret}")
+    m = torch.from_numpy(np.random.default_rng(4).integers(-(1 << 62), 1 << 62, size=n, dtype=np.int64)).cuda()
+    ct = he.encrypt(k, m, seed=17)
+    out, back = torch.empty_like(ct), torch.empty_like(m)
+    overflow = torch.zeros(1, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free, _ = torch.cuda.mem_get_info()
+    hold = torch.empty(free - (320 << 20), dtype=torch.uint8, device="cuda")
+    try:
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        say("without room")
+        he.encrypt(k, m, seed=17, out=out, stream=side)
+        he._check(he._decrypt(k.handle, he._ptr(out), n, he._ptr(back), None, he._ptr(overflow), side.cuda_stream))
+        side.synchronize()
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+    assert torch.equal(out, ct) and torch.equal(back, m) and int(overflow.item()) == 0
+    k.close()

@@ -246,3 +246,45 @@ out["none"] = [plan(env["n"])]
         assert rc == 0 and not any("k_hist_pairs" in x for x in names)
         assert any("k_hist_chunkILi2ELi4ELb1E" in x for x in names)
     assert got["none"][0][0] == -5
+
+
+@pytest.mark.parametrize("bits", [1024, 2048])
+def test_exponentiations_with_little_room_for_tables(tmp_path, primes, bits):
+    """One lane per integer on every SIMD takes 0.6 to 1.25 GB of window tables. With
+    less memory (as much as the former kernels needed at 2048 bits, then hardly
+    more than the operands) encryption and decryption run on fewer blocks, the
+    tuner (with the 830 MB it needed then) tries what fits, and only calls without room for their operands fail."""
+    got = record(tmp_path, PINS + r"""
+n = 200000
+def call(name, stream):
+    rec.rec_reset()
+    if name == "encrypt":
+        return lib.he_encrypt(plain, A, u64(n), None, u64(1), u64(0), B, stream)
+    if name == "secret":
+        return lib.he_encrypt(secret, A, u64(n), None, u64(1), u64(0), B, stream)
+    if name == "public":
+        return lib.he_encrypt_public(plain, A, u64(n), None, u64(1), u64(0), B, stream)
+    return lib.he_decrypt(plain if name == "decrypt" else secret, A, u64(n), B, None, None, stream)
+
+stream = 1
+for room in (0, 443, 160, 20):
+    for name in ("encrypt", "secret", "public", "decrypt", "secret decrypt"):
+        stream += 1  # a stream has its own workspace
+        base = rec.rec_total()
+        rec.rec_limit(base + (room << 20) if room else (1 << 63))
+        rc = call(name, vp(stream))
+        out[f"{room} {name}"] = [rc, max([g for s, g, _ in launches() if "k_pow" in s] or [0]), rec.rec_total() - base]
+rec.rec_limit(rec.rec_total() + (env["tune"] << 20))
+out["tune"] = tune(plain, 20000, 20000)
+rec.rec_limit(1 << 63)
+""", bits=bits, p=primes[bits][0], q=primes[bits][1], tune=830)
+    for name in ("encrypt", "secret", "public", "decrypt", "secret decrypt"):
+        full = got[f"0 {name}"]
+        assert full[0] == 0 and full[1] >= 256
+        for room in (443, 160):
+            rc, grid, used = got[f"{room} {name}"]
+            assert rc == 0 and 1 <= grid <= full[1] and used <= room << 20, (room, name)
+        assert got[f"20 {name}"][0] == -5
+    assert got["160 encrypt"][1] < got["0 encrypt"][1] or got["0 encrypt"][2] <= 160 << 20
+    choice, ms = got["tune"]
+    assert ms[1] > 0 and ms[2] > 0
