@@ -514,7 +514,8 @@ def main():
             "exponentiation_shapes": {k: {"lanes": v.lanes or "default plan",
                                           "waves_per_simd": v.waves or "own occupancy",
                                           "last_round_lanes": (v.tail_lanes or "same launch") if v.lanes else "planned",
-                                          "tuning_ms": round(v.ms, 3)} for k, v in exp_shapes.items()},
+                                          "tuning_ms": round(v.ms, 3)} for k, v in exp_shapes.items()
+                                      if k != "mod_p"},  # a step of constant-time keys only
         },
         "stages": {
             "encode_ms": round(avg["encode"], 3),

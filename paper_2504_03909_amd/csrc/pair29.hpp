@@ -28,8 +28,9 @@
 // Measured (2048-bit key, against the same powers as one integer mod P^2 at 4
 // to 16 lanes): 200,000 lifts 131 -> 84 ms, 16,384 decryptions 12.2 -> 8.0 ms,
 // 2,006 lifts 4.4 -> 2.6 ms, 2,501 pairs of powers mod n^2 28.5 -> 17.0 ms.
-// What bounds it: VALU issue (a LanePair square is 4,554 multiply-adds of 4.2
-// cycles); below a wave per SIMD, the latency of a step.
+// What bounds it: VALU issue (a LanePair square is 4,630 multiply-adds of 4.2
+// cycles, 4,554 of them limb products, the rest hand over quotient digits and
+// join wide columns); below a wave per SIMD, the latency of a step.
 #pragma once
 #include "mont29.hpp"
 

@@ -369,7 +369,7 @@ def hist_aggregate(key: Key, ct: torch.Tensor, jobs: Sequence[Job], form: int = 
 def hist_aggregate_counted(key: Key, ct: torch.Tensor, jobs: Sequence[Job], form: int = HE_FORM_CANONICAL,
                            chunk: int = 0, split: int = 2, lanes: int = 0, waves: int = 0, stream=None):
     """hist_aggregate at an explicit work shape (chunk, groups per item,
-    lanes per ciphertext, waves per SIMD; 0 = default) plus the work
+    lanes per sample, waves per SIMD; 0 = default) plus the work
     counters: returns (hists, [real products, executed products, conversions
     out of Montgomery form])."""
     arr = (HistJob * len(jobs))(*[j.as_c(key) for j in jobs])
