@@ -279,7 +279,7 @@ const std::vector<PowCost> &pow_costs(int KP, int kind) {
   static const std::vector<PowCost> mod16 = {{1, 2.5, 2.55}, {2, 2.0, 1.65}, {4, 1.15, .6}, {8, 1.2, .45}, {16, 1.53, .42}};
   static const std::vector<PowCost> mod32 = {{1, 11, 10.4}, {2, 6.5, 7.7}, {4, 3.5, 2.7}, {8, 3.3, 1.8}, {16, 3.4, 1.5}};
   static const std::vector<PowCost> mask16 = {{1, 5.2, 5.25}, {2, 2.7, 2.55}, {4, 1.9, 1.05}, {8, 1.6, .7}, {16, 1.34, .55}};
-  static const std::vector<PowCost> mask32 = {{1, 32, 23.5}, {2, 14, 12.7}, {4, 8.4, 6.1}, {8, 5, 3.35}, {16, 4.2, 2.3}};
+  static const std::vector<PowCost> mask32 = {{1, 32, 22.5}, {2, 14, 12.7}, {4, 8.4, 6.3}, {8, 5, 3.35}, {16, 4.2, 2.3}};
   static const std::vector<PowCost> pair16 = {{1, 1.93, 1.72}, {2, 1.2, .98}, {4, .88, .55}, {8, .72, .41}, {16, .78, .38}};
   static const std::vector<PowCost> pair32 = {{1, 13.1, 12.1}, {2, 7.95, 7.1}, {4, 4.7, 3.6}, {8, 2.9, 2.1}, {16, 2.58, 1.53}};
   static const std::vector<PowCost> joint16 = {{1, 2.5, 2.2}, {2, 1.65, 1.35}, {4, 1.12, .74}, {8, .93, .54}, {16, .98, .46}};
