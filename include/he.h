@@ -94,7 +94,7 @@ int he_key_export(const he_key *key, uint32_t *n, uint32_t *p, uint32_t *q);
  * 5-bit windows, one multiplication per window whatever its digit, and
  * every window reads all 32 table entries and keeps the one its digit names
  * by a mask, so neither the operations nor the device addresses touched
- * depend on the exponent (about 2.1x the default's encryption time on the
+ * depend on the exponent (about 2.2x the default's encryption time on the
  * 2048-bit pass).  Results are identical bit for bit.  Applies to calls enqueued
  * after it returns; must not run concurrently with other calls on the same key.  HE_ERR_ARG for a null key. */
 int he_key_set_constant_time(he_key *key, int on);

@@ -276,8 +276,8 @@ __global__ __launch_bounds__(256) void k_sample_enc(uint64_t seed, uint64_t offs
 // instead of nine: transforms, product and sums stay in registers.  Each part
 // transforms u again: a block that made both from one transform had to hold it
 // beside the inverse's values and spilled, and took 1.14 ms for 1,000
-// ciphertexts at N = 2^14 where this takes 0.8 (2.1 with a launch per step); for
-// ten the parts also spread over twice the compute units (105 -> 34 us).
+// ciphertexts at N = 2^14 where this takes 0.64 (2.1 with a launch per step); for
+// ten the parts also spread over twice the compute units (105 -> 25 us).
 template <int LOGN>
 __global__ __launch_bounds__(Ntt<LOGN>::T) void k_encrypt(const uint32_t *pt, Tables T, const uint32_t *keys,
                                                           uint32_t *ct) {
