@@ -38,6 +38,7 @@ extern "C" {
 // ---- controls
 void rec_reset() { launches.clear(); timed = 0; }
 int rec_count() { return (int)launches.size(); }
+int rec_registered() { return (int)names.size(); }
 const char *rec_name(int i) { return launches[i].name.c_str(); }
 uint32_t rec_grid(int i) { return launches[i].grid; }
 uint64_t rec_dyn(int i) { return launches[i].dyn; }
@@ -120,6 +121,8 @@ env = json.loads(sys.argv[3])
 # loaded first and globally, so that the library's references find it before the real runtime
 rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 lib = ctypes.CDLL(sys.argv[2])
+# the calls below pass addresses that are no device memory: never to a real runtime
+assert rec.rec_registered() > 0, "the library is not bound to the stand-in"
 u32, u64, vp = ctypes.c_uint32, ctypes.c_uint64, ctypes.c_void_p
 rec.rec_name.restype = ctypes.c_char_p
 for f in ("rec_dyn", "rec_arg0", "rec_arg1", "rec_total"):
